@@ -8,6 +8,7 @@
 #include "gap_diag.hpp"
 #include "gap_qtab.hpp"
 #include "gap_protons.hpp"
+#include "gap_fused.hpp"
 
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
@@ -259,6 +260,14 @@ struct gap_t {
   long long* part = nullptr;
   long long* part2 = nullptr;
   unsigned long long* fscan = nullptr;   // single-pass field: 4 words per block, epoch, done count
+  // device words the host reads back at every synchronising call: the sticky
+  // error bits, and each store's chunk count + 1 as its last re-sort left it
+  struct Status { int err, pad; long long chunks[2]; };
+  Status* status = nullptr;
+  // what the last such call found (chunks -1: not known), and the re-sorts
+  // enqueued since
+  int64_t seen_l = -1, seen_p = -1;
+  int rb_seen = 0;
   float* tab = nullptr;
   float* qs = nullptr;     // quantum photon-spectrum table (tubes with GAP_QUANTUM)
   float* qb = nullptr;     // quantum pair-split table
@@ -327,6 +336,7 @@ struct gap_t {
   WinState win;
   hipGraphExec_t gexec = nullptr;
   int64_t gsteps = -1;
+  bool graph_fused = false;   // the captured steps take the fused form
   int gs_l = -1, gs_p = -1, ge_l = -1, ge_p = -1, gs_r = -1, ge_r = -1;
   int64_t gs_since = -1, ge_since = -1, gs_step = -1;
 };
@@ -603,6 +613,7 @@ void rebucket_t(gap_t* g, Store& st, B src, B dst, hipStream_t s) {
   cx.window = g->R;
   cx.tchunk = st.tchunk;
   cx.wh = st.wh;
+  cx.chunks_seen = &g->status->chunks[std::is_same<B, PhoBuf>::value ? 1 : 0];
   cx.n_tiles = g->n_tiles;
   // (the tile and class counts were cleared by rebucket_clear)
   k_rb_count<B><<<kGrid, TPB, 0, s>>>(cx);
@@ -662,6 +673,7 @@ void rebucket_all(gap_t* g) {
     g->pr_cur ^= 1;
   }
   join_stores(g, ps);
+  g->rb_seen = std::min(g->rb_seen + 1, 1 << 20);
 }
 
 // With `done`, the single-pass kernel's own completion is recorded into that
@@ -1083,6 +1095,94 @@ void join_photon_side(gap_t* g) {
   g->s2_pending = false;
 }
 
+// The particle passes of a step in their general form: on two streams, or
+// (two == false) on the caller's.
+void enqueue_passes(gap_t* g, bool two, bool merged) {
+  Ctx cx = make_ctx(g);
+  hipStream_t ps = g->s;
+  if (two) {
+    ps = g->s2;
+    // the previous step's field kernel carries ev_l when nothing came after it
+    if (merged || !g->ev_l_bound) (void)hipEventRecord(g->ev_l, g->s);
+    (void)hipStreamWaitEvent(g->s2, g->ev_l, 0);
+  }
+  g->ev_l_bound = false;
+  {
+    Timer t(g, KT_PRE, ps);
+    if (two) hipExtLaunchKernelGGL(k_pre, dim3(1), dim3(pre_threads(g)), 0, ps, nullptr, g->ev_pre, 0, cx, g->n_tubes);
+    else k_pre<<<1, pre_threads(g), 0, ps>>>(cx, g->n_tubes);
+  }
+  { Timer t(g, KT_PHOTONS, ps); k_photons<<<g->grid_pho, TPB, 0, ps>>>(cx); }
+  { Timer t(g, KT_CONV, ps); launch_conversions(g, cx, ps); }
+  if (two) {
+    (void)hipEventRecord(g->ev_p, g->s2);
+    g->s2_pending = true;
+  }
+  { Timer t(g, KT_LEPTONS); launch_leptons(g, cx, g->s); }
+  if (two) (void)hipStreamWaitEvent(g->s, g->ev_pre, 0);
+  { Timer t(g, KT_TAILS); launch_tails(g, cx, g->s); }
+  if (g->any_protons) {
+    Timer t(g, KT_TAILS);
+    k_protons<<<std::max(8, g->grid_tail), TPB, 0, g->s>>>(cx);
+  }
+}
+
+// The fused form of the particle passes (gap_fused.hpp) is for photon stores
+// of at most this many chunks (1024 slots each).  128 steps of the paper's
+// setup with 1000 to 4000 photon chunks take 7.7 ms in it and 10.6 ms in the
+// general form; 136 steps of the production gap with 13000 take 24.4 and 21.0.
+constexpr int64_t FUSED_PHO_CHUNKS = 4096;
+
+// Whether the next step takes the fused form.  A store's chunk count, read
+// back at every synchronising call, holds until the next re-sort, and is
+// taken as a sign of its size for the period after that; a longer run
+// without such a call may have grown the store, and goes over to the general
+// form.  (No result depends on it.)
+bool fused_form(const gap_t* g) {
+  return !g->timing && g->seen_l >= 0 && g->seen_p >= 0 && g->seen_p <= FUSED_PHO_CHUNKS && g->rb_seen <= 1;
+}
+
+template <bool Q, bool A, int V>
+void launch_fused(gap_t* g, Ctx cx, int gp, int gl, const RestGrid& n) {
+  k_sorted<Q, A, V><<<FUSED_PRE + gp + gl, TPB, 0, g->s>>>(cx, g->n_tubes, gp, gl);
+  k_rest<Q, A, V><<<n.births + n.conv + n.tails + n.protons, TPB, 0, g->s>>>(cx, n);
+}
+
+// The particle passes of one step on the caller's stream.
+void enqueue_fused(gap_t* g) {
+  Ctx cx = make_ctx(g);
+  // Known counts: a workgroup per chunk up to the usual grids, and a store of
+  // fewer chunks than CUs in pieces of a quarter chunk.  Else, and in a graph
+  // that will be replayed on other counts, one resident round.
+  const bool known = g->rb_seen == 0 && !g->capturing;
+  const bool pieces = known && g->seen_l < g->cus && g->seen_p < g->cus;
+  auto grid = [&](int64_t chunks, int most) {
+    if (!known) return most;
+    const int64_t n = (pieces ? PPC : 1) * chunks;
+    return (int)std::max<int64_t>(8, std::min<int64_t>((n + 7) / 8 * 8, most));
+  };
+  const int gl = grid(g->seen_l, g->grid_lep), gp = grid(g->seen_p, std::min(g->grid_pho, g->round_pho));
+  cx.bq_groups = gl;
+  RestGrid n;
+  n.births = std::min(births_wg(g), gl);
+  n.nseg = gp;
+  n.split = known && !pieces ? VEC : 1;
+  n.conv = (gp * n.split + CONV_SEGS - 1) / CONV_SEGS;
+  n.tails = tails_grid(g);
+  n.protons = g->any_protons ? std::max(8, g->grid_tail) : 0;
+  const int form = (g->any_quantum ? 4 : 0) | (g->any_atm ? 2 : 0) | (pieces ? 1 : 0);
+  switch (form) {
+    case 0: launch_fused<false, false, VEC>(g, cx, gp, gl, n); break;
+    case 1: launch_fused<false, false, 1>(g, cx, gp, gl, n); break;
+    case 2: launch_fused<false, true, VEC>(g, cx, gp, gl, n); break;
+    case 3: launch_fused<false, true, 1>(g, cx, gp, gl, n); break;
+    case 4: launch_fused<true, false, VEC>(g, cx, gp, gl, n); break;
+    case 5: launch_fused<true, false, 1>(g, cx, gp, gl, n); break;
+    case 6: launch_fused<true, true, VEC>(g, cx, gp, gl, n); break;
+    default: launch_fused<true, true, 1>(g, cx, gp, gl, n); break;
+  }
+}
+
 // One step.  Photon side (second stream): prologue (injection, lepton tail
 // snapshot, step index), sorted photon pass, conversion draws.  Lepton side
 // (caller's stream): sorted lepton pass, then, once the prologue is done,
@@ -1109,37 +1209,18 @@ void enqueue_step(gap_t* g, bool more) {
     Timer t(g, KT_MERGE);
     merge_all(g);
   }
-  Ctx cx = make_ctx(g);
-  hipStream_t ps = g->s;
-  if (two) {
-    ps = g->s2;
-    // the previous step's field kernel carries ev_l when nothing came after it
-    if (merge || !g->ev_l_bound) (void)hipEventRecord(g->ev_l, g->s);
-    (void)hipStreamWaitEvent(g->s2, g->ev_l, 0);
-  }
-  g->ev_l_bound = false;
-  {
-    Timer t(g, KT_PRE, ps);
-    if (two) hipExtLaunchKernelGGL(k_pre, dim3(1), dim3(pre_threads(g)), 0, ps, nullptr, g->ev_pre, 0, cx, g->n_tubes);
-    else k_pre<<<1, pre_threads(g), 0, ps>>>(cx, g->n_tubes);
-  }
-  { Timer t(g, KT_PHOTONS, ps); k_photons<<<g->grid_pho, TPB, 0, ps>>>(cx); }
-  { Timer t(g, KT_CONV, ps); launch_conversions(g, cx, ps); }
-  if (two) {
-    (void)hipEventRecord(g->ev_p, g->s2);
-    g->s2_pending = true;
-  }
-  { Timer t(g, KT_LEPTONS); launch_leptons(g, cx, g->s); }
-  if (two) (void)hipStreamWaitEvent(g->s, g->ev_pre, 0);
-  { Timer t(g, KT_TAILS); launch_tails(g, cx, g->s); }
-  if (g->any_protons) {
-    Timer t(g, KT_TAILS);
-    k_protons<<<std::max(8, g->grid_tail), TPB, 0, g->s>>>(cx);
+  const bool fused = g->capturing ? g->graph_fused : fused_form(g);
+  if (fused) {
+    if (two) join_photon_side(g);
+    g->ev_l_bound = false;
+    enqueue_fused(g);
+  } else {
+    enqueue_passes(g, two, merge);
   }
   {
     // another step follows at once, with no re-sort or merge in between:
     // its photon side can wait on the field kernel itself
-    const bool bind = two && more && g->since_rb + 1 < g->R &&
+    const bool bind = two && !fused && more && g->since_rb + 1 < g->R &&
                       !(g->merge_on && (g->host_step + 1) % g->merge_every == 0);
     Timer t(g, KT_FIELD);
     g->ev_l_bound = field_pass(g, 0, bind ? g->ev_l : nullptr);
@@ -1158,8 +1239,12 @@ void enqueue_step(gap_t* g, bool more) {
 }
 
 int read_err(gap_t* g) {
-  int e = 0;
-  if (hipMemcpy(&e, g->err, sizeof(int), hipMemcpyDeviceToHost) != hipSuccess) return GAP_EDEVICE;
+  gap_t::Status st{};
+  if (hipMemcpy(&st, g->status, sizeof(st), hipMemcpyDeviceToHost) != hipSuccess) return GAP_EDEVICE;
+  const int e = st.err;
+  g->seen_l = st.chunks[0] - 1;
+  g->seen_p = st.chunks[1] - 1;
+  g->rb_seen = 0;
   if (e & E_TILE) g->sticky = GAP_ETILE;
   else if (e & E_NAN) g->sticky = GAP_ENAN;
   else if (e & E_SCAN) g->sticky = GAP_EDEVICE;
@@ -1348,7 +1433,9 @@ int build(gap_t* g, const gap_params* p, int n_tubes) {
     if (!g->E0 || !g->Du) return GAP_ENOMEM;
   }
   g->tab = (float*)dalloc(g, sizeof(float) * 2 * (NTAB + 1));
-  g->err = (int*)dalloc(g, sizeof(int));
+  g->status = (gap_t::Status*)dalloc(g, sizeof(gap_t::Status));
+  if (!g->status) return GAP_ENOMEM;
+  g->err = &g->status->err;
   g->live = (long long*)dalloc(g, sizeof(long long) * n_tubes);
   g->shard = (long long*)dalloc(g, sizeof(long long) * n_tubes * NSHARD * C_N);
   if (!g->shard) return GAP_ENOMEM;
@@ -1570,6 +1657,7 @@ int export_store(gap_t* g, const Store& st, bool photon, int tube, std::vector<H
 
 int graph_capture(gap_t* g, int64_t n) {
   drop_graph(g);
+  g->graph_fused = fused_form(g);
   g->gs_l = g->lep.cur; g->gs_p = g->pho.cur; g->gs_r = g->pr_cur; g->gs_since = g->since_rb; g->gs_step = g->host_step;
   hipGraph_t graph = nullptr;
   HIPCHK(hipStreamBeginCapture(g->s, hipStreamCaptureModeThreadLocal));
@@ -1745,6 +1833,7 @@ int gap_step_graph(gap_t* g, int64_t n_steps) {
   const bool valid = g->gexec && g->gsteps == n_steps && g->lep.cur == g->gs_l && g->pho.cur == g->gs_p &&
                      g->pr_cur == g->gs_r &&
                      g->since_rb == g->gs_since &&
+                     !(g->graph_fused && g->seen_p > FUSED_PHO_CHUNKS) &&
                      (!g->merge_on || (g->host_step - g->gs_step) % g->merge_every == 0);
   if (!valid) {
     int e = graph_capture(g, n_steps);

@@ -335,13 +335,16 @@ constexpr int PRE_THREADS = 256;
 // except through atomics (the surface charge dq); the photon tail's snapshot
 // is taken by the field scan at the end of the previous step, after every
 // photon birth of that step.
-__global__ __launch_bounds__(PRE_THREADS, 5) void k_pre(Ctx cx, int n_tubes) {
+// A: some tube has a thermal atmosphere.  count_cold: the step's photon pass
+// starts after the prologue, which counts the cold guarantee down for it.
+template <bool A>
+__device__ __forceinline__ void prologue(const Ctx& cx, int n_tubes, bool count_cold) {
   // (appends never leave the tails past the limit; the passes below stay
   // inside the stores whatever the tails hold)
   if (threadIdx.x == 0) {
     clamp_tail(cx.lc);
     cx.lc->tail_pre = cx.lc->tail;
-    if (cx.pc->cold_steps >= 0) cx.pc->cold_steps -= 1;
+    if (count_cold && cx.pc->cold_steps >= 0) cx.pc->cold_steps -= 1;
   }
   __syncthreads();
   const long long S = cx.lc->n_sorted_chunks * CHUNK;
@@ -351,7 +354,7 @@ __global__ __launch_bounds__(PRE_THREADS, 5) void k_pre(Ctx cx, int n_tubes) {
     // the photon passes of this step read its index from step_now: the
     // field update (which counts the step) may run beside them
     T.step_now = T.step;
-    if (T.atm_ppc > 0 && !(T.flags & F_PERIODIC)) atmosphere_refill(cx, T, t, S, lim);
+    if (A && T.atm_ppc > 0 && !(T.flags & F_PERIODIC)) atmosphere_refill(cx, T, t, S, lim);
     if (T.inj_per_step <= 0.0 || (T.flags & F_PERIODIC)) continue;
     T.inj_acc += T.inj_per_step;
     const double fl = floor(T.inj_acc);
@@ -382,6 +385,8 @@ __global__ __launch_bounds__(PRE_THREADS, 5) void k_pre(Ctx cx, int n_tubes) {
     cx.lc->tail_snap = cx.lc->tail;
   }
 }
+
+__global__ __launch_bounds__(PRE_THREADS, 5) void k_pre(Ctx cx, int n_tubes) { prologue<true>(cx, n_tubes, true); }
 
 // ------------------------------------------------------------------ leptons
 // Flush the LDS node-charge window of tile `tile` into the global accumulator.
@@ -762,16 +767,42 @@ __device__ void load_window(const Ctx& cx, int tile, float* s_eb) {
   __syncthreads();
 }
 
-// Records of VEC consecutive slots of a sorted chunk (one thread).
-struct Lep4 { float4 w; uint4 pos; float4 u; int tile; uint32_t slot0; };
+// V consecutive records of one thread in the sorted passes, loaded and stored
+// with one access of 4 V bytes.
+template <class T, int V> struct Rec;
+template <class T> struct Rec<T, 1> { T x; };
+template <> struct Rec<float, 4> { float4 v; };
+template <> struct Rec<uint32_t, 4> { uint4 v; };
+template <> struct Rec<int32_t, 4> { int4 v; };
+template <class T> __device__ __forceinline__ T& rec_first(Rec<T, 1>& r) { return r.x; }
+template <class T> __device__ __forceinline__ T& rec_first(Rec<T, 4>& r) { return r.v.x; }
+// the first record to the end, its place taken by `last`
+template <class T> __device__ __forceinline__ void rec_rotate(Rec<T, 1>& r, T last) { r.x = last; }
+template <class T> __device__ __forceinline__ void rec_rotate(Rec<T, 4>& r, T last) {
+  r.v.x = r.v.y;
+  r.v.y = r.v.z;
+  r.v.z = r.v.w;
+  r.v.w = last;
+}
+template <class T, int V> __device__ __forceinline__ Rec<T, V> rec_load(const T* p) {
+  return *reinterpret_cast<const Rec<T, V>*>(p);
+}
+template <class T, int V> __device__ __forceinline__ void rec_store(T* p, const Rec<T, V>& r) {
+  *reinterpret_cast<Rec<T, V>*>(p) = r;
+}
 
-__device__ __forceinline__ Lep4 lep_load4(const Ctx& cx, long long c) {
-  Lep4 r;
-  r.slot0 = (uint32_t)c * CHUNK + VEC * threadIdx.x;
-  r.tile = cx.lchunk[c];
-  r.w = *reinterpret_cast<const float4*>(cx.L.w + r.slot0);
-  r.pos = *reinterpret_cast<const uint4*>(cx.L.pos + r.slot0);
-  r.u = *reinterpret_cast<const float4*>(cx.L.u + r.slot0);
+// Records of V consecutive slots of a sorted chunk (one thread); c counts
+// pieces of V TPB slots.
+template <int V> struct LepV { Rec<float, V> w; Rec<uint32_t, V> pos; Rec<float, V> u; int tile; uint32_t slot0; };
+
+template <int V>
+__device__ __forceinline__ LepV<V> lep_load(const Ctx& cx, long long c) {
+  LepV<V> r;
+  r.slot0 = (uint32_t)c * (V * TPB) + V * threadIdx.x;
+  r.tile = cx.lchunk[V == VEC ? c : c / (VEC / V)];
+  r.w = rec_load<float, V>(cx.L.w + r.slot0);
+  r.pos = rec_load<uint32_t, V>(cx.L.pos + r.slot0);
+  r.u = rec_load<float, V>(cx.L.u + r.slot0);
   return r;
 }
 
@@ -794,10 +825,12 @@ __device__ __forceinline__ void piece_slot(long long q, long long nsq, long long
 // and the next chunk's records are prefetched while the current one is
 // pushed.  The chunk's tile constants sit in scalar registers; gather and
 // deposit go through an LDS window of the tile.
-// (six waves per SIMD: the register cap spills one value, stored once on
-// entry and reloaded once per chunk)
-template <bool Q, bool A>
-__global__ __launch_bounds__(TPB, 6) void k_leptons(Ctx cx) {
+// V: slots per thread and piece.  VEC is the general form; 1 (a quarter of a
+// chunk per workgroup and iteration) gives a small store four times the
+// workgroups and a quarter of the serial work of each.
+template <bool Q, bool A, int V>
+__device__ __forceinline__ void leptons_sorted(const Ctx& cx, int bx, int G) {
+  constexpr int U = V * TPB;
   const Room proom = load_room(cx.pc);
   __shared__ long long s_rho[WIN + 2];
   __shared__ float s_eb[WIN + 2];
@@ -806,20 +839,25 @@ __global__ __launch_bounds__(TPB, 6) void k_leptons(Ctx cx) {
   lcn.clear();
   __shared__ int s_bqn;        // photon births queued by this workgroup
   int ctube = -1;
+  const long long nsc = cx.lc->n_sorted_chunks * (CHUNK / U);
+  const int r = (bx & 7) * (G >> 3) + (bx >> 3);
+  const long long c0 = nsc * r / G, c1 = nsc * (r + 1) / G;
+  if (c0 >= c1) {              // no chunk for this workgroup
+    if (threadIdx.x == 0) {
+      cx.bq_count[bx] = 0;
+      cx.bq_start[bx] = 0;
+    }
+    return;
+  }
   for (int j = threadIdx.x; j < WIN + 2; j += blockDim.x) s_rho[j] = 0;
   if (threadIdx.x == 0) s_bqn = 0;
   __syncthreads();
-  const long long nsc = cx.lc->n_sorted_chunks;
-  const int G = gridDim.x, bx = blockIdx.x;
-  const int r = (bx & 7) * (G >> 3) + (bx >> 3);
-  const long long c0 = nsc * r / G, c1 = nsc * (r + 1) / G;
   int held = -1;
   KC kc;
-  Lep4 cur;
-  if (c0 < c1) cur = lep_load4(cx, c0);
+  LepV<V> cur = lep_load<V>(cx, c0);
   for (long long c = c0; c < c1; ++c) {
-    Lep4 nxt;
-    if (c + 1 < c1) nxt = lep_load4(cx, c + 1);
+    LepV<V> nxt;
+    if (c + 1 < c1) nxt = lep_load<V>(cx, c + 1);
     const int tile = cur.tile;
     if (tile != held) {
       if (held >= 0) flush_window(cx, held, s_rho);
@@ -831,29 +869,38 @@ __global__ __launch_bounds__(TPB, 6) void k_leptons(Ctx cx) {
       }
       load_window(cx, tile, s_eb);
     }
-    float4 w = cur.w, u = cur.u;
-    uint4 p = cur.pos;
-    // one body, four records: process .x, write the result into .x, rotate
+    Rec<float, V> w = cur.w, u = cur.u;
+    Rec<uint32_t, V> p = cur.pos;
+    // one body, V records: process the first, write the result into its
+    // place, rotate
 #pragma unroll 1
-    for (int j = 0; j < VEC; ++j) {
+    for (int j = 0; j < V; ++j) {
       uint32_t po;
       float uo;
-      lepton_one<true, Q, A>(cx, cur.slot0 + j, tile, kc, s_rho, s_eb, lcn, w.x, p.x, u.x, &po, &uo, proom, &s_bqn, c0 * CHUNK);
-      w = make_float4(w.y, w.z, w.w, w.x);
-      p = make_uint4(p.y, p.z, p.w, po);
-      u = make_float4(u.y, u.z, u.w, uo);
+      lepton_one<true, Q, A>(cx, cur.slot0 + j, tile, kc, s_rho, s_eb, lcn, rec_first(w), rec_first(p), rec_first(u), &po,
+                             &uo, proom, &s_bqn, c0 * U);
+      rec_rotate(w, rec_first(w));
+      rec_rotate(p, po);
+      rec_rotate(u, uo);
     }
-    *reinterpret_cast<uint4*>(cx.L.pos + cur.slot0) = p;
-    *reinterpret_cast<float4*>(cx.L.u + cur.slot0) = u;
+    rec_store<uint32_t, V>(cx.L.pos + cur.slot0, p);
+    rec_store<float, V>(cx.L.u + cur.slot0, u);
     cur = nxt;
   }
-  if (held >= 0) flush_window(cx, held, s_rho);
-  if (ctube >= 0) flush_counts<0>(cx.shard, ctube, lcn, s_cnt);
+  flush_window(cx, held, s_rho);
+  flush_counts<0>(cx.shard, ctube, lcn, s_cnt);
   // (flush_counts ends with a barrier: every wave has queued its births)
   if (threadIdx.x == 0) {
-    cx.bq_count[blockIdx.x] = c0 < c1 ? s_bqn : 0;
-    cx.bq_start[blockIdx.x] = c0 * CHUNK;
+    cx.bq_count[bx] = s_bqn;
+    cx.bq_start[bx] = c0 * U;
   }
+}
+
+// (six waves per SIMD: the register cap spills one value, stored once on
+// entry and reloaded once per chunk)
+template <bool Q, bool A>
+__global__ __launch_bounds__(TPB, 6) void k_leptons(Ctx cx) {
+  leptons_sorted<Q, A, VEC>(cx, blockIdx.x, gridDim.x);
 }
 
 // Lepton pass over the tail (particles appended since the last re-sort):
@@ -1007,19 +1054,24 @@ __device__ void photon_one(const Ctx& cx, uint32_t slot, int tile, const KC& ku,
   }
 }
 
-struct Pho4 { float4 x; uint4 pos; int4 n0; int tile; int hot; uint32_t slot0; };
+template <int V> struct PhoV { Rec<float, V> x; Rec<uint32_t, V> pos; Rec<int32_t, V> n0; int tile; int hot; uint32_t slot0; };
 
-// One chunk's records for this thread.  hot: the chunk's leading slots that
-// may draw (all of them without the re-sort's guarantee); a chunk with none
-// does not need the birth steps.
-__device__ __forceinline__ Pho4 pho_load4(const Ctx& cx, long long c, bool cold_ok) {
-  Pho4 r;
-  r.slot0 = (uint32_t)c * CHUNK + VEC * threadIdx.x;
-  r.tile = cx.pchunk[c];
-  r.hot = cold_ok ? (int)cx.pchot[c] : CHUNK;
-  r.x = *reinterpret_cast<const float4*>(cx.P.x + r.slot0);
-  r.pos = *reinterpret_cast<const uint4*>(cx.P.pos + r.slot0);
-  r.n0 = r.hot > 0 ? *reinterpret_cast<const int4*>(cx.P.n0 + r.slot0) : make_int4(0, 0, 0, 0);
+// The records of V consecutive slots of a sorted chunk for this thread (c
+// counts pieces of V TPB slots).  hot: the piece's leading slots that may
+// draw (all of them without the re-sort's guarantee); a piece with none does
+// not need the birth steps.
+template <int V>
+__device__ __forceinline__ PhoV<V> pho_load(const Ctx& cx, long long c, bool cold_ok) {
+  constexpr int U = V * TPB;
+  PhoV<V> r;
+  r.slot0 = (uint32_t)c * U + V * threadIdx.x;
+  const long long ch = V == VEC ? c : c / (VEC / V);
+  r.tile = cx.pchunk[ch];
+  r.hot = cold_ok ? (int)cx.pchot[ch] - (V == VEC ? 0 : (int)(c & (VEC / V - 1)) * U) : U;
+  r.x = rec_load<float, V>(cx.P.x + r.slot0);
+  r.pos = rec_load<uint32_t, V>(cx.P.pos + r.slot0);
+  if (r.hot > 0) r.n0 = rec_load<int32_t, V>(cx.P.n0 + r.slot0);
+  else r.n0 = Rec<int32_t, V>{};
   return r;
 }
 
@@ -1081,44 +1133,53 @@ __device__ __forceinline__ void chunk_range(long long nsc, int G, int bx, long l
 // per slot of its range, so the segment cannot overflow), and the
 // conversion kernel works through the queue.  No barrier stands between
 // chunks.
-__global__ __launch_bounds__(TPB) void k_photons(Ctx cx) {
+// FUSED: in one launch with the step's prologue, which may not have run yet:
+// the step index is the tubes' own, and the cold guarantee is not yet counted
+// down.
+template <int V, bool FUSED>
+__device__ __forceinline__ void photons_sorted(const Ctx& cx, int bx, int G) {
+  constexpr int U = V * TPB;
   long long c0, c1;
-  chunk_range(cx.pc->n_sorted_chunks, gridDim.x, blockIdx.x, &c0, &c1);
+  chunk_range(cx.pc->n_sorted_chunks * (CHUNK / U), G, bx, &c0, &c1);
   __shared__ long long s_cnt[8];
   __shared__ int q_n;
+  if (c0 >= c1) {              // no chunk for this workgroup
+    if (threadIdx.x == 0) cx.pq_count[bx] = 0;
+    return;
+  }
   if (threadIdx.x == 0) q_n = 0;
   __syncthreads();
-  uint4* const q = cx.pq + c0 * CHUNK;
+  uint4* const q = cx.pq + c0 * U;
   LocalCounts lcn;
   lcn.clear();
   int ctube = -1;
   KC kc;
   int held = -1;
-  const bool cold_ok = cx.pc->cold_steps >= 0;
-  Pho4 cur;
-  if (c0 < c1) cur = pho_load4(cx, c0, cold_ok);
+  const bool cold_ok = cx.pc->cold_steps >= (FUSED ? 1 : 0);
+  PhoV<V> cur = pho_load<V>(cx, c0, cold_ok);
   for (long long c = c0; c < c1; ++c) {
-    Pho4 nxt;
-    if (c + 1 < c1) nxt = pho_load4(cx, c + 1, cold_ok);
+    PhoV<V> nxt;
+    if (c + 1 < c1) nxt = pho_load<V>(cx, c + 1, cold_ok);
     if (cur.tile != held) {
       held = cur.tile;
-      kc = load_kc(cx, held, true);
+      kc = load_kc(cx, held, !FUSED);
       if (kc.tube != ctube) {
         if (ctube >= 0) flush_counts<1>(cx.shard, ctube, lcn, s_cnt);
         ctube = kc.tube;
       }
     }
-    float4 x = cur.x;
+    Rec<float, V> x = cur.x;
     bool xchg = false;
-    uint4 p = cur.pos;
-    int4 n0 = cur.n0;
+    Rec<uint32_t, V> p = cur.pos;
+    Rec<int32_t, V> n0 = cur.n0;
 #pragma unroll 1
-    for (int j = 0; j < VEC; ++j) {
+    for (int j = 0; j < V; ++j) {
       uint32_t po;
       float xo, pr;
       bool ev;
-      photon_move(cx, kc, x.x, p.x, n0.x, (int)(VEC * threadIdx.x) + j < cur.hot, lcn, &po, &xo, &pr, &ev);
-      xchg |= xo != x.x;
+      photon_move(cx, kc, rec_first(x), rec_first(p), rec_first(n0), (int)(V * threadIdx.x) + j < cur.hot, lcn, &po, &xo,
+                  &pr, &ev);
+      xchg |= xo != rec_first(x);
       const uint64_t m = __ballot(ev);
       if (m) {
         int base = 0;
@@ -1126,18 +1187,20 @@ __global__ __launch_bounds__(TPB) void k_photons(Ctx cx) {
         base = __shfl(base, 0);
         if (ev) q[base + rank_in(m)] = make_uint4(cur.slot0 + j, __float_as_uint(pr), (uint32_t)held, (uint32_t)kc.tube);
       }
-      x = make_float4(x.y, x.z, x.w, xo);
-      p = make_uint4(p.y, p.z, p.w, po);
-      n0 = make_int4(n0.y, n0.z, n0.w, n0.x);
+      rec_rotate(x, xo);
+      rec_rotate(p, po);
+      rec_rotate(n0, rec_first(n0));
     }
-    *reinterpret_cast<uint4*>(cx.P.pos + cur.slot0) = p;
-    if (xchg) *reinterpret_cast<float4*>(cx.P.x + cur.slot0) = x;   // only when a photon left
+    rec_store<uint32_t, V>(cx.P.pos + cur.slot0, p);
+    if (xchg) rec_store<float, V>(cx.P.x + cur.slot0, x);   // only when a photon left
     cur = nxt;
   }
-  if (ctube >= 0) flush_counts<1>(cx.shard, ctube, lcn, s_cnt);
+  flush_counts<1>(cx.shard, ctube, lcn, s_cnt);
   __syncthreads();
-  if (threadIdx.x == 0) cx.pq_count[blockIdx.x] = q_n;
+  if (threadIdx.x == 0) cx.pq_count[bx] = q_n;
 }
+
+__global__ __launch_bounds__(TPB) void k_photons(Ctx cx) { photons_sorted<VEC, false>(cx, blockIdx.x, gridDim.x); }
 
 // Photon pass, second kernel: the conversion draws of the queued photons and
 // the pairs they create: e- and e+ at the photon's new position, gamma = x/2
@@ -1163,10 +1226,13 @@ constexpr int CONV_SEGS = 2;
 // step about a millisecond.)
 constexpr int PAIR_BLOCK_MAX = 128;
 
-template <bool Q>
-__global__ __launch_bounds__(TPB) void k_conversions(Ctx cx, int nseg, int split) {
+// V: the photon pass's slots per thread and piece (its ranges are in pieces
+// of V TPB slots).
+template <bool Q, int V>
+__device__ __forceinline__ void conversions(const Ctx& cx, int bx, int nseg, int split) {
+  constexpr int U = V * TPB;
   const Room lroom = load_room(cx.lc);
-  const long long nsc = cx.pc->n_sorted_chunks;
+  const long long nsc = cx.pc->n_sorted_chunks * (CHUNK / U);
   __shared__ long long s_blk[TPB / WAVE][3];    // per wave: next slot, block end, next block size
   long long* blk = s_blk[threadIdx.x / WAVE];
   if (lane_id() == 0) { blk[0] = 0; blk[1] = 0; blk[2] = 2; }
@@ -1175,7 +1241,7 @@ __global__ __launch_bounds__(TPB) void k_conversions(Ctx cx, int nseg, int split
   int nmax = 0;
 #pragma unroll
   for (int j = 0; j < CONV_SEGS; ++j) {
-    const int v = (int)blockIdx.x * CONV_SEGS + j;
+    const int v = bx * CONV_SEGS + j;
     const int sg = v / split;
     long long c0 = 0, c1 = 0;
     n[j] = 0;
@@ -1185,7 +1251,7 @@ __global__ __launch_bounds__(TPB) void k_conversions(Ctx cx, int nseg, int split
     }
     // rounds part, part + split, ... of the segment
     const int part = v - sg * split;
-    q0[j] = c0 * CHUNK + (long long)part * TPB;
+    q0[j] = c0 * U + (long long)part * TPB;
     n[j] -= part * TPB;
     nmax = max(nmax, n[j]);
   }
@@ -1282,6 +1348,11 @@ __global__ __launch_bounds__(TPB) void k_conversions(Ctx cx, int nseg, int split
     cx.L.id[s32] = 0;
     cx.ltt[s32] = 0;
   }
+}
+
+template <bool Q>
+__global__ __launch_bounds__(TPB) void k_conversions(Ctx cx, int nseg, int split) {
+  conversions<Q, VEC>(cx, (int)blockIdx.x, nseg, split);
 }
 
 template <bool Q>
@@ -1429,16 +1500,17 @@ __device__ __forceinline__ void births_queue(const Ctx& cx, int b0, int nb) {
 // go past the photon tail's snapshot, like every birth of the step): their
 // chain of dependent loads then runs beside the tail passes.
 template <bool Q, bool A>
-__global__ __launch_bounds__(TPB) void k_tails(Ctx cx, int bq_wg) {
-  if ((int)blockIdx.x < bq_wg) {
-    births_queue<Q>(cx, (int)blockIdx.x, bq_wg);
-    return;
-  }
-  const int bx = (int)blockIdx.x - bq_wg;
+__device__ __forceinline__ void both_tails(const Ctx& cx, int bx, int grid) {
   const int bid = ((bx >> 4) << 3) | (bx & 7);
-  const int nblk = ((int)gridDim.x - bq_wg) >> 1;
+  const int nblk = grid >> 1;
   if ((bx >> 3) & 1) photons_tail<Q>(cx, bid, nblk);
   else leptons_tail<Q, A>(cx, bid, nblk);
+}
+
+template <bool Q, bool A>
+__global__ __launch_bounds__(TPB) void k_tails(Ctx cx, int bq_wg) {
+  if ((int)blockIdx.x < bq_wg) births_queue<Q>(cx, (int)blockIdx.x, bq_wg);
+  else both_tails<Q, A>(cx, (int)blockIdx.x - bq_wg, (int)gridDim.x - bq_wg);
 }
 
 // ------------------------------------------------------------------ field
@@ -1903,6 +1975,7 @@ struct RbCtx {
   uint8_t* cls;          // per source slot: the class the count kernel decided
   uint16_t* chot;        // photons, per chunk of the new layout: class-0 slots at its start
   int window;            // steps until the next re-sort
+  long long* chunks_seen;  // the new layout's chunk count + 1, for the host
   long long* tchunk;     // first chunk of each tile in the new layout (n_tiles + 1)
   int32_t* wh;           // [grid][RB_HW][N]: each count workgroup's window counts by tile and class
   int n_tiles;
@@ -2258,6 +2331,7 @@ __global__ void k_rb_finish(RbCtx<B> cx) {
     cx.ctl->tail = 0;
     cx.ctl->tail_snap = 0;
     cx.ctl->cold_steps = cx.chot ? cx.window : -1;
+    *cx.chunks_seen = cx.ctl->total_chunks_new + 1;
   }
 }
 

@@ -13,9 +13,9 @@ namespace gap {
 // 2^-24 fixed point as the leptons, absorption at h = 0 (the charge returns
 // to the star), free outflow at h = L, deposit of the first-order split.
 // Protons left in cell 0 are counted for the atmosphere refill.
-__global__ __launch_bounds__(TPB) void k_protons(Ctx cx) {
+__device__ __forceinline__ void protons_pass(const Ctx& cx, int bx, int nblk) {
   const long long n = min(*cx.pr_n, cx.pr_cap);
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
+  for (long long i = (long long)bx * TPB + threadIdx.x; i < n; i += (long long)nblk * TPB) {
     const float w = cx.R.w[i];
     if (w == 0.0f) continue;
     const int t = cx.R.tube[i];
@@ -58,6 +58,8 @@ __global__ __launch_bounds__(TPB) void k_protons(Ctx cx) {
     cx.R.u[i] = u;
   }
 }
+
+__global__ __launch_bounds__(TPB) void k_protons(Ctx cx) { protons_pass(cx, (int)blockIdx.x, (int)gridDim.x); }
 
 // Charge of every live proton into rho (initial field, loaded states).
 __global__ __launch_bounds__(TPB) void k_deposit_protons(Ctx cx) {
