@@ -245,9 +245,11 @@ struct gap_t {
   std::vector<Derived> D;
   std::vector<Tube> th;
   std::vector<Tile> tiles_h;
+  std::vector<LTile> ltiles_h;
   std::vector<FBlk> fb_h;
   Tube* tubes = nullptr;
   Tile* tiles = nullptr;
+  LTile* ltiles = nullptr;
   int n_tiles = 0;
   long long total_nodes = 0, total_cells = 0;
   int max_cells = 1;   // largest tube
@@ -506,6 +508,7 @@ Ctx make_ctx(gap_t* g) {
   Ctx c;
   c.tubes = g->tubes;
   c.tiles = g->tiles;
+  c.ltiles = g->ltiles;
   c.L = g->lep.lep(g->lep.cur);
   c.lc = g->lep.ctl;
   c.lchunk = g->lep.chunk[g->lep.cur];
@@ -1309,6 +1312,38 @@ int download_tubes(gap_t* g) {
   return from_hip(hipMemcpy(g->th.data(), g->tubes, sizeof(Tube) * g->n_tubes, hipMemcpyDeviceToHost));
 }
 
+// The sorted lepton pass's constants of one tile.
+LTile lepton_tile(const Tube& T, const Tile& tl, double xc_floor) {
+  LTile k{};
+  k.tube = tl.tube;
+  k.base = tl.base;
+  k.N = T.N;
+  k.node_off = T.node_off;
+  k.flags = (uint32_t)T.flags;
+  const bool per = (T.flags & GAP_PERIODIC) != 0;
+  const int64_t b0 = (int64_t)tl.base * (1 << FRAC), last = 0xFFFFFFFFll;
+  k.xlo = per || tl.base >= 0 ? 0u : (uint32_t)(-b0);
+  k.xtop = (uint32_t)(per ? last : std::min(((int64_t)T.N << FRAC) - b0 - 1, last));
+  const int64_t z = T.hfix - b0 - 1;      // last offset inside the QED zone
+  k.zone = per || z >= 0;
+  k.ztop = (uint32_t)(per ? last : std::max(std::min(z, last), (int64_t)0));
+  k.dt = T.dt;
+  k.cfl24 = T.cfl24;
+  k.lr = T.lr;
+  k.emit_k = T.emit_k;
+  k.xc_floor = T.xc_floor;
+  k.x_thr = T.x_thr;
+  // x_c = 1.5 gamma^3 lambda~/R~ reaches the floor at this gamma; one per
+  // cent under its momentum x_c is at least 0.5 % under the floor (from
+  // gamma = 1.1 on), far beyond the rounding of the passes' FP32 x_c
+  const double gf = std::cbrt(xc_floor / (1.5 * (double)T.lr));
+  k.u_skip = gf > 1.1 ? (float)(0.99 * std::sqrt(gf * gf - 1.0)) : 0.0f;
+  k.nsub_max = T.nsub_max;
+  k.hfix = T.hfix;
+  k.seed = T.seed;
+  return k;
+}
+
 int build(gap_t* g, const gap_params* p, int n_tubes) {
   g->n_tubes = n_tubes;
   g->P.assign(p, p + n_tubes);
@@ -1372,6 +1407,7 @@ int build(gap_t* g, const gap_params* p, int n_tubes) {
       tl.base = tl.first - MARGIN;
       tl.ncell = std::min(TILE, q.n_cells - tl.first);
       g->tiles_h.push_back(tl);
+      g->ltiles_h.push_back(lepton_tile(T, tl, q.xc_floor));
     }
     const int nb = (q.n_cells + FB_NODES - 1) / FB_NODES;
     const int first = (int)g->fb_h.size();
@@ -1419,6 +1455,8 @@ int build(gap_t* g, const gap_params* p, int n_tubes) {
 
   g->tubes = (Tube*)dalloc(g, sizeof(Tube) * n_tubes);
   g->tiles = (Tile*)dalloc(g, sizeof(Tile) * g->n_tiles);
+  g->ltiles = (LTile*)dalloc(g, sizeof(LTile) * g->n_tiles);
+  if (!g->ltiles) return GAP_ENOMEM;
   g->rho = (long long*)dalloc(g, sizeof(long long) * g->total_nodes);
   g->rho_last = (long long*)dalloc(g, sizeof(long long) * g->total_nodes);
   g->E = (float*)dalloc(g, sizeof(float) * g->total_cells);
@@ -1534,6 +1572,7 @@ int build(gap_t* g, const gap_params* p, int n_tubes) {
   HIPCHK(hipStreamSynchronize(g->s));
   if ((e = upload_tubes(g))) return e;
   HIPCHK(hipMemcpy(g->tiles, g->tiles_h.data(), sizeof(Tile) * g->n_tiles, hipMemcpyHostToDevice));
+  HIPCHK(hipMemcpy(g->ltiles, g->ltiles_h.data(), sizeof(LTile) * g->n_tiles, hipMemcpyHostToDevice));
   HIPCHK(hipMemcpy(g->fb, g->fb_h.data(), sizeof(FBlk) * g->n_fb, hipMemcpyHostToDevice));
   const std::vector<float>& tab = sync_table();
   HIPCHK(hipMemcpy(g->tab, tab.data(), sizeof(float) * tab.size(), hipMemcpyHostToDevice));

@@ -94,6 +94,28 @@ struct Tile {
   int32_t tube, first, base, ncell;   // base = first - MARGIN (tube-local cells)
 };
 
+// Constants of one tile and its tube for the sorted lepton pass, laid out at
+// initialisation.  Positions are 32-bit offsets from the window base, and so
+// are the limits: a new position below xlo (the surface) or above xtop (the
+// top of the box) has left a non-periodic tube, and one at or below ztop is
+// inside the QED zone (zone: some offset is).  u_skip: leptons of smaller |u|
+// are below xc_floor.
+struct LTile {
+  int32_t tube, base, N, node_off;
+  uint32_t flags, xlo, xtop, ztop;
+  float dt, cfl24, lr, emit_k;
+  float xc_floor, x_thr, u_skip;
+  int32_t nsub_max;
+  int64_t hfix;
+  uint64_t seed;
+  int32_t zone, pad;
+};
+
+// A pointer to memory that no kernel of the launch writes: uniform reads
+// through it are scalar loads.
+template <class T> using CPtr = const T __attribute__((address_space(4)))*;
+template <class T> __device__ __forceinline__ CPtr<T> cptr(const T* p) { return (CPtr<T>)p; }
+
 struct Ctl {                  // control block of one store
   int64_t n_sorted_chunks;    // sorted region = slots [0, CHUNK * n_sorted_chunks)
   int64_t tail;               // tail length (slots after the sorted region)

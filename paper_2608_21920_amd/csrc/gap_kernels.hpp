@@ -10,6 +10,7 @@ namespace gap {
 struct Ctx {
   Tube* tubes;
   const Tile* tiles;
+  const LTile* ltiles;
   // lepton store (current buffers)
   LepBuf L;
   Ctl* lc;
@@ -389,28 +390,6 @@ __device__ __forceinline__ void prologue(const Ctx& cx, int n_tubes, bool count_
 __global__ __launch_bounds__(PRE_THREADS, 5) void k_pre(Ctx cx, int n_tubes) { prologue<true>(cx, n_tubes, true); }
 
 // ------------------------------------------------------------------ leptons
-// Flush the LDS node-charge window of tile `tile` into the global accumulator.
-__device__ void flush_window(const Ctx& cx, int tile, long long* s_rho) {
-  __syncthreads();
-  const Tile tl = cx.tiles[tile];
-  const Tube& T = cx.tubes[tl.tube];
-  const bool per = (T.flags & F_PERIODIC) != 0;
-  for (int j = threadIdx.x; j <= WIN; j += blockDim.x) {
-    long long v = s_rho[j];
-    if (v != 0) {
-      int node = tl.base + j;
-      if (per) node = wrap_cell(node, T.N);
-      atomicAdd((unsigned long long*)&cx.rho[T.node_off + node], (unsigned long long)v);
-      s_rho[j] = 0;
-    }
-  }
-  if (per && threadIdx.x == 0) {   // the wave sums of the current, past the window's nodes
-    atomic_add_i64(&cx.tubes[tl.tube].dcur, s_rho[WIN + 1]);
-    s_rho[WIN + 1] = 0;
-  }
-  __syncthreads();
-}
-
 // Constants of one tile and its tube, read once per tile switch and held in
 // scalar registers (the tube records are also written by the kernels, so the
 // compiler cannot turn per-lane reads of them into scalar loads).
@@ -562,24 +541,32 @@ __device__ __forceinline__ void queue_births(const Ctx& cx, int* s_bqn, long lon
                                                          (uint32_t)(evmask >> 32));
 }
 
-// One lepton: gather, kick, emission (Monte Carlo with recoil), drift,
-// boundaries, deposit, photon births.  UNI: the lane's tile is the
-// wave-uniform tile of a sorted chunk (tube constants come through scalar
-// loads, gather and deposit go through the LDS window); otherwise the lane's
-// own tile (tail) with global memory.  `tile` < 0: no particle in this lane.
-template <bool UNI, bool Q, bool A>
-__device__ void lepton_one(const Ctx& cx, uint32_t slot, int tile, const KC& ku, long long* s_rho, const float* s_eb,
-                           LocalCounts& lcn, float w, uint32_t pos, float u, uint32_t* pos_out, float* u_out,
-                           const Room& proom, int* s_bqn, long long seg0) {
-  bool alive;
-  KC k;
-  if (UNI) {
-    k = ku;
-    alive = w != 0.0f;
-  } else {
-    alive = tile >= 0 && w != 0.0f;
-    k = lane_kc(cx, alive ? tile : 0, false);   // tile 0 always exists; no branch on the struct
-  }
+// The kick, the optical depth and sub-step count of an emission evaluation and
+// the drift, with explicit roundings: the sorted and the tail pass agree bit
+// for bit.  (1 - xi is exact.)
+__device__ __forceinline__ float kicked(float u, float sg, float xi, float e0, float e1, float dt) {
+  const float e = __fmaf_rn(xi, e1, __fmul_rn(1.0f - xi, e0));
+  return __fmaf_rn(dt, __fmul_rn(sg, e), u);
+}
+__device__ __forceinline__ float emit_dtau(float emit_k, float g, float chi) {
+  return __fmul_rn(__fmul_rn(emit_k, g), t_syn(chi));
+}
+__device__ __forceinline__ int emit_nsub(float dtau, int most) {
+  return max(1, min((int)ceilf(__fmul_rn(dtau, 10.0f)), most));
+}
+__device__ __forceinline__ int drift_fix(float u, float cfl24) {
+  return __float2int_rn(__fmul_rn(cfl24, __fmul_rn(u, __builtin_amdgcn_rsqf(__fmaf_rn(u, u, 1.0f)))));
+}
+
+// One lepton of the tail: gather, kick, emission (Monte Carlo with recoil),
+// drift, boundaries, deposit, photon births, with the lane's own tile and
+// global memory.  `tile` < 0: no particle in this lane.  The sorted pass
+// (leptons_sorted) does the same arithmetic with the same roundings.
+template <bool Q, bool A>
+__device__ void lepton_one(const Ctx& cx, uint32_t slot, int tile, LocalCounts& lcn, float w, uint32_t pos, float u,
+                           const Room& proom) {
+  const bool alive = tile >= 0 && w != 0.0f;
+  const KC k = lane_kc(cx, alive ? tile : 0, false);   // tile 0 always exists; no branch on the struct
   if (!alive) { pos = 0; u = 0.0f; }
   const int tube = alive ? k.tube : -1;
   const int N = k.N;
@@ -596,11 +583,11 @@ __device__ void lepton_one(const Ctx& cx, uint32_t slot, int tile, const KC& ku,
   const float xi = (float)frac * 5.9604645e-8f;
   float e0 = 0.0f, e1 = 0.0f;
   if (alive) {
-    if (UNI) { e0 = s_eb[off]; e1 = s_eb[off + 1]; }
-    else { e0 = cx.ebar[k.node_off + cg]; e1 = cx.ebar[k.node_off + cg + 1]; }
+    e0 = cx.ebar[k.node_off + cg];
+    e1 = cx.ebar[k.node_off + cg + 1];
   }
   const float sg = w < 0.0f ? -1.0f : 1.0f;
-  u += sg * ((1.0f - xi) * e0 + xi * e1) * k.dt;
+  u = kicked(u, sg, xi, e0, e1, k.dt);
 
   // curvature emission: rate alpha_em gamma/R~ T_syn(chi), chi = gamma^2 lambda~/R~,
   // photon energy xi_s x_c with x_c = 1.5 gamma chi, QED zone h < H
@@ -616,9 +603,8 @@ __device__ void lepton_one(const Ctx& cx, uint32_t slot, int tile, const KC& ku,
     if (xc >= k.xc_floor) {
       eval = true;
       id = cx.L.id[slot];
-      const float dtau = k.emit_k * g * t_syn(chi);
-      int nsub = (int)ceilf(dtau * 10.0f);
-      nsub = max(1, min(nsub, k.nsub_max));
+      const float dtau = emit_dtau(k.emit_k, g, chi);
+      const int nsub = emit_nsub(dtau, k.nsub_max);
       const float p = one_minus_exp_neg(dtau / (float)nsub);
       float au = fabsf(u);
       for (int j = 0; j < nsub; ++j) {
@@ -636,7 +622,7 @@ __device__ void lepton_one(const Ctx& cx, uint32_t slot, int tile, const KC& ku,
   }
 
   // drift: dh/dt = u / gamma, in fixed point
-  const int dfix = __float2int_rn(u * __builtin_amdgcn_rsqf(1.0f + u * u) * k.cfl24);
+  const int dfix = drift_fix(u, k.cfl24);
   const long long npl = (long long)pos + dfix;
   const int noff = (int)(npl >> FRAC);
   const uint32_t nfrac = (uint32_t)npl & 0xFFFFFFu;
@@ -650,10 +636,7 @@ __device__ void lepton_one(const Ctx& cx, uint32_t slot, int tile, const KC& ku,
     else if (ncell >= N) { outflow = true; dead = true; }
   }
   if (alive && dead) cx.L.w[slot] = 0.0f;
-  if (UNI) {           // the caller stores the chunk's records with vector stores
-    *pos_out = (uint32_t)npl;
-    *u_out = u;
-  } else if (alive && !dead) {
+  if (alive && !dead) {
     cx.L.pos[slot] = (uint32_t)npl;
     cx.L.u[slot] = u;
   }
@@ -661,16 +644,7 @@ __device__ void lepton_one(const Ctx& cx, uint32_t slot, int tile, const KC& ku,
     atomic_add_i64(&cx.tubes[tube].dq, sg > 0 ? Tw : -Tw);
     return_add(cx.ret, cx.ret_thr, tube, u, w);
   }
-  // Periodic tubes: the current.  One add per wave, into LDS for a sorted
-  // chunk (flushed with its node-charge window): every lepton adds to the one
-  // word of its tube, and such atomics are served one at a time (one per
-  // lepton made a step of 48 000 leptons take 0.61 ms; 0.052 ms now).
-  if (UNI) {
-    if (per) {
-      const long long c = wave_sum_ll((alive && !dead) ? (sg > 0 ? Tw : -Tw) * (int64_t)dfix : 0);
-      if (lane_id() == 0 && c != 0) atomicAdd((unsigned long long*)&s_rho[WIN + 1], (unsigned long long)c);
-    }
-  } else if (__ballot(per)) {
+  if (__ballot(per)) {   // the current (see leptons_sorted), one add per wave and tube
     const bool has = per && alive && !dead;
     add_by_tube(cx.tubes, has ? tube : -1, has ? (sg > 0 ? Tw : -Tw) * (int64_t)dfix : 0);
   }
@@ -684,23 +658,16 @@ __device__ void lepton_one(const Ctx& cx, uint32_t slot, int tile, const KC& ku,
     const unsigned long long Au = ((unsigned long long)Tw * nfrac + (1ull << 23)) >> FRAC;
     const long long a = sg > 0 ? (long long)Au : -(long long)Au;
     const long long ta = sg > 0 ? (long long)(Tw - (int64_t)Au) : -(long long)(Tw - (int64_t)Au);
-    if (UNI) {
-      atomicAdd((unsigned long long*)&s_rho[noff], (unsigned long long)ta);
-      atomicAdd((unsigned long long*)&s_rho[noff + 1], (unsigned long long)a);
-    } else {
-      int n1 = ncg + 1;
-      if (per && n1 == N) n1 = 0;
-      atomicAdd((unsigned long long*)&cx.rho[k.node_off + ncg], (unsigned long long)ta);
-      atomicAdd((unsigned long long*)&cx.rho[k.node_off + n1], (unsigned long long)a);
-    }
+    int n1 = ncg + 1;
+    if (per && n1 == N) n1 = 0;
+    atomicAdd((unsigned long long*)&cx.rho[k.node_off + ncg], (unsigned long long)ta);
+    atomicAdd((unsigned long long*)&cx.rho[k.node_off + n1], (unsigned long long)a);
   }
 
   // photon births at the post-drift position, inside the QED zone
   const bool keep = alive && !dead && (((int64_t)ncg << FRAC) + nfrac < k.hfix);
   const int nst = keep ? ncand : 0;
-  if (UNI) {
-    if (__ballot(nst > 0)) queue_births(cx, s_bqn, seg0, nst > 0, slot, upk, evmask);
-  } else if (__ballot(nst > 0)) {
+  if (__ballot(nst > 0)) {
     int dropped = 0;
     const long long first = reserve_tail(cx.pc, proom, nst, &dropped);
     const long long lim = proom.L;
@@ -735,36 +702,18 @@ __device__ void lepton_one(const Ctx& cx, uint32_t slot, int tile, const KC& ku,
     lcn.v[4] += dropped;
   }
 
-  // event counts: sorted chunks accumulate per thread (flushed per
-  // workgroup); tail lanes may belong to different tubes
+  // event counts (the lanes may belong to different tubes)
   lcn.v[0] += alive ? 1 : 0;
   lcn.v[1] += eval ? 1 : 0;
   lcn.v[2] += nev;
   lcn.v[5] += absorbed ? 1 : 0;
   lcn.v[6] += outflow ? 1 : 0;
-  if (!UNI) {
 #pragma unroll
-    for (int i = 0; i < 7; ++i) {
-      const int v = lcn.v[i];
-      if (__ballot(v != 0)) count_by_tube(cx.shard, v != 0 ? tube : -1, cnt_index<2>(i), v);
-    }
-    lcn.clear();
+  for (int i = 0; i < 7; ++i) {
+    const int v = lcn.v[i];
+    if (__ballot(v != 0)) count_by_tube(cx.shard, v != 0 ? tube : -1, cnt_index<2>(i), v);
   }
-}
-
-// Node field of a tile window into LDS (nodes base .. base + WIN).
-__device__ void load_window(const Ctx& cx, int tile, float* s_eb) {
-  const Tile tl = cx.tiles[tile];
-  const Tube& T = cx.tubes[tl.tube];
-  const bool per = (T.flags & F_PERIODIC) != 0;
-  for (int j = threadIdx.x; j <= WIN; j += blockDim.x) {
-    int node = tl.base + j;
-    float v = 0.0f;
-    if (per) v = cx.ebar[T.node_off + wrap_cell(node, T.N)];
-    else if (node >= 0 && node <= T.N) v = cx.ebar[T.node_off + node];
-    s_eb[j] = v;
-  }
-  __syncthreads();
+  lcn.clear();
 }
 
 // V consecutive records of one thread in the sorted passes, loaded and stored
@@ -793,13 +742,12 @@ template <class T, int V> __device__ __forceinline__ void rec_store(T* p, const 
 
 // Records of V consecutive slots of a sorted chunk (one thread); c counts
 // pieces of V TPB slots.
-template <int V> struct LepV { Rec<float, V> w; Rec<uint32_t, V> pos; Rec<float, V> u; int tile; uint32_t slot0; };
+template <int V> struct LepV { Rec<float, V> w; Rec<uint32_t, V> pos; Rec<float, V> u; uint32_t slot0; };
 
 template <int V>
 __device__ __forceinline__ LepV<V> lep_load(const Ctx& cx, long long c) {
   LepV<V> r;
   r.slot0 = (uint32_t)c * (V * TPB) + V * threadIdx.x;
-  r.tile = cx.lchunk[V == VEC ? c : c / (VEC / V)];
   r.w = rec_load<float, V>(cx.L.w + r.slot0);
   r.pos = rec_load<uint32_t, V>(cx.L.pos + r.slot0);
   r.u = rec_load<float, V>(cx.L.u + r.slot0);
@@ -819,27 +767,110 @@ __device__ __forceinline__ void piece_slot(long long q, long long nsq, long long
   }
 }
 
+// The constants of a sorted chunk's tile, held in scalar registers.
+struct LK : LTile {
+  bool per, emit, recoil, all;
+  int64_t step;
+};
+
+__device__ __forceinline__ LK load_lk(const Ctx& cx, int tile) {
+  LK k;
+  struct Words { uint32_t w[sizeof(LTile) / 4]; } raw;
+  const CPtr<uint32_t> q = (CPtr<uint32_t>)(cx.ltiles + tile);
+#pragma unroll
+  for (int i = 0; i < (int)(sizeof(LTile) / 4); ++i) raw.w[i] = q[i];
+  static_cast<LTile&>(k) = __builtin_bit_cast(LTile, raw);
+  k.per = (k.flags & F_PERIODIC) != 0;
+  k.recoil = !(k.flags & F_RECOIL_OFF);
+  k.all = (k.flags & F_TRACK_ALL) != 0;
+  k.emit = !(k.flags & (F_QED_OFF | F_EMIT_OFF)) && k.zone;
+  k.step = cptr(cx.tubes)[k.tube].step;
+  return k;
+}
+// Inside the QED zone (h < H): periodic tubes compare the wrapped cell.
+__device__ __forceinline__ bool in_zone(const LK& k, uint32_t pos) {
+  if (!k.per) return pos <= k.ztop;
+  const int c = wrap_cell(k.base + (int)(pos >> FRAC), k.N);
+  return ((int64_t)c << FRAC) + (pos & 0xFFFFFFu) < k.hfix;
+}
+
+// Node field at node j of a tile's window (0 outside the tube).
+__device__ __forceinline__ float window_node(const Ctx& cx, CPtr<LTile> t, int j) {
+  int node = t->base + j;
+  if (t->flags & F_PERIODIC) node = wrap_cell(node, t->N);
+  return node >= 0 && node <= t->N ? cx.ebar[t->node_off + node] : 0.0f;
+}
+
+// Adds a tile's LDS node charges (and, periodic, the wave sums of the current
+// past the window's nodes) to the global accumulator and clears them; every
+// wave has finished with the window.
+__device__ __forceinline__ void flush_window(const Ctx& cx, const LK& k, long long* s_rho) {
+  for (int j = threadIdx.x; j <= WIN; j += TPB) {
+    const long long v = s_rho[j];
+    if (v != 0) {
+      int node = k.base + j;
+      if (k.per) node = wrap_cell(node, k.N);
+      atomicAdd((unsigned long long*)&cx.rho[k.node_off + node], (unsigned long long)v);
+      s_rho[j] = 0;
+    }
+  }
+  if (k.per && threadIdx.x == 0) {
+    atomic_add_i64(&cx.tubes[k.tube].dcur, s_rho[WIN + 1]);
+    s_rho[WIN + 1] = 0;
+  }
+}
+
+// V records of a thread as arrays (all loops over them are unrolled).
+template <class T> __device__ __forceinline__ void rec_get(const Rec<T, 1>& r, T* a) { a[0] = r.x; }
+template <class T> __device__ __forceinline__ void rec_get(const Rec<T, 4>& r, T* a) {
+  a[0] = r.v.x; a[1] = r.v.y; a[2] = r.v.z; a[3] = r.v.w;
+}
+template <class T> __device__ __forceinline__ void rec_put(Rec<T, 1>& r, const T* a) { r.x = a[0]; }
+template <class T> __device__ __forceinline__ void rec_put(Rec<T, 4>& r, const T* a) {
+  r.v.x = a[0]; r.v.y = a[1]; r.v.z = a[2]; r.v.w = a[3];
+}
+
 // Lepton pass over the sorted region.  Each workgroup takes a contiguous
 // range of chunks (XCD-aware: consecutive ranges go to the same XCD); each
-// thread pushes VEC consecutive slots loaded and stored as 16-byte vectors,
-// and the next chunk's records are prefetched while the current one is
-// pushed.  The chunk's tile constants sit in scalar registers; gather and
-// deposit go through an LDS window of the tile.
-// V: slots per thread and piece.  VEC is the general form; 1 (a quarter of a
-// chunk per workgroup and iteration) gives a small store four times the
-// workgroups and a quarter of the serial work of each.
+// thread pushes V consecutive slots loaded and stored as vectors.  The
+// chunk's tile constants sit in scalar registers; gather and deposit go
+// through an LDS window of the tile.  V: slots per thread and piece.  VEC is
+// the general form; 1 (a quarter of a chunk per workgroup and iteration)
+// gives a small store four times the workgroups and a quarter of the serial
+// work of each.
+//
+// Memory waits are in order on this chip: a wait for a load waits for every
+// older one too.  So a piece is pushed in two phases with its loads placed
+// for that.  Phase 1 gathers, kicks and finds the evaluating slots of all V
+// records; then the ids of those slots are loaded (V consecutive ids, two
+// vectors), then the next piece's records; phase 2 does emission, drift,
+// deposit and births slot by slot, and in it only the ids are waited for.
+//
+// The LDS windows (node charge, node field) are double-buffered.  While the
+// last piece of a tile is pushed, the next tile's node field is on its way to
+// registers; the switch writes it to the other buffer and takes one barrier,
+// after which the old charges are added to global memory while the next
+// piece is pushed.  The tiles' constants come through scalar loads from one
+// record per tile.
+//
+// Bound by HBM where few leptons evaluate (3.8e7 leptons in 64 tubes: 205 us,
+// 3.7 TB/s; loads and stores of the same layout alone reach 5.1), and by
+// instruction issue where many do (8.4e6 leptons of the production gap, half
+// of them evaluating: 64 us beside the photon side).  The former form, one
+// slot at a time in a loop whose first wait took the prefetched piece in
+// full, with two barriers and three dependent loads per tile switch, took 248
+// and 93 us.
 template <bool Q, bool A, int V>
 __device__ __forceinline__ void leptons_sorted(const Ctx& cx, int bx, int G) {
   constexpr int U = V * TPB;
-  const Room proom = load_room(cx.pc);
-  __shared__ long long s_rho[WIN + 2];
-  __shared__ float s_eb[WIN + 2];
+  __shared__ long long s_rho2[2][WIN + 2];
+  __shared__ float s_eb2[2][WIN + 2];
   __shared__ long long s_cnt[8];
+  __shared__ int s_bqn;        // photon births queued by this workgroup
   LocalCounts lcn;
   lcn.clear();
-  __shared__ int s_bqn;        // photon births queued by this workgroup
-  int ctube = -1;
-  const long long nsc = cx.lc->n_sorted_chunks * (CHUNK / U);
+  int n_alive = 0, n_eval = 0;   // of the wave (uniform)
+  const long long nsc = rfl64(cx.lc->n_sorted_chunks) * (CHUNK / U);
   const int r = (bx & 7) * (G >> 3) + (bx >> 3);
   const long long c0 = nsc * r / G, c1 = nsc * (r + 1) / G;
   if (c0 >= c1) {              // no chunk for this workgroup
@@ -849,46 +880,196 @@ __device__ __forceinline__ void leptons_sorted(const Ctx& cx, int bx, int G) {
     }
     return;
   }
-  for (int j = threadIdx.x; j < WIN + 2; j += blockDim.x) s_rho[j] = 0;
-  if (threadIdx.x == 0) s_bqn = 0;
-  __syncthreads();
-  int held = -1;
-  KC kc;
+  auto tile_of = [&](long long c) { return cptr(cx.lchunk)[V == VEC ? c : c / (VEC / V)]; };
   LepV<V> cur = lep_load<V>(cx, c0);
+  int held = tile_of(c0), buf = 0;
+  LK k = load_lk(cx, held);
+  const int j0 = (int)threadIdx.x;
+  s_eb2[0][j0] = window_node(cx, cptr(cx.ltiles) + held, j0);
+  if (j0 == 0) s_eb2[0][WIN] = window_node(cx, cptr(cx.ltiles) + held, WIN);
+  for (int j = j0; j < 2 * (WIN + 2); j += TPB) (&s_rho2[0][0])[j] = 0;
+  if (j0 == 0) s_bqn = 0;
+  __syncthreads();
   for (long long c = c0; c < c1; ++c) {
-    LepV<V> nxt;
-    if (c + 1 < c1) nxt = lep_load<V>(cx, c + 1);
-    const int tile = cur.tile;
-    if (tile != held) {
-      if (held >= 0) flush_window(cx, held, s_rho);
-      held = tile;
-      kc = load_kc(cx, tile, false);
-      if (kc.tube != ctube) {
-        if (ctube >= 0) flush_counts<0>(cx.shard, ctube, lcn, s_cnt);
-        ctube = kc.tube;
-      }
-      load_window(cx, tile, s_eb);
-    }
-    Rec<float, V> w = cur.w, u = cur.u;
-    Rec<uint32_t, V> p = cur.pos;
-    // one body, V records: process the first, write the result into its
-    // place, rotate
-#pragma unroll 1
+    const int next = c + 1 < c1 ? tile_of(c + 1) : held;
+    long long* const s_rho = s_rho2[buf];
+    const float* const s_eb = s_eb2[buf];
+    const uint32_t slot0 = cur.slot0;
+    float w[V], u[V];
+    uint32_t p[V];
+    rec_get(cur.w, w);
+    rec_get(cur.u, u);
+    rec_get(cur.pos, p);
+
+    // ---- phase 1: gather (node field, first-order shape) and kick; which
+    // slots evaluate emission (x_c = 1.5 gamma chi >= floor inside the zone;
+    // below u_skip none does)
+    uint32_t ev = 0;
+#pragma unroll
     for (int j = 0; j < V; ++j) {
-      uint32_t po;
-      float uo;
-      lepton_one<true, Q, A>(cx, cur.slot0 + j, tile, kc, s_rho, s_eb, lcn, rec_first(w), rec_first(p), rec_first(u), &po,
-                             &uo, proom, &s_bqn, c0 * U);
-      rec_rotate(w, rec_first(w));
-      rec_rotate(p, po);
-      rec_rotate(u, uo);
+      const uint32_t off = p[j] >> FRAC;
+      const float xi = (float)(p[j] & 0xFFFFFFu) * 5.9604645e-8f;
+      u[j] = kicked(u[j], w[j] < 0.0f ? -1.0f : 1.0f, xi, s_eb[off], s_eb[off + 1], k.dt);
     }
-    rec_store<uint32_t, V>(cx.L.pos + cur.slot0, p);
-    rec_store<float, V>(cx.L.u + cur.slot0, u);
+    if (k.emit) {
+#pragma unroll
+      for (int j = 0; j < V; ++j) {
+        const bool may = w[j] != 0.0f && fabsf(u[j]) >= k.u_skip;
+        if (__ballot(may)) {
+          float g, chi;
+          if (may && emit_xc(u[j], k.lr, &g, &chi) >= k.xc_floor && in_zone(k, p[j])) ev |= 1u << j;
+        }
+      }
+    }
+    uint64_t id[V];
+    if (ev != 0) {
+      if constexpr (V == 4) {
+        const ulonglong2 a = *reinterpret_cast<const ulonglong2*>(cx.L.id + slot0);
+        const ulonglong2 b = *reinterpret_cast<const ulonglong2*>(cx.L.id + slot0 + 2);
+        id[0] = a.x; id[1] = a.y; id[2] = b.x; id[3] = b.y;
+      } else {
+        id[0] = cx.L.id[slot0];
+      }
+    }
+    // (the last piece loads itself again: with the same loads on every path
+    // the wait for the ids does not have to cover them)
+    const LepV<V> nxt = lep_load<V>(cx, c + 1 < c1 ? c + 1 : c);
+    float eb0 = 0.0f, eb1 = 0.0f;
+    if (next != held) {
+      eb0 = window_node(cx, cptr(cx.ltiles) + next, j0);
+      if (j0 == 0) eb1 = window_node(cx, cptr(cx.ltiles) + next, WIN);
+    }
+
+    // ---- phase 2
+#pragma unroll
+    for (int j = 0; j < V; ++j) {
+      const uint32_t slot = slot0 + j;
+      const bool alive = w[j] != 0.0f;
+      const float upk = u[j];
+      uint64_t evmask = 0;
+      int ncand = 0;
+      // curvature emission: rate alpha_em gamma/R~ T_syn(chi), chi = gamma^2 lambda~/R~,
+      // photon energy xi_s x_c, recoil on the lepton
+      const bool eval = (ev >> j) & 1u;
+      const uint64_t em = __ballot(eval);
+      if (em) {
+        n_eval += (int)__popcll(em);
+        if (eval) {
+          float g, chi;
+          const float xc = emit_xc(upk, k.lr, &g, &chi);
+          const float dtau = emit_dtau(k.emit_k, g, chi);
+          const int nsub = emit_nsub(dtau, k.nsub_max);
+          float per_sub = dtau;                      // (dtau / 1 is dtau)
+          if (__ballot(nsub > 1)) per_sub = dtau / (float)nsub;
+          const uint32_t thr = bern_thr(one_minus_exp_neg(per_sub));
+          float au = fabsf(upk);
+          // (the key is kept from being known ahead of the loop: its twenty
+          // round keys would be held in spilled scalar registers)
+          uint32_t k0 = (uint32_t)k.seed, k1 = (uint32_t)(k.seed >> 32);
+          for (int q = 0; q < nsub; ++q) {
+            asm volatile("" : "+s"(k0), "+s"(k1));
+            const u4 rr = philox<true>((uint32_t)id[j], (uint32_t)(id[j] >> 32), (uint32_t)k.step,
+                                       (T_EMIT << 16) | (uint32_t)q, k0, k1);
+            if (bern_t(rr.a, thr)) {
+              const float x = fminf(photon_energy<Q>(cx, k.flags, rr.b, xc, upk, k.lr), au);
+              au -= x;
+              evmask |= 1ull << q;
+              ++lcn.v[2];
+              if (x >= k.x_thr || k.all) ++ncand;
+            }
+          }
+          if (k.recoil) u[j] = copysignf(au, upk);
+        }
+      }
+      // drift: dh/dt = u / gamma, in fixed point
+      const int dfix = drift_fix(u[j], k.cfl24);
+      const uint32_t np = p[j] + (uint32_t)dfix;
+      const bool wrapped = dfix >= 0 ? np < p[j] : np > p[j];   // left the 256-cell window
+      bool live = alive;
+      if (__ballot(alive & (wrapped | (np < k.xlo) | (np > k.xtop)))) {
+        if (alive && wrapped) {
+          atomicOr(cx.err, E_TILE);
+          live = false;
+        } else if (alive && !k.per && (np < k.xlo || np > k.xtop)) {
+          live = false;
+          if (np < k.xlo) {                          // absorbed at the surface
+            const int64_t Tw = __float2ll_rn(fabsf(w[j]) * 16777216.0f);
+            atomic_add_i64(&cx.tubes[k.tube].dq, w[j] > 0.0f ? Tw : -Tw);
+            return_add(cx.ret, cx.ret_thr, k.tube, u[j], w[j]);
+            ++lcn.v[5];
+          } else {
+            ++lcn.v[6];
+          }
+        }
+        if (alive && !live) cx.L.w[slot] = 0.0f;
+      }
+      n_alive += (int)__popcll(__ballot(alive));
+      // deposit at the new position: node k gets s (T - A), node k+1 gets s A,
+      // A = round(T xi) (half up), exact integers; T < 2^31 fits 32 bits
+      const uint32_t noff = np >> FRAC, nfrac = np & 0xFFFFFFu;
+      if (!__ballot(!(fabsf(w[j]) < 128.0f))) {
+        if (live) {
+          const uint32_t T = (uint32_t)__float2int_rn(fabsf(w[j]) * 16777216.0f);
+          const int32_t a = (int32_t)(((uint64_t)T * nfrac + (1u << 23)) >> FRAC), t = (int32_t)T - a;
+          const bool neg = w[j] < 0.0f;
+          atomicAdd((unsigned long long*)&s_rho[noff], (unsigned long long)(long long)(neg ? -t : t));
+          atomicAdd((unsigned long long*)&s_rho[noff + 1], (unsigned long long)(long long)(neg ? -a : a));
+        }
+      } else if (live) {
+        const int64_t T = __float2ll_rn(fabsf(w[j]) * 16777216.0f);
+        const int64_t a = (int64_t)(((unsigned long long)T * nfrac + (1ull << 23)) >> FRAC);
+        const bool neg = w[j] < 0.0f;
+        atomicAdd((unsigned long long*)&s_rho[noff], (unsigned long long)(neg ? a - T : T - a));
+        atomicAdd((unsigned long long*)&s_rho[noff + 1], (unsigned long long)(neg ? -a : a));
+      }
+      // Periodic tubes: the current, one add per wave and slot into LDS,
+      // flushed with the node charges: every lepton adds to the one word of
+      // its tube, and such atomics are served one at a time (one global
+      // atomic per lepton made a step of 48 000 leptons take 0.61 ms)
+      if (k.per) {
+        const int64_t T = __float2ll_rn(fabsf(w[j]) * 16777216.0f);
+        const long long cur_sum = wave_sum_ll(live ? (w[j] > 0.0f ? T : -T) * (int64_t)dfix : 0);
+        if (lane_id() == 0 && cur_sum != 0) atomicAdd((unsigned long long*)&s_rho[WIN + 1], (unsigned long long)cur_sum);
+      }
+      // electrons left in cell 0 by this push refill the atmosphere next step
+      if (A && k.base < 0) {
+        if (live && w[j] < 0.0f && np - k.xlo < (1u << FRAC)) atomicAdd(&cx.tubes[k.tube].atm_cnt[k.step & 1], 1);
+      }
+      // photon births at the post-drift position, inside the QED zone
+      if (em) {
+        const bool has = live && ncand > 0 && in_zone(k, np);
+        if (__ballot(has)) queue_births(cx, &s_bqn, c0 * U, has, slot, upk, evmask);
+      }
+      p[j] = np;
+    }
+    rec_put(cur.u, u);
+    rec_put(cur.pos, p);
+    rec_store<uint32_t, V>(cx.L.pos + slot0, cur.pos);
+    rec_store<float, V>(cx.L.u + slot0, cur.u);
     cur = nxt;
+    if (next != held) {
+      // (the other buffer was last read before the previous switch's barrier)
+      s_eb2[buf ^ 1][j0] = eb0;
+      if (j0 == 0) s_eb2[buf ^ 1][WIN] = eb1;
+      __syncthreads();
+      flush_window(cx, k, s_rho);
+      const int tube = k.tube;
+      k = load_lk(cx, next);
+      if (k.tube != tube) {
+        lcn.v[0] = lane_id() == 0 ? n_alive : 0;
+        lcn.v[1] = lane_id() == 0 ? n_eval : 0;
+        n_alive = n_eval = 0;
+        flush_counts<0>(cx.shard, tube, lcn, s_cnt);
+      }
+      held = next;
+      buf ^= 1;
+    }
   }
-  flush_window(cx, held, s_rho);
-  flush_counts<0>(cx.shard, ctube, lcn, s_cnt);
+  __syncthreads();
+  flush_window(cx, k, s_rho2[buf]);
+  lcn.v[0] = lane_id() == 0 ? n_alive : 0;
+  lcn.v[1] = lane_id() == 0 ? n_eval : 0;
+  flush_counts<0>(cx.shard, k.tube, lcn, s_cnt);
   // (flush_counts ends with a barrier: every wave has queued its births)
   if (threadIdx.x == 0) {
     cx.bq_count[bx] = s_bqn;
@@ -896,8 +1077,6 @@ __device__ __forceinline__ void leptons_sorted(const Ctx& cx, int bx, int G) {
   }
 }
 
-// (six waves per SIMD: the register cap spills one value, stored once on
-// entry and reloaded once per chunk)
 template <bool Q, bool A>
 __global__ __launch_bounds__(TPB, 6) void k_leptons(Ctx cx) {
   leptons_sorted<Q, A, VEC>(cx, blockIdx.x, gridDim.x);
@@ -914,7 +1093,6 @@ __device__ __forceinline__ void leptons_tail(const Ctx& cx, int bid, int nblk) {
   const long long S = nsc * CHUNK;
   const long long tail = cx.lc->tail_snap;
   const long long nq = (tail + TPB - 1) / TPB;
-  const KC kc0 = load_kc(cx, 0, false);
   for (long long q = bid; q < nq; q += nblk) {
     uint32_t slot;
     int tile;
@@ -922,7 +1100,7 @@ __device__ __forceinline__ void leptons_tail(const Ctx& cx, int bid, int nblk) {
     const float w = cx.L.w[slot];
     const uint32_t pos = cx.L.pos[slot];
     const float u = cx.L.u[slot];
-    lepton_one<false, Q, A>(cx, slot, tile, kc0, nullptr, nullptr, lcn, w, pos, u, nullptr, nullptr, proom, nullptr, 0);
+    lepton_one<Q, A>(cx, slot, tile, lcn, w, pos, u, proom);
   }
 }
 
