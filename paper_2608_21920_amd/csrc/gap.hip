@@ -218,7 +218,8 @@ struct WinState {
   uint32_t* tpos = nullptr; float* tu = nullptr; TapeMeta* meta = nullptr;
   float* teb = nullptr; float* tE = nullptr; float* wlast = nullptr;
   float* lam[2][3] = {{nullptr, nullptr, nullptr}, {nullptr, nullptr, nullptr}};
-  double* lamE = nullptr; double* suf = nullptr; double* lamEb = nullptr;
+  double* lamE = nullptr; double* suf = nullptr; double* lamEb[2] = {nullptr, nullptr};
+  unsigned long long* frec = nullptr;   // records of the reverse field scan
   AdjTube* at = nullptr;
   uint32_t* hvals = nullptr; uint64_t hmask = 0;
 };
@@ -590,6 +591,7 @@ FieldCtx make_fctx(gap_t* g, int mode) {
   f.part2 = g->part2;
   f.err = g->err;
   f.pc = g->pho.ctl;
+  f.loss = nullptr;
   f.fs = g->fscan;
   f.E0 = g->E0;
   f.Du = g->Du;
@@ -691,9 +693,8 @@ void rebucket_all(gap_t* g) {
 
 // With `done`, the single-pass kernel's own completion is recorded into that
 // event (no separate marker on the stream); returns whether it was.
-bool field_pass(gap_t* g, int mode, hipEvent_t done = nullptr) {
-  FieldCtx f = make_fctx(g, mode);
-  const bool filt = g->any_filter && mode == 0;
+bool field_pass(gap_t* g, const FieldCtx& f, hipEvent_t done = nullptr) {
+  const bool filt = g->any_filter && f.mode == 0;
   if (filt) done = nullptr;   // the step's field is complete only after k_filter
   bool bound = false;
   if (!g->any_periodic) {
@@ -716,7 +717,7 @@ void rebuild_field(gap_t* g) {
   k_fill_i64<<<grid, 256, 0, g->s>>>(g->rho, g->total_nodes, 0);
   k_deposit_all<<<kGrid, TPB, 0, g->s>>>(make_ctx(g));
   if (g->any_protons) k_deposit_protons<<<kGrid, TPB, 0, g->s>>>(make_ctx(g));
-  field_pass(g, 1);
+  field_pass(g, make_fctx(g, 1));
 }
 
 template <class B>
@@ -840,14 +841,33 @@ void fork_photon_side(gap_t* g, const Ctx& cx) {
   g->s2_pending = true;
 }
 
-// One step of a window: no merge, no re-sort (slots stay put).
-void enqueue_window_step(gap_t* g) {
-  Ctx cx = make_ctx(g);
-  k_pre<<<1, pre_threads(g), 0, g->s>>>(cx, g->n_tubes);
+bool fused_form(const gap_t* g);
+void enqueue_fused(gap_t* g, Ctx cx, bool pre);
+
+// The particle passes of a window step whose prologue has run.
+void window_passes(gap_t* g, const Ctx& cx) {
+  if (fused_form(g)) {
+    enqueue_fused(g, cx, false);
+    return;
+  }
   fork_photon_side(g, cx);
   launch_leptons(g, cx, g->s);
   launch_tails(g, cx, g->s);
-  field_pass(g, 0);
+}
+
+// One step of a window: no merge, no re-sort (slots stay put).  loss: per
+// field block, accumulates the sum of E^2 after the step.
+void enqueue_window_step(gap_t* g, double* loss) {
+  const Ctx cx = make_ctx(g);
+  if (fused_form(g)) {
+    enqueue_fused(g, cx, true);
+  } else {
+    k_pre<<<1, pre_threads(g), 0, g->s>>>(cx, g->n_tubes);
+    window_passes(g, cx);
+  }
+  FieldCtx f = make_fctx(g, 0);
+  f.loss = loss;
+  field_pass(g, f);
   join_photon_side(g);
   ++g->host_step;
 }
@@ -861,6 +881,9 @@ int save_ckpt(gap_t* g, WinCkpt& c) {
   if (c.lctl.tail != 0 || c.pctl.tail != 0) return GAP_ESTATE;
   c.nch_l = c.lctl.n_sorted_chunks;
   c.nch_p = c.pctl.n_sorted_chunks;
+  g->seen_l = c.nch_l;
+  g->seen_p = c.nch_p;
+  g->rb_seen = 0;
   c.nl = c.nch_l * CHUNK;
   c.np = c.nch_p * CHUNK;
   const size_t nl = (size_t)c.nl, np = (size_t)c.np;
@@ -921,6 +944,9 @@ int restore_ckpt(gap_t* g, const WinCkpt& c) {
   HIPCHK(hipStreamSynchronize(g->s));
   g->host_step = c.host_step;
   g->since_rb = 0;
+  g->seen_l = c.nch_l;
+  g->seen_p = c.nch_p;
+  g->rb_seen = 0;
   return GAP_OK;
 }
 
@@ -938,7 +964,7 @@ int window_forward(gap_t* g, int64_t W, int64_t K, double* loss) {
   w.K = K;
   w.nseg = (W + K - 1) / K;
   w.ck.resize((size_t)w.nseg + 1);
-  w.loss_acc = (double*)walloc(g, sizeof(double) * g->n_tubes);
+  w.loss_acc = (double*)walloc(g, sizeof(double) * g->n_fb);
   if (!w.loss_acc) return GAP_ENOMEM;
   int e;
   for (int64_t sg = 0; sg < w.nseg; ++sg) {
@@ -946,10 +972,7 @@ int window_forward(gap_t* g, int64_t W, int64_t K, double* loss) {
     g->since_rb = 0;
     if ((e = save_ckpt(g, w.ck[sg]))) return e;
     const int64_t Ks = std::min(K, W - sg * K);
-    for (int64_t j = 0; j < Ks; ++j) {
-      enqueue_window_step(g);
-      k_loss<<<g->n_tubes, ADJ_THREADS, 0, g->s>>>(g->E, g->tubes, w.loss_acc);
-    }
+    for (int64_t j = 0; j < Ks; ++j) enqueue_window_step(g, w.loss_acc);
     HIPCHK(hipStreamSynchronize(g->s));
     const Ctl c = read_ctl(g->lep);
     w.max_used = std::max<long long>(w.max_used, c.n_sorted_chunks * CHUNK + c.tail);
@@ -958,9 +981,10 @@ int window_forward(gap_t* g, int64_t W, int64_t K, double* loss) {
   g->since_rb = 0;
   if ((e = save_ckpt(g, w.ck[(size_t)w.nseg]))) return e;
   if ((e = sync_and_err(g))) return e;
-  std::vector<double> acc(g->n_tubes);
-  HIPCHK(hipMemcpy(acc.data(), w.loss_acc, sizeof(double) * g->n_tubes, hipMemcpyDeviceToHost));
-  for (int t = 0; t < g->n_tubes; ++t) loss[t] = acc[t] / ((double)W * g->P[t].n_cells);
+  std::vector<double> acc(g->n_fb), sum(g->n_tubes, 0.0);
+  HIPCHK(hipMemcpy(acc.data(), w.loss_acc, sizeof(double) * g->n_fb, hipMemcpyDeviceToHost));
+  for (int b = 0; b < g->n_fb; ++b) sum[g->fb_h[b].tube] += acc[b];
+  for (int t = 0; t < g->n_tubes; ++t) loss[t] = sum[t] / ((double)W * g->P[t].n_cells);
   w.step_end = g->host_step;
   w.valid = true;
   return GAP_OK;
@@ -974,21 +998,22 @@ int backward_alloc(gap_t* g) {
   w.tpos = (uint32_t*)walloc(g, (K + 1) * M * 4);
   w.tu = (float*)walloc(g, (K + 1) * M * 4);
   w.meta = (TapeMeta*)walloc(g, (K + 1) * sizeof(TapeMeta));
-  w.teb = (float*)walloc(g, K * (size_t)g->total_nodes * 4);
+  w.teb = (float*)walloc(g, (K + 1) * (size_t)g->total_nodes * 4);
   w.tE = (float*)walloc(g, (K + 1) * (size_t)g->total_cells * 4);
   w.wlast = (float*)walloc(g, M * 4);
   for (int b = 0; b < 2; ++b)
     for (int k = 0; k < 3; ++k) w.lam[b][k] = (float*)walloc(g, M * 4);
   w.lamE = (double*)walloc(g, (size_t)g->total_cells * 8);
   w.suf = (double*)walloc(g, (size_t)g->total_nodes * 8);
-  w.lamEb = (double*)walloc(g, (size_t)g->total_nodes * 8);
+  for (int b = 0; b < 2; ++b) w.lamEb[b] = (double*)walloc(g, (size_t)g->total_nodes * 8);
+  w.frec = (unsigned long long*)walloc(g, sizeof(unsigned long long) * (4 * (size_t)g->n_fb + 2));
   w.at = (AdjTube*)walloc(g, sizeof(AdjTube) * g->n_tubes);
   uint64_t hs = 1024;
   while (hs < 2 * (uint64_t)M) hs <<= 1;
   w.hmask = hs - 1;
   w.hvals = (uint32_t*)walloc(g, hs * 4);
-  if (!w.tpos || !w.tu || !w.meta || !w.teb || !w.tE || !w.wlast || !w.lamE || !w.suf || !w.lamEb || !w.at ||
-      !w.hvals)
+  if (!w.tpos || !w.tu || !w.meta || !w.teb || !w.tE || !w.wlast || !w.lamE || !w.suf || !w.lamEb[0] ||
+      !w.lamEb[1] || !w.frec || !w.at || !w.hvals)
     return GAP_ENOMEM;
   for (int b = 0; b < 2; ++b)
     for (int k = 0; k < 3; ++k)
@@ -1018,26 +1043,40 @@ int backward(gap_t* g, double* dalpha, double* dninj) {
     HIPCHK(hipStreamSynchronize(g->s));
     HIPCHK(hipMemcpy(w.at, at.data(), sizeof(AdjTube) * g->n_tubes, hipMemcpyHostToDevice));
   }
-  const size_t M = (size_t)w.M;
+  const size_t M = (size_t)w.M, nn = (size_t)g->total_nodes, nc = (size_t)g->total_cells;
   const int fgrid = (int)std::min<long long>(4096, (w.M + 255) / 256);
   int cur = 0;
+  // node-field adjoints of the step being reversed and of the one before it
+  int nb = 0;
+  for (int b = 0; b < 2; ++b)
+    k_fill_i64<<<std::max(1, (int)std::min<size_t>(1024, (nn + 255) / 256)), 256, 0, g->s>>>((long long*)w.lamEb[b],
+                                                                                             (long long)nn, 0);
+  // the reverse field pass: of the window's last field, or (step) of the one
+  // before a step whose leptons have been reversed
+  auto adj_field = [&](const float* E, bool step) {
+    AdjFieldCtx f{g->fb, w.frec, w.lamE, w.suf, step ? w.lamEb[nb] : nullptr, w.lamEb[nb ^ 1], E, w.at, g->err};
+    k_adj_field<<<g->n_fb, FB_THREADS, 0, g->s>>>(f);
+    if (step) nb ^= 1;
+  };
   for (int64_t sg = w.nseg - 1; sg >= 0; --sg) {
     if ((e = restore_ckpt(g, w.ck[(size_t)sg]))) return e;
     const int64_t Ks = std::min(w.K, w.W - sg * w.K);
-    D2D(w.tE, g->E, sizeof(float) * g->total_cells);
-    // recompute the segment, taping the lepton store before each step
+    D2D(w.tE, g->E, sizeof(float) * nc);
+    D2D(w.teb, g->ebar, sizeof(float) * nn);
+    // recompute the segment, taping the lepton store before each step and the
+    // fields as they are made (the handle's own are restored at the end)
     for (int64_t j = 0; j < Ks; ++j) {
       Ctx cx = make_ctx(g);
+      cx.ebar = w.teb + j * nn;
       k_pre<<<1, pre_threads(g), 0, g->s>>>(cx, g->n_tubes);
       k_tape<<<fgrid, 256, 0, g->s>>>(cx.L, g->lep.ctl, w.tpos + j * M, w.tu + j * M, w.wlast, w.meta + j,
                                       w.M, 0, g->err);
-      fork_photon_side(g, cx);       // (the tape of the leptons is taken; photons are not taped)
-      D2D(w.teb + j * (size_t)g->total_nodes, g->ebar, sizeof(float) * g->total_nodes);
-      launch_leptons(g, cx, g->s);
-      launch_tails(g, cx, g->s);
-      field_pass(g, 0);
+      window_passes(g, cx);          // (the tape of the leptons is taken; photons are not taped)
+      FieldCtx f = make_fctx(g, 0);
+      f.E = w.tE + (j + 1) * nc;
+      f.ebar = w.teb + (j + 1) * nn;
+      field_pass(g, f);
       ++g->host_step;
-      D2D(w.tE + (j + 1) * (size_t)g->total_cells, g->E, sizeof(float) * g->total_cells);
       join_photon_side(g);
     }
     {
@@ -1048,7 +1087,7 @@ int backward(gap_t* g, double* dalpha, double* dninj) {
     // adjoint of the state after the segment, in this recomputed layout
     if (sg == w.nseg - 1) {
       for (int k = 0; k < 3; ++k) k_fill_i32<<<fgrid, 256, 0, g->s>>>((int32_t*)w.lam[cur][k], w.M, 0);
-      k_adj_init<<<g->n_tubes, ADJ_THREADS, 0, g->s>>>(w.lamE, w.tE + Ks * (size_t)g->total_cells, w.at);
+      adj_field(w.tE + Ks * nc, false);
     } else {
       const WinCkpt& nx = w.ck[(size_t)sg + 1];
       const int hgrid = (int)std::min<uint64_t>(4096, (w.hmask + 256) / 256);
@@ -1072,19 +1111,17 @@ int backward(gap_t* g, double* dalpha, double* dninj) {
     ac.lw = w.lam[cur][2];
     ac.lamE = w.lamE;
     ac.suf = w.suf;
-    ac.lamEb = w.lamEb;
     ac.at = w.at;
     for (int64_t j = Ks - 1; j >= 0; --j) {
-      k_adj_field<<<g->n_tubes, ADJ_THREADS, 0, g->s>>>(w.lamE, w.suf, w.at);
       ac.pos0 = w.tpos + j * M;
       ac.u0 = w.tu + j * M;
       ac.pos1 = w.tpos + (j + 1) * M;
       ac.u1 = w.tu + (j + 1) * M;
       ac.meta0 = w.meta + j;
-      ac.eb0 = w.teb + j * (size_t)g->total_nodes;
-      k_adj_leptons<<<kGrid, TPB, 0, g->s>>>(ac);
-      const float* Eprev = (sg > 0 || j > 0) ? w.tE + j * (size_t)g->total_cells : nullptr;
-      k_adj_nodes<<<g->n_tubes, ADJ_THREADS, 0, g->s>>>(w.lamE, w.lamEb, Eprev, w.at);
+      ac.eb0 = w.teb + j * nn;
+      ac.lamEb = w.lamEb[nb];
+      k_adj_leptons<<<ADJ_GRID, TPB, 0, g->s>>>(ac);
+      if (sg > 0 || j > 0) adj_field(w.tE + j * nc, true);   // (the window's start field is not in the loss)
     }
   }
   if ((e = sync_and_err(g))) return e;
@@ -1156,14 +1193,14 @@ bool fused_form(const gap_t* g) {
 }
 
 template <bool Q, bool A, int V>
-void launch_fused(gap_t* g, Ctx cx, int gp, int gl, const RestGrid& n) {
-  k_sorted<Q, A, V><<<FUSED_PRE + gp + gl, TPB, 0, g->s>>>(cx, g->n_tubes, gp, gl);
+void launch_fused(gap_t* g, const Ctx& cx, bool pre, int gp, int gl, const RestGrid& n) {
+  k_sorted<Q, A, V><<<FUSED_PRE + gp + gl, TPB, 0, g->s>>>(cx, pre ? g->n_tubes : -1, gp, gl);
   k_rest<Q, A, V><<<n.births + n.conv + n.tails + n.protons, TPB, 0, g->s>>>(cx, n);
 }
 
-// The particle passes of one step on the caller's stream.
-void enqueue_fused(gap_t* g) {
-  Ctx cx = make_ctx(g);
+// The particle passes of one step on the caller's stream (pre: the prologue
+// with them).
+void enqueue_fused(gap_t* g, Ctx cx, bool pre) {
   // Known counts: a workgroup per chunk up to the usual grids, and a store of
   // fewer chunks than CUs in pieces of a quarter chunk.  Else, and in a graph
   // that will be replayed on other counts, one resident round.
@@ -1185,14 +1222,14 @@ void enqueue_fused(gap_t* g) {
   n.protons = g->any_protons ? std::max(8, g->grid_tail) : 0;
   const int form = (g->any_quantum ? 4 : 0) | (g->any_atm ? 2 : 0) | (pieces ? 1 : 0);
   switch (form) {
-    case 0: launch_fused<false, false, VEC>(g, cx, gp, gl, n); break;
-    case 1: launch_fused<false, false, 1>(g, cx, gp, gl, n); break;
-    case 2: launch_fused<false, true, VEC>(g, cx, gp, gl, n); break;
-    case 3: launch_fused<false, true, 1>(g, cx, gp, gl, n); break;
-    case 4: launch_fused<true, false, VEC>(g, cx, gp, gl, n); break;
-    case 5: launch_fused<true, false, 1>(g, cx, gp, gl, n); break;
-    case 6: launch_fused<true, true, VEC>(g, cx, gp, gl, n); break;
-    default: launch_fused<true, true, 1>(g, cx, gp, gl, n); break;
+    case 0: launch_fused<false, false, VEC>(g, cx, pre, gp, gl, n); break;
+    case 1: launch_fused<false, false, 1>(g, cx, pre, gp, gl, n); break;
+    case 2: launch_fused<false, true, VEC>(g, cx, pre, gp, gl, n); break;
+    case 3: launch_fused<false, true, 1>(g, cx, pre, gp, gl, n); break;
+    case 4: launch_fused<true, false, VEC>(g, cx, pre, gp, gl, n); break;
+    case 5: launch_fused<true, false, 1>(g, cx, pre, gp, gl, n); break;
+    case 6: launch_fused<true, true, VEC>(g, cx, pre, gp, gl, n); break;
+    default: launch_fused<true, true, 1>(g, cx, pre, gp, gl, n); break;
   }
 }
 
@@ -1226,7 +1263,7 @@ void enqueue_step(gap_t* g, bool more) {
   if (fused) {
     if (two) join_photon_side(g);
     g->ev_l_bound = false;
-    enqueue_fused(g);
+    enqueue_fused(g, make_ctx(g), true);
   } else {
     enqueue_passes(g, two, merge);
   }
@@ -1236,7 +1273,7 @@ void enqueue_step(gap_t* g, bool more) {
     const bool bind = two && !fused && more && g->since_rb + 1 < g->R &&
                       !(g->merge_on && (g->host_step + 1) % g->merge_every == 0);
     Timer t(g, KT_FIELD);
-    g->ev_l_bound = field_pass(g, 0, bind ? g->ev_l : nullptr);
+    g->ev_l_bound = field_pass(g, make_fctx(g, 0), bind ? g->ev_l : nullptr);
   }
   if (g->wf_every > 0) {
     WfCtx w{g->tubes, g->E, g->wf_ring, g->wf_steps, g->wf_every, g->wf_B, g->wf_cap, g->wf_nbmax};

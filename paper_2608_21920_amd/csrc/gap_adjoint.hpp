@@ -90,64 +90,59 @@ __global__ __launch_bounds__(TPB) void k_tape(LepBuf L, const Ctl* lc, uint32_t*
   }
 }
 
-// Sum of E^2 over each tube's cells, added to acc[tube] (one workgroup per
-// tube, fixed reduction order).
-__device__ __forceinline__ double block_sum_d(double v, double* sh) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d);
-  const int w = threadIdx.x / WAVE;
-  if (lane_id() == 0) sh[w] = v;
-  __syncthreads();
-  double t = 0.0;
-  if (threadIdx.x < WAVE) {
-    t = threadIdx.x < (int)(blockDim.x / WAVE) ? sh[threadIdx.x] : 0.0;
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) t += __shfl_xor(t, d);
-  }
-  if (threadIdx.x == 0) sh[0] = t;
-  __syncthreads();
-  t = sh[0];
-  __syncthreads();
-  return t;
-}
-
-constexpr int ADJ_THREADS = 1024;
-
-__global__ __launch_bounds__(ADJ_THREADS) void k_loss(const float* E, const Tube* tubes, double* acc) {
-  __shared__ double sh[ADJ_THREADS / WAVE];
-  const Tube& T = tubes[blockIdx.x];
-  double s = 0.0;
-  for (int k = threadIdx.x; k < T.N; k += blockDim.x) {
-    const double e = (double)E[T.cell_off + k];
-    s += e * e;
-  }
-  s = block_sum_d(s, sh);
-  if (threadIdx.x == 0) acc[blockIdx.x] += s;
-}
-
-// lamE = lossw * E (adjoint of the loss at the window's last field)
-__global__ __launch_bounds__(ADJ_THREADS) void k_adj_init(double* lamE, const float* E, const AdjTube* at) {
-  const AdjTube& a = at[blockIdx.x];
-  for (int k = threadIdx.x; k < a.N; k += blockDim.x) lamE[a.cell_off + k] = a.lossw * (double)E[a.cell_off + k];
-}
-
 // ------------------------------------------------------------------ reverse
-// Field after step j: E_s receives sum_k lamE_k; suffix sums for the weights;
-// alpha enters E_s as alpha s_co dt.  One workgroup per tube: thread t sums
-// a run of consecutive cells, one block scan gives each run the sum of the
-// runs above it, and each thread then writes its run's suffix sums from the
-// top down (one round of barriers instead of one per ADJ_THREADS cells).
-__global__ __launch_bounds__(ADJ_THREADS) void k_adj_field(const double* lamE, double* suf, AdjTube* at) {
-  __shared__ double sh[ADJ_THREADS / WAVE];
-  AdjTube& a = at[blockIdx.x];
+// The field of one step in reverse, one launch: the node-field adjoints of
+// the step after it (nb) become cell-field adjoints (and E_s's share), the
+// loss term of the field is added, and the suffix sums of the cell-field
+// adjoints are formed for the weights; E_s receives their total and alpha
+// enters it as alpha s_co dt.  At the window's last field there is no step
+// after it (nb null).
+//
+// Blocks of FB_NODES cells, one tube's from its top down, find the sum over
+// the cells above them by looking back over the records of lower-indexed
+// blocks, as k_field_1p does (same records, termination and bounded wait).
+// The former form, one workgroup per tube in two launches, took 48 us per
+// step at 16384 cells; this one 9.
+struct AdjFieldCtx {
+  const FBlk* fb;
+  unsigned long long* rec;   // a four-word record per block, then the epoch and a done count
+  double* lamE;
+  double* suf;
+  const double* nb;          // node-field adjoints of the step after (null: none)
+  double* nb_clear;          // the other buffer, cleared for the step before
+  const float* E;            // the field whose loss term is added (null: outside the window)
+  AdjTube* at;
+  int* err;
+};
+
+__global__ __launch_bounds__(FB_THREADS) void k_adj_field(AdjFieldCtx f) {
+  constexpr int NW = FB_THREADS / WAVE;
+  __shared__ double sh[NW];
+  __shared__ double s_above;
+  __shared__ unsigned long long s_ep;
+  const FBlk b = f.fb[blockIdx.x];
+  AdjTube& a = f.at[b.tube];
   const int N = a.N;
-  const double* lm = lamE + a.cell_off;
-  const int per = (N + ADJ_THREADS - 1) / ADJ_THREADS;
-  const int k0 = min(N, (int)threadIdx.x * per), k1 = min(N, k0 + per);
-  double t = 0.0;
-  for (int k = k0; k < k1; ++k) t += lm[k];
-  // inclusive suffix of the run sums over the wave's lanes, then over waves
-  double incl = t;
+  const int bx = (int)blockIdx.x;
+  const int q = b.nblk - 1 - (bx - b.first_blk);   // the tube's top block comes first
+  const int k = q * FB_NODES + (int)threadIdx.x * FB_PER;
+  unsigned long long* epoch = f.rec + 4 * gridDim.x;
+  const double* nb = f.nb ? f.nb + a.node_off : nullptr;
+  double v[FB_PER], loc = 0.0;
+#pragma unroll
+  for (int i = FB_PER - 1; i >= 0; --i) {
+    v[i] = 0.0;
+    if (k + i < N) {
+      if (nb) v[i] = k + i < N - 1 ? 0.5 * (nb[k + i] + nb[k + i + 1]) : 0.5 * nb[N - 1] + nb[N];
+      if (f.E) v[i] += a.lossw * (double)f.E[a.cell_off + k + i];
+      f.lamE[a.cell_off + k + i] = v[i];
+      f.nb_clear[a.node_off + k + i] = 0.0;
+      if (k + i == N - 1) f.nb_clear[a.node_off + N] = 0.0;
+    }
+    loc += v[i];
+  }
+  // inclusive suffix over the wave's lanes, then over the waves
+  double incl = loc;
 #pragma unroll
   for (int d = 1; d < WAVE; d <<= 1) {
     const double o = __shfl_down(incl, d);
@@ -155,75 +150,126 @@ __global__ __launch_bounds__(ADJ_THREADS) void k_adj_field(const double* lamE, d
   }
   const int wv = threadIdx.x / WAVE;
   if (lane_id() == 0) sh[wv] = incl;
+  if (threadIdx.x == 0) s_ep = __hip_atomic_load(epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
-  double after = 0.0;
-  for (int q = ADJ_THREADS / WAVE - 1; q > wv; --q) after += sh[q];
-  // the sum of the runs above this one, then this run's suffix sums
-  const double above = __shfl_down(incl, 1);
-  double s = (lane_id() + 1 < WAVE ? above : 0.0) + after;
-  for (int k = k1 - 1; k >= k0; --k) {
-    s += lm[k];
-    suf[a.node_off + k] = s;
+  if (threadIdx.x < WAVE) {
+    double tot = 0.0;
+    for (int w = NW - 1; w >= 0; --w) tot += sh[w];
+    const uint32_t cur = (uint32_t)(s_ep + 1) << 2;
+    double above = 0.0;
+    if (bx == b.first_blk) {
+      if (lane_id() == 0) fs_put(f.rec + 4 * bx, cur | FS_INCL, 0, tot);
+    } else {
+      if (lane_id() == 0) fs_put(f.rec + 4 * bx, cur | FS_AGG, 0, tot);
+      for (int top = bx - 1; top >= b.first_blk; top -= WAVE) {
+        const int p = top - lane_id();
+        const bool in = p >= b.first_blk;
+        uint32_t t = 0;
+        long long pv = 0;
+        double pe = 0.0;
+        if (in) {
+          int spin = 0;
+          t = fs_get(f.rec + 4 * p, &pv, &pe);
+          while ((t & ~3u) != cur && ++spin < FS_SPIN) {
+            __builtin_amdgcn_s_sleep(2);
+            t = fs_get(f.rec + 4 * p, &pv, &pe);
+          }
+          if ((t & ~3u) != cur) atomicOr(f.err, E_SCAN);
+        }
+        const unsigned long long im = __ballot(in && t == (cur | FS_INCL));
+        const int stop = im ? __ffsll((long long)im) - 1 : WAVE;
+        double x = (in && lane_id() <= stop && (t & ~3u) == cur) ? pe : 0.0;
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d);
+        above += x;
+        if (im) break;
+      }
+      if (lane_id() == 0) fs_put(f.rec + 4 * bx, cur | FS_INCL, 0, above + tot);
+    }
+    if (lane_id() == 0) {
+      s_above = above;
+      if (q == 0) {                     // every cell of the tube is in
+        const double total = above + tot;
+        a.lamEs += (nb ? 0.5 * nb[0] : 0.0) + total;
+        a.cw += a.w0 * total;
+        a.dalpha += a.lamEs * a.s_co * a.dt;
+      }
+    }
   }
+  __syncthreads();
+  double s = s_above + (incl - loc);
+  for (int w = NW - 1; w > wv; --w) s += sh[w];
+#pragma unroll
+  for (int i = FB_PER - 1; i >= 0; --i) {
+    if (k + i >= N) continue;
+    s += v[i];
+    f.suf[a.node_off + k + i] = s;
+    if (k + i == N - 1) f.suf[a.node_off + N] = 0.0;
+  }
+  // the last block out advances the epoch (every block read it before this)
   if (threadIdx.x == 0) {
-    const double total = s;          // thread 0's run starts at cell 0
-    suf[a.node_off + N] = 0.0;
-    a.lamEs += total;
-    a.cw += a.w0 * total;
-    a.dalpha += a.lamEs * a.s_co * a.dt;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    const unsigned long long d = __hip_atomic_fetch_add(epoch + 1, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (d == gridDim.x - 1) {
+      __hip_atomic_store(epoch + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(epoch, s_ep + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
   }
 }
 
-// One lepton slot, step j in reverse: field term at the post-step position,
-// drift, recoil (identity), kick; node-field adjoint into LDS (s_eb, sorted
-// chunks) or global memory (tail).
-__device__ __forceinline__ void adj_one(const AdjCtx& c, long long slot, int tile, double* s_eb, long long inj0,
-                                        long long inj1) {
+// One live lepton, step j in reverse: field term at the post-step position,
+// drift, recoil (identity), kick.  e, sd: the adjoint of its cell's field
+// after the step and the sum of those above it, less the tube's total (dead
+// after the step: unused); e0, e1: the node field around it before.  Gives
+// the adjoint of the field it was kicked by.
+__device__ __forceinline__ float adj_push(const AdjTube& a, uint32_t p0, uint32_t p1, float u1, float w, int cell0,
+                                          double e, double sd, float e0, float e1, float* lxi, float* lu, float* lw) {
+  const float dt = (float)a.dt, cfl = (float)a.cfl;
+  const double w0 = a.w0;
+  if (p1 != TAPE_DEAD) {
+    const double xi1 = (double)(p1 & 0xFFFFFFu) * 5.9604644775390625e-8;
+    *lxi += (float)(-w0 * (double)w * e);
+    // w0 ((1 - xi) lamE_k + sum_{m>k} lamE_m), less the common w0 sum_m lamE_m
+    *lw += (float)(w0 * ((1.0 - xi1) * e + sd));
+    const float g = sqrtf(1.0f + u1 * u1);
+    *lu += *lxi * cfl / (g * g * g);
+  } else {
+    // gone during step j: absorbed below the surface (its charge enters E_s)
+    // or out of the top of the box
+    *lxi = 0.0f;
+    *lu = 0.0f;
+    *lw = (float)((cell0 < a.N / 2 ? a.lamEs * w0 : 0.0) - a.cw);
+  }
+  const float lEp = (w < 0.0f ? -1.0f : 1.0f) * dt * *lu;
+  *lxi += lEp * (e1 - e0);
+  return lEp;
+}
+
+// A slot of the tail: global memory for the field adjoints.
+__device__ __forceinline__ void adj_tail(const AdjCtx& c, long long slot, int tile, long long inj0, long long inj1) {
   const uint32_t p0 = c.pos0[slot];
   if (p0 == TAPE_DEAD) return;
   const Tile tl = c.tiles[tile];
   AdjTube& a = c.at[tl.tube];
-  const double w0 = a.w0;
-  const float dt = (float)a.dt, cfl = (float)a.cfl;
   const float w = c.wlast[slot];
-  const float sg = w < 0.0f ? -1.0f : 1.0f;
-  const int off0 = (int)(p0 >> FRAC);
-  const int cell0 = tl.base + off0;
+  const int cell0 = tl.base + (int)(p0 >> FRAC);
   const float xi0 = (float)(p0 & 0xFFFFFFu) * 5.9604645e-8f;
   float lxi = c.lxi[slot], lu = c.lu[slot], lw = c.lw[slot];
   const uint32_t p1 = c.pos1[slot];
+  double e = 0.0, sd = 0.0;
   if (p1 != TAPE_DEAD) {
     const int cell1 = tl.base + (int)(p1 >> FRAC);
-    const double xi1 = (double)(p1 & 0xFFFFFFu) * 5.9604644775390625e-8;
-    const double e = c.lamE[a.cell_off + cell1];
-    lxi += (float)(-w0 * (double)w * e);
-    // w0 ((1 - xi) lamE_k + sum_{m>k} lamE_m), less the common w0 sum_m lamE_m
-    lw += (float)(w0 * ((1.0 - xi1) * e + (c.suf[a.node_off + cell1 + 1] - c.suf[a.node_off])));
-    const float u1 = c.u1[slot];
-    const float g = sqrtf(1.0f + u1 * u1);
-    lu += lxi * cfl / (g * g * g);
-  } else {
-    // gone during step j: absorbed below the surface (its charge enters E_s)
-    // or out of the top of the box
-    lxi = 0.0f;
-    lu = 0.0f;
-    lw = (float)((cell0 < a.N / 2 ? a.lamEs * w0 : 0.0) - a.cw);
+    e = c.lamE[a.cell_off + cell1];
+    sd = c.suf[a.node_off + cell1 + 1] - c.suf[a.node_off];
   }
-  const float e0 = c.eb0[a.node_off + cell0], e1 = c.eb0[a.node_off + cell0 + 1];
-  const float lEp = sg * dt * lu;
-  lxi += lEp * (e1 - e0);
-  const double d0 = (double)((1.0f - xi0) * lEp), d1 = (double)(xi0 * lEp);
-  if (s_eb) {
-    atomicAdd(&s_eb[off0], d0);
-    atomicAdd(&s_eb[off0 + 1], d1);
-  } else {
-    atomicAdd(&c.lamEb[a.node_off + cell0], d0);
-    atomicAdd(&c.lamEb[a.node_off + cell0 + 1], d1);
-  }
+  const float lEp = adj_push(a, p0, p1, c.u1[slot], w, cell0, e, sd, c.eb0[a.node_off + cell0],
+                             c.eb0[a.node_off + cell0 + 1], &lxi, &lu, &lw);
+  atomicAdd(&c.lamEb[a.node_off + cell0], (double)((1.0f - xi0) * lEp));
+  atomicAdd(&c.lamEb[a.node_off + cell0 + 1], (double)(xi0 * lEp));
   if (slot >= inj0 && slot < inj1) {
     // injected at the start of step j with weight -inj_w; its injection also
     // raised E_s by inj_w w0
-    atomicAdd(&a.dinjw, -(double)lw + (a.lamEs * w0 - a.cw));
+    atomicAdd(&a.dinjw, -(double)lw + (a.lamEs * a.w0 - a.cw));
     lxi = 0.0f;
     lu = 0.0f;
     lw = 0.0f;
@@ -233,48 +279,85 @@ __device__ __forceinline__ void adj_one(const AdjCtx& c, long long slot, int til
   c.lw[slot] = lw;
 }
 
+// The leptons of step j in reverse.  Sorted slots: a contiguous range of
+// chunks per workgroup, VEC slots per thread in 16-byte accesses, and the
+// tile's field adjoints, suffix sums and node field in an LDS window beside
+// the one that collects the node-field adjoints (injected electrons are in
+// the tail).  Tail slots go through global memory.
+// Bound by HBM: both ends of the step (12 B of the tape), the weight, and
+// three adjoints in and out, 40 B a slot.  4.0e6 slots took 56 us with a
+// chunk and a window per workgroup and gathers from global memory.
+constexpr int ADJ_GRID = 1024;
+
 __global__ __launch_bounds__(TPB) void k_adj_leptons(AdjCtx c) {
-  __shared__ double s_eb[WIN + 2];
+  __shared__ double s_acc[WIN + 2];
+  __shared__ double s_lam[WIN], s_sd[WIN];
+  __shared__ float s_e0[WIN + 2];
   const TapeMeta m = *c.meta0;
   const long long S = m.S, used = m.used;
-  const long long inj0 = S + m.tail_pre, inj1 = S + m.tail_post;
   const long long nsc = S / CHUNK, ntp = (used - S + TPB - 1) / TPB;
-  for (long long q = blockIdx.x; q < nsc + ntp; q += gridDim.x) {
-    if (q < nsc) {
-      const int tile = c.chunk[q];
-      for (int j = threadIdx.x; j < WIN + 2; j += blockDim.x) s_eb[j] = 0.0;
+  const int j0 = (int)threadIdx.x;
+  long long q0, q1;
+  chunk_range(nsc, gridDim.x, blockIdx.x, &q0, &q1);
+  int held = -1;
+  Tile tl{};
+  for (int j = j0; j < WIN + 2; j += TPB) s_acc[j] = 0.0;
+  auto flush = [&](const AdjTube& a) {
+    for (int j = j0; j <= WIN; j += TPB) {
+      const double v = s_acc[j];
+      if (v != 0.0) {
+        atomicAdd(&c.lamEb[a.node_off + tl.base + j], v);
+        s_acc[j] = 0.0;
+      }
+    }
+  };
+  for (long long q = q0; q < q1; ++q) {
+    const long long s0 = q * CHUNK + VEC * j0;
+    const uint4 p0 = *reinterpret_cast<const uint4*>(c.pos0 + s0), p1 = *reinterpret_cast<const uint4*>(c.pos1 + s0);
+    const float4 u1 = *reinterpret_cast<const float4*>(c.u1 + s0), w = *reinterpret_cast<const float4*>(c.wlast + s0);
+    float4 lxi = *reinterpret_cast<const float4*>(c.lxi + s0), lu = *reinterpret_cast<const float4*>(c.lu + s0),
+           lw = *reinterpret_cast<const float4*>(c.lw + s0);
+    const int tile = cptr(c.chunk)[q];
+    if (tile != held) {
       __syncthreads();
-#pragma unroll
-      for (int v = 0; v < VEC; ++v) adj_one(c, q * CHUNK + v * TPB + threadIdx.x, tile, s_eb, inj0, inj1);
-      __syncthreads();
-      const Tile tl = c.tiles[tile];
+      if (held >= 0) flush(c.at[tl.tube]);
+      held = tile;
+      tl = c.tiles[tile];
       const AdjTube& a = c.at[tl.tube];
-      for (int j = threadIdx.x; j <= WIN; j += blockDim.x) {
-        const double v = s_eb[j];
-        if (v != 0.0) atomicAdd(&c.lamEb[a.node_off + tl.base + j], v);
+      const int cell = tl.base + j0;
+      const bool in = cell >= 0 && cell < a.N;
+      s_lam[j0] = in ? c.lamE[a.cell_off + cell] : 0.0;
+      s_sd[j0] = in ? c.suf[a.node_off + cell + 1] - c.suf[a.node_off] : 0.0;
+      for (int j = j0; j <= WIN; j += TPB) {
+        const int node = tl.base + j;
+        s_e0[j] = node >= 0 && node <= a.N ? c.eb0[a.node_off + node] : 0.0f;
       }
       __syncthreads();
-    } else {
-      const long long slot = S + (q - nsc) * TPB + threadIdx.x;
-      if (slot < used) adj_one(c, slot, c.tt[slot], nullptr, inj0, inj1);
     }
+    const AdjTube& a = c.at[tl.tube];
+    auto one = [&](uint32_t x0, uint32_t x1, float uu, float ww, float& gx, float& gu, float& gw) {
+      if (x0 == TAPE_DEAD) return;
+      const int off0 = (int)(x0 >> FRAC), off1 = (int)(x1 >> FRAC);
+      const float xi0 = (float)(x0 & 0xFFFFFFu) * 5.9604645e-8f;
+      const float lEp = adj_push(a, x0, x1, uu, ww, tl.base + off0, s_lam[off1], s_sd[off1], s_e0[off0], s_e0[off0 + 1],
+                                 &gx, &gu, &gw);
+      atomicAdd(&s_acc[off0], (double)((1.0f - xi0) * lEp));
+      atomicAdd(&s_acc[off0 + 1], (double)(xi0 * lEp));
+    };
+    one(p0.x, p1.x, u1.x, w.x, lxi.x, lu.x, lw.x);
+    one(p0.y, p1.y, u1.y, w.y, lxi.y, lu.y, lw.y);
+    one(p0.z, p1.z, u1.z, w.z, lxi.z, lu.z, lw.z);
+    one(p0.w, p1.w, u1.w, w.w, lxi.w, lu.w, lw.w);
+    *reinterpret_cast<float4*>(c.lxi + s0) = lxi;
+    *reinterpret_cast<float4*>(c.lu + s0) = lu;
+    *reinterpret_cast<float4*>(c.lw + s0) = lw;
   }
-}
-
-// Node field -> cell field and surface field of the start of step j; the
-// loss term of that field (when it lies inside the window); clears lamEb.
-__global__ __launch_bounds__(ADJ_THREADS) void k_adj_nodes(double* lamE, double* lamEb, const float* Eprev, AdjTube* at) {
-  AdjTube& a = at[blockIdx.x];
-  const int N = a.N;
-  const double* nb = lamEb + a.node_off;
-  for (int k = threadIdx.x; k < N; k += blockDim.x) {
-    double v = (k < N - 1) ? 0.5 * (nb[k] + nb[k + 1]) : 0.5 * nb[N - 1] + nb[N];
-    if (Eprev) v += a.lossw * (double)Eprev[a.cell_off + k];
-    lamE[a.cell_off + k] = v;
-  }
-  if (threadIdx.x == 0) a.lamEs += 0.5 * nb[0];
   __syncthreads();
-  for (int k = threadIdx.x; k <= N; k += blockDim.x) lamEb[a.node_off + k] = 0.0;
+  if (held >= 0) flush(c.at[tl.tube]);
+  for (long long q = blockIdx.x; q < ntp; q += gridDim.x) {
+    const long long slot = S + q * TPB + j0;
+    if (slot < used) adj_tail(c, slot, c.tt[slot], S + m.tail_pre, S + m.tail_post);
+  }
 }
 
 // ------------------------------------------------------------------ id map

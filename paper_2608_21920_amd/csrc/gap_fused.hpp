@@ -29,7 +29,7 @@ namespace gap {
 
 constexpr int FUSED_PRE = 8;   // workgroups before the passes (one XCD round; the first is the prologue)
 
-// Workgroups [0, FUSED_PRE): the prologue; then gp of the photon pass; then gl
+// Workgroups [0, FUSED_PRE): the prologue (n_tubes < 0: already done); then gp of the photon pass; then gl
 // of the lepton pass (gp and gl multiples of 8, for the XCD-aware ranges).
 // The short roles come first so that a lepton pass of several rounds does
 // not keep them waiting.
@@ -37,7 +37,7 @@ template <bool Q, bool A, int V>
 __global__ __launch_bounds__(TPB, 6) void k_sorted(Ctx cx, int n_tubes, int gp, int gl) {
   const int bx = (int)blockIdx.x;
   if (bx < FUSED_PRE) {
-    if (bx == 0) prologue<A>(cx, n_tubes, false);
+    if (bx == 0 && n_tubes >= 0) prologue<A>(cx, n_tubes, false);
   } else if (bx < FUSED_PRE + gp) {
     photons_sorted<V, true>(cx, bx - FUSED_PRE, gp);
   } else {

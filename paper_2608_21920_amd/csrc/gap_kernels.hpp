@@ -1715,6 +1715,7 @@ struct FieldCtx {
   unsigned long long* fs;   // single-pass form: a four-word record per block, then the epoch and a done count
   double* E0;         // filtered tubes: the reference field (set in mode 1)
   double* Du;         // filtered tubes, mode 0: E_u - E0, which k_filter smooths
+  double* loss;       // window steps: per block, the sum over the steps of its sum of E^2 (else null)
   Ctl* pc;            // photon store: its tail snapshot for the next step is taken here
   int mode;           // 0: step (surface update, step += 1); 1: rebuild E only
 };
@@ -2009,6 +2010,7 @@ __global__ __launch_bounds__(FB_THREADS) void k_field_1p(FieldCtx f) {
   const double Es = s_es;
   const long long bgu = T.bg_unit;
   double eprev = k == 0 ? Es : (double)(run + bgu * (long long)(k - 1) + bgu / 2) * T.scale + Es;
+  double e2 = 0.0;
 #pragma unroll
   for (int i = 0; i < FB_PER; ++i) {
     const int kk = k + i;
@@ -2020,6 +2022,7 @@ __global__ __launch_bounds__(FB_THREADS) void k_field_1p(FieldCtx f) {
         f.Du[T.cell_off + kk] = e - f.E0[T.cell_off + kk];
       } else {
         f.E[T.cell_off + kk] = (float)e;
+        e2 += (double)(float)e * (double)(float)e;
         f.ebar[T.node_off + kk] = (float)(0.5 * (eprev + e));
         if (filt) f.E0[T.cell_off + kk] = e;
       }
@@ -2032,6 +2035,18 @@ __global__ __launch_bounds__(FB_THREADS) void k_field_1p(FieldCtx f) {
       if (!frozen && !(filt && f.mode == 0)) f.ebar[T.node_off + N] = (float)e;   // ghost E_{N+1/2} = E_{N-1/2}
       f.rho_last[T.node_off + N] = f.rho[T.node_off + N];
       f.rho[T.node_off + N] = 0;
+    }
+  }
+  if (f.loss != nullptr) {              // (fixed order of summation)
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) e2 += __shfl_xor(e2, d);
+    __shared__ double s_e2[NW];
+    if (lane_id() == 0) s_e2[wv] = e2;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      double t = 0.0;
+      for (int w = 0; w < NW; ++w) t += s_e2[w];
+      f.loss[blockIdx.x] += t;
     }
   }
   if (threadIdx.x == 0 && f.mode == 0 && b.k0 == 0) T.step += 1;
