@@ -262,7 +262,7 @@ struct gap_t {
   int n_fb = 0;
   long long* part = nullptr;
   long long* part2 = nullptr;
-  unsigned long long* fscan = nullptr;   // single-pass field: 4 words per block, epoch, done count
+  unsigned long long* fscan = nullptr;   // single-pass field: 4 words per block, then an epoch per tube
   // device words the host reads back at every synchronising call: the sticky
   // error bits, and each store's chunk count + 1 as its last re-sort left it
   struct Status { int err, pad; long long chunks[2]; };
@@ -1006,7 +1006,7 @@ int backward_alloc(gap_t* g) {
   w.lamE = (double*)walloc(g, (size_t)g->total_cells * 8);
   w.suf = (double*)walloc(g, (size_t)g->total_nodes * 8);
   for (int b = 0; b < 2; ++b) w.lamEb[b] = (double*)walloc(g, (size_t)g->total_nodes * 8);
-  w.frec = (unsigned long long*)walloc(g, sizeof(unsigned long long) * (4 * (size_t)g->n_fb + 2));
+  w.frec = (unsigned long long*)walloc(g, sizeof(unsigned long long) * (4 * (size_t)g->n_fb + g->n_tubes));
   w.at = (AdjTube*)walloc(g, sizeof(AdjTube) * g->n_tubes);
   uint64_t hs = 1024;
   while (hs < 2 * (uint64_t)M) hs <<= 1;
@@ -1511,7 +1511,7 @@ int build(gap_t* g, const gap_params* p, int n_tubes) {
   g->fb = (FBlk*)dalloc(g, sizeof(FBlk) * g->n_fb);
   g->part = (long long*)dalloc(g, sizeof(long long) * g->n_fb);
   g->part2 = (long long*)dalloc(g, sizeof(long long) * g->n_fb);
-  g->fscan = (unsigned long long*)dalloc(g, sizeof(unsigned long long) * (4 * (size_t)g->n_fb + 2));
+  g->fscan = (unsigned long long*)dalloc(g, sizeof(unsigned long long) * (4 * (size_t)g->n_fb + g->n_tubes));
   if (g->any_filter) {
     g->E0 = (double*)dalloc(g, sizeof(double) * g->total_cells);
     g->Du = (double*)dalloc(g, sizeof(double) * g->total_cells);
