@@ -36,6 +36,7 @@ constexpr double kPi = 3.14159265358979323846;
 constexpr double kTwo24 = 16777216.0;
 
 constexpr int kGrid = 2048;        // workgroups of the particle passes (multiple of 8)
+constexpr int kDiagGrid = 1024;    // workgroups of the diagnostics' passes (multiple of 8)
 
 // ---------------------------------------------------------------- spectrum table
 // Cumulative classical synchrotron photon-number spectrum C(xi) =
@@ -2012,7 +2013,7 @@ int gap_diag(gap_t* g, int32_t kind, int32_t tube, void* host_buf, size_t buf_by
       const long long nacc = (long long)nb * PROF_G * PROF_M;
       k_fill_i64<<<std::max(1, (int)std::min<long long>(1024, (nacc + 255) / 256)), 256, 0, g->s>>>(
           (long long*)g->prof_acc, nacc, 0);
-      k_profile<<<kGrid, TPB, 0, g->s>>>(make_ctx(g), tube, B, nb, g->prof_acc);
+      k_profile<<<kDiagGrid, TPB, 0, g->s>>>(make_ctx(g), tube, B, nb, g->prof_acc);
       const double bppc = (double)B * (double)g->P[tube].ppc_ref;
       if (kind == GAP_DIAG_PROFILE) {
         k_profile_finish<<<std::max(1, std::min(1024, (nb * PROF_G + 255) / 256)), 256, 0, g->s>>>(g->prof_acc, nb,
@@ -2075,7 +2076,9 @@ int gap_diag(gap_t* g, int32_t kind, int32_t tube, void* host_buf, size_t buf_by
       }
       k_fill_i64<<<std::max(1, (int)std::min<size_t>(1024, (n + 255) / 256)), 256, 0, g->s>>>(
           (long long*)g->phase_acc, (long long)n, 0);
-      k_phase<<<kGrid, TPB, 0, g->s>>>(make_ctx(g), tube, B, nb, g->spec_thr, g->phase_acc);
+      const int lw = phase_window(B);
+      k_phase<<<kDiagGrid, TPB, sizeof(double) * 2 * lw * PHASE_NP, g->s>>>(make_ctx(g), tube, B, nb, g->spec_thr,
+                                                                           g->phase_acc, lw);
       HIPCHK(hipStreamSynchronize(g->s));
       HIPCHK(hipMemcpy(host_buf, g->phase_acc, sizeof(double) * n, hipMemcpyDeviceToHost));
       return sync_and_err(g);
@@ -2083,7 +2086,7 @@ int gap_diag(gap_t* g, int32_t kind, int32_t tube, void* host_buf, size_t buf_by
     case GAP_DIAG_SPECTRA: {
       if (!fits(sizeof(double) * 3 * SPEC_NB)) return GAP_EINVAL;
       k_fill_i64<<<1, 256, 0, g->s>>>((long long*)g->spec_acc, 3 * SPEC_NB, 0);
-      k_spectra<<<kGrid, TPB, 0, g->s>>>(make_ctx(g), tube, g->spec_thr, g->spec_acc);
+      k_spectra<<<kDiagGrid, TPB, 0, g->s>>>(make_ctx(g), tube, g->spec_thr, g->spec_acc);
       HIPCHK(hipStreamSynchronize(g->s));
       HIPCHK(hipMemcpy(host_buf, g->spec_acc, sizeof(double) * 3 * SPEC_NB, hipMemcpyDeviceToHost));
       return sync_and_err(g);

@@ -51,111 +51,150 @@ __device__ __forceinline__ void prof_wave_add(int key, double v0, double v1, dou
   }
 }
 
-// Profile moments of one slot: key = bin * PROF_G + group (-1: none).
-__device__ __forceinline__ int prof_moments(const Ctx& cx, bool lep, uint32_t slot, int tile, int tube, int B,
-                                            double* v0, double* v1, double* v2) {
+// Profile moments of one particle of tube T: key = bin * PROF_G + group (-1:
+// none).  a: lepton weight or photon energy (0: no particle); u: lepton
+// momentum; pw: photon weight.
+__device__ __forceinline__ int prof_moments(const Tube& T, bool lep, int base, uint32_t pos, float a, float u, float pw,
+                                            int B, double* v0, double* v1, double* v2) {
   *v0 = *v1 = *v2 = 0.0;
-  if (tile < 0) return -1;
-  const Tile tl = cx.tiles[tile];
-  const float a = lep ? cx.L.w[slot] : cx.P.x[slot];
-  if (tl.tube != tube || a == 0.0f) return -1;
-  const Tube& T = cx.tubes[tube];
-  const uint32_t pos = lep ? cx.L.pos[slot] : cx.P.pos[slot];
-  int cell = tl.base + (int)(pos >> FRAC);
+  if (a == 0.0f) return -1;
+  int cell = base + (int)(pos >> FRAC);
   if (T.flags & F_PERIODIC) cell = wrap_cell(cell, T.N);
   const int bin = min(max(cell, 0), T.N - 1) / B;
   if (lep) {
-    const double u = (double)cx.L.u[slot];
+    const double ud = (double)u;
     const double w = fabs((double)a);
-    const double g = sqrt(1.0 + u * u);
+    const double g = sqrt(1.0 + ud * ud);
     *v0 = w;
     *v1 = w * g;
     *v2 = w / (g * g * g);
-    return bin * PROF_G + (a < 0.0f ? 0 : 2) + (u > 0.0 ? 0 : 1);
+    return bin * PROF_G + (a < 0.0f ? 0 : 2) + (ud > 0.0 ? 0 : 1);
   }
   if (!(fabsf(a) > 2.0f)) return -1;
-  const double w = (double)cx.P.w[slot];
+  const double w = (double)pw;
   *v0 = w;
   *v1 = w * fabs((double)a);
   return bin * PROF_G + 4 + (a > 0.0f ? 0 : 1);
 }
 
-constexpr int PROF_LW = 80;   // LDS window of bins per workgroup (bins of >= 4 cells cover a tile's 256-cell window)
+// The sorted part of one store, for the diagnostics of one tube: workgroup bx
+// of G takes a contiguous range of chunks, VEC slots per thread in 16-byte
+// loads, and calls enter(tile) (block-uniform) when the tile changes and
+// slot(tile base, position, w or x, u or 0, 0 or photon w) for every slot.
+template <class Enter, class Slot>
+__device__ __forceinline__ void diag_sorted(const Ctx& cx, bool lep, int tube, Enter enter, Slot each) {
+  long long c0, c1;
+  chunk_range((lep ? cx.lc : cx.pc)->n_sorted_chunks, gridDim.x, blockIdx.x, &c0, &c1);
+  const CPtr<int32_t> chunk = cptr(lep ? cx.lchunk : cx.pchunk);
+  const float* const fa = lep ? cx.L.w : cx.P.x;
+  const float* const fb = lep ? cx.L.u : cx.P.w;
+  const uint32_t* const fp = lep ? cx.L.pos : cx.P.pos;
+  int held = -1, base = 0;
+  bool mine = false;
+  for (long long c = c0; c < c1; ++c) {
+    const int tile = chunk[c];
+    if (tile != held) {
+      held = tile;
+      const Tile tl = cx.tiles[tile];
+      base = tl.base;
+      mine = tl.tube == tube;
+      if (mine) enter(base);
+    }
+    if (!mine) continue;
+    const long long s0 = c * CHUNK + VEC * (int)threadIdx.x;
+    float a[VEC], b[VEC];
+    uint32_t p[VEC];
+    rec_get(rec_load<float, VEC>(fa + s0), a);
+    rec_get(rec_load<float, VEC>(fb + s0), b);
+    rec_get(rec_load<uint32_t, VEC>(fp + s0), p);
+#pragma unroll
+    for (int j = 0; j < VEC; ++j) each(base, p[j], a[j], b[j]);
+  }
+}
+// The tail of one store, strided over all workgroups: one slot per lane (the
+// lanes of a wave go together; a lane without a particle of the tube has a = 0).
+template <class Slot>
+__device__ __forceinline__ void diag_tail(const Ctx& cx, bool lep, int tube, Slot each) {
+  const Ctl* ctl = lep ? cx.lc : cx.pc;
+  const long long S = ctl->n_sorted_chunks * CHUNK, tail = ctl->tail;
+  const long long nsq = S / TPB, nq = nsq + (tail + TPB - 1) / TPB;
+  for (long long q = nsq + blockIdx.x; q < nq; q += gridDim.x) {
+    uint32_t slot;
+    int tile;
+    piece_slot(q, nsq, S, tail, lep ? cx.lchunk : cx.pchunk, lep ? cx.ltt : cx.ptt, &slot, &tile);
+    const Tile tl = cx.tiles[tile >= 0 ? tile : 0];
+    const bool in = tile >= 0 && tl.tube == tube;
+    each(tl.base, lep ? cx.L.pos[slot] : cx.P.pos[slot], in ? (lep ? cx.L.w[slot] : cx.P.x[slot]) : 0.0f,
+         lep ? cx.L.u[slot] : cx.P.w[slot]);
+  }
+}
+
+constexpr int PROF_LDS = 80 * PROF_G * PROF_M;   // LDS sums of a workgroup
 
 // Moments of tube `tube`'s particles into acc[nb][PROF_G][PROF_M], which the
-// caller has zeroed.  Each workgroup takes a contiguous range of the sorted
-// rows of each store (one slot per thread and 256-slot row): their particles
-// lie within a tile's window, so with bins of at least 4 cells they are summed
-// into an LDS window of bins (FP64 LDS atomics), flushed to acc when the tile
-// changes and at the end; tail rows (and narrower bins) add to acc directly,
-// one atomic per distinct key of a wave.
+// caller has zeroed.  The particles of a sorted chunk lie within its tile's
+// 256-cell window, so with bins of at least 4 cells they are summed into an
+// LDS window of bins (FP64 LDS atomics), flushed to acc when the tile changes
+// and at the end; tail rows (and narrower bins) add to acc directly, one
+// atomic per distinct key of a wave.  Few bins in the window mean many lanes
+// on one word, served one at a time: the window is kept in as many copies as
+// the LDS holds (up to 16), a lane's copy by its index (4.0e6 particles, bins
+// of 64 cells: 37 us with one copy and one slot per thread).
 __global__ __launch_bounds__(TPB) void k_profile(Ctx cx, int tube, int B, int nb, double* acc) {
-  __shared__ double s_w[PROF_LW * PROF_G * PROF_M];
+  __shared__ double s_w[PROF_LDS];
   const bool win = B >= 4;
-  for (int j = threadIdx.x; j < PROF_LW * PROF_G * PROF_M; j += blockDim.x) s_w[j] = 0.0;
+  const int lw = win ? (WIN - 1) / B + 2 : 1;            // bins a tile's window can reach
+  const int stride = lw * PROF_G * PROF_M;
+  int copies = 1;
+  while (copies < 16 && 2 * copies * stride <= PROF_LDS) copies *= 2;
+  const Tube& T = cx.tubes[tube];
+  for (int j = threadIdx.x; j < PROF_LDS; j += blockDim.x) s_w[j] = 0.0;
   int lo = -1;                              // first bin of the LDS window (block-uniform)
   __syncthreads();
+  auto flush = [&]() {
+    __syncthreads();
+    if (lo >= 0)
+      for (int j = threadIdx.x; j < stride; j += blockDim.x) {
+        double v = 0.0;
+        for (int r = 0; r < copies; ++r) {
+          v += s_w[r * stride + j];
+          s_w[r * stride + j] = 0.0;
+        }
+        if (v != 0.0 && lo + j / (PROF_G * PROF_M) < nb) atomicAdd(&acc[(size_t)lo * PROF_G * PROF_M + j], v);
+      }
+    __syncthreads();
+  };
   for (int sp = 0; sp < 2; ++sp) {
     const bool lep = sp == 0;
-    const Ctl* ctl = lep ? cx.lc : cx.pc;
-    const long long S = ctl->n_sorted_chunks * CHUNK, tail = ctl->tail;
-    const long long nsq = S / TPB, nq = nsq + (tail + TPB - 1) / TPB;
-    const int32_t* chunk = lep ? cx.lchunk : cx.pchunk;
-    const int32_t* tt = lep ? cx.ltt : cx.ptt;
-    // sorted rows: a contiguous range per workgroup
-    const long long r0 = nsq * blockIdx.x / gridDim.x, r1 = nsq * (blockIdx.x + 1) / gridDim.x;
-    for (long long q = r0; q < r1; ++q) {
-      uint32_t slot;
-      int tile;
-      piece_slot(q, nsq, S, tail, chunk, tt, &slot, &tile);
+    diag_sorted(
+        cx, lep, tube,
+        [&](int base) {
+          const int wl = max(base, 0) / B;
+          if (win && wl != lo) {
+            flush();
+            lo = wl;
+          }
+        },
+        [&](int base, uint32_t pos, float a, float b) {
+          double v0, v1, v2;
+          const int key = prof_moments(T, lep, base, pos, a, b, b, B, &v0, &v1, &v2);
+          const int kb = win && key >= 0 ? key / PROF_G - lo : -1;
+          const bool in = kb >= 0 && kb < lw;
+          if (in) {
+            double* e = &s_w[(lane_id() & (copies - 1)) * stride + (kb * PROF_G + key % PROF_G) * PROF_M];
+            atomicAdd(&e[0], v0);
+            atomicAdd(&e[1], v1);
+            if (v2 != 0.0) atomicAdd(&e[2], v2);
+          }
+          if (__ballot(key >= 0 && !in)) prof_wave_add(in ? -1 : key, v0, v1, v2, acc);   // (every lane takes part)
+        });
+    diag_tail(cx, lep, tube, [&](int base, uint32_t pos, float a, float b) {
       double v0, v1, v2;
-      const int key = prof_moments(cx, lep, slot, tile, tube, B, &v0, &v1, &v2);
-      if (win) {
-        // the row's tile (uniform: a sorted row lies in one chunk) sets the window
-        const int wl = __builtin_amdgcn_readfirstlane(max(cx.tiles[tile].base, 0) / B);
-        if (wl != lo) {
-          __syncthreads();
-          if (lo >= 0)
-            for (int j = threadIdx.x; j < PROF_LW * PROF_G * PROF_M; j += blockDim.x) {
-              const double v = s_w[j];
-              if (v != 0.0) {
-                const int bb = lo + j / (PROF_G * PROF_M);
-                if (bb < nb) atomicAdd(&acc[(size_t)lo * PROF_G * PROF_M + j], v);
-                s_w[j] = 0.0;
-              }
-            }
-          lo = wl;
-          __syncthreads();
-        }
-        const int kb = key >= 0 ? key / PROF_G - lo : -1;
-        const bool in = kb >= 0 && kb < PROF_LW;
-        if (in) {
-          double* e = &s_w[((size_t)kb * PROF_G + key % PROF_G) * PROF_M];
-          atomicAdd(&e[0], v0);
-          atomicAdd(&e[1], v1);
-          if (v2 != 0.0) atomicAdd(&e[2], v2);
-        }
-        prof_wave_add(in ? -1 : key, v0, v1, v2, acc);   // (every lane takes part)
-      } else {
-        prof_wave_add(key, v0, v1, v2, acc);
-      }
-    }
-    // tail rows: strided over all workgroups
-    for (long long q = nsq + blockIdx.x; q < nq; q += gridDim.x) {
-      uint32_t slot;
-      int tile;
-      piece_slot(q, nsq, S, tail, chunk, tt, &slot, &tile);
-      double v0, v1, v2;
-      const int key = prof_moments(cx, lep, slot, tile, tube, B, &v0, &v1, &v2);
+      const int key = prof_moments(T, lep, base, pos, a, b, b, B, &v0, &v1, &v2);
       prof_wave_add(key, v0, v1, v2, acc);
-    }
+    });
   }
-  __syncthreads();
-  if (lo >= 0)
-    for (int j = threadIdx.x; j < PROF_LW * PROF_G * PROF_M; j += blockDim.x) {
-      const double v = s_w[j];
-      if (v != 0.0 && lo + j / (PROF_G * PROF_M) < nb) atomicAdd(&acc[(size_t)lo * PROF_G * PROF_M + j], v);
-    }
+  flush();
 }
 
 // Sums to the profile: out[nb][PROF_G][3] = multiplicity, <gamma> (photons
@@ -317,14 +356,17 @@ __global__ void k_fft_power(const double2* X, int M, double* P) {
 constexpr int SPEC_EDGES = 89;
 constexpr int SPEC_NB = SPEC_EDGES + 1;
 
-__device__ __forceinline__ int spec_bin(const double* thr, double p2) {
-  int lo = 0, hi = SPEC_EDGES;              // count of edges <= p2, in [0, SPEC_EDGES]
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (thr[mid] <= p2) lo = mid + 1;
-    else hi = mid;
-  }
-  return lo;
+// (A guess from the FP32 logarithm, off by at most one bin, settled by the
+// exact comparisons with its two edges.)
+__device__ __forceinline__ int spec_bin(const double* thr, float p) {
+  const double p2 = (double)p * (double)p;
+  if (!(p2 >= thr[0])) return 0;
+  // edges at log2 |p| = (b - 16) log2(10) / 8
+  const int c = (int)floorf(__log2f(fabsf(p)) * (8.0f * 0.30102999566398120f)) + 17;
+  int n = min(max(c, 1), SPEC_EDGES);
+  if (n < SPEC_EDGES && thr[n] <= p2) ++n;
+  else if (thr[n - 1] > p2) --n;
+  return n;
 }
 
 __global__ __launch_bounds__(TPB) void k_spectra(Ctx cx, int tube, const double* thr, double* acc) {
@@ -335,28 +377,13 @@ __global__ __launch_bounds__(TPB) void k_spectra(Ctx cx, int tube, const double*
   __syncthreads();
   for (int sp = 0; sp < 2; ++sp) {
     const bool lep = sp == 0;
-    const Ctl* ctl = lep ? cx.lc : cx.pc;
-    const long long S = ctl->n_sorted_chunks * CHUNK, tail = ctl->tail;
-    const long long nsq = S / TPB, nq = nsq + (tail + TPB - 1) / TPB;
-    const int32_t* chunk = lep ? cx.lchunk : cx.pchunk;
-    const int32_t* tt = lep ? cx.ltt : cx.ptt;
-    for (long long q = blockIdx.x; q < nq; q += gridDim.x) {
-      uint32_t slot;
-      int tile;
-      piece_slot(q, nsq, S, tail, chunk, tt, &slot, &tile);
-      if (tile < 0 || cx.tiles[tile].tube != tube) continue;
-      if (lep) {
-        const float w = cx.L.w[slot];
-        if (w == 0.0f) continue;
-        const double u = (double)cx.L.u[slot];
-        atomicAdd(&s_h[(w < 0.0f ? 0 : 1) * SPEC_NB + spec_bin(s_thr, u * u)], (double)fabsf(w));
-      } else {
-        const float x = cx.P.x[slot];
-        if (x == 0.0f) continue;
-        const double xd = (double)x;
-        atomicAdd(&s_h[2 * SPEC_NB + spec_bin(s_thr, xd * xd)], (double)cx.P.w[slot]);
-      }
-    }
+    auto add = [&](int, uint32_t, float a, float b) {
+      if (a == 0.0f) return;
+      const int s3 = lep ? (a < 0.0f ? 0 : 1) : 2;
+      atomicAdd(&s_h[s3 * SPEC_NB + spec_bin(s_thr, lep ? b : a)], (double)(lep ? fabsf(a) : b));
+    };
+    diag_sorted(cx, lep, tube, [](int) {}, add);
+    diag_tail(cx, lep, tube, add);
   }
   __syncthreads();
   for (int j = threadIdx.x; j < 3 * SPEC_NB; j += blockDim.x)
@@ -366,59 +393,68 @@ __global__ __launch_bounds__(TPB) void k_spectra(Ctx cx, int tube, const double*
 // Phase space (Fig. 3, rows 1-4): the weights of the momentum spectra, per
 // bin of B cells and signed momentum column (column SPEC_NB + b for p > 0,
 // SPEC_NB - 1 - b for p <= 0, b the spectrum bin of |p|), added to
-// acc[3][nb][2 SPEC_NB] with one atomic per distinct key of a wave.
+// acc[3][nb][2 SPEC_NB].  Sorted chunks go through an LDS window of the lw
+// bins their tile can reach (2 lepton species or the photons), flushed when
+// the tile changes; the tails, and bins too narrow for the LDS (lw = 0), add
+// to acc directly.  (One global atomic per distinct key of a wave, found one
+// after the other, took 545 us for 4.0e6 particles.)
 constexpr int PHASE_NP = 2 * SPEC_NB;
-
-__device__ __forceinline__ void phase_wave_add(long long key, double v, double* acc) {
-  while (true) {
-    const uint64_t m = __ballot(key >= 0);
-    if (!m) break;
-    const int lead = __ffsll((long long)m) - 1;
-    const long long kk = __shfl(key, lead);
-    double a = key == kk ? v : 0.0;
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) a += __shfl_xor(a, d);
-    if (lane_id() == lead) atomicAdd(&acc[kk], a);
-    if (key == kk) key = -1;
-  }
+constexpr int PHASE_LDS = 60 * 1024;
+// Bins of the LDS window for bins of B cells (0: too many).
+inline int phase_window(int B) {
+  const int lw = (WIN - 1) / B + 2;
+  return 2 * lw * PHASE_NP * (int)sizeof(double) <= PHASE_LDS ? lw : 0;
 }
 
-__global__ __launch_bounds__(TPB) void k_phase(Ctx cx, int tube, int B, int nb, const double* thr, double* acc) {
+__global__ __launch_bounds__(TPB) void k_phase(Ctx cx, int tube, int B, int nb, const double* thr, double* acc, int lw) {
+  extern __shared__ double s_h[];           // [2][lw][PHASE_NP]
   __shared__ double s_thr[SPEC_EDGES];
   for (int j = threadIdx.x; j < SPEC_EDGES; j += blockDim.x) s_thr[j] = thr[j];
+  const int n = lw * PHASE_NP;
+  for (int j = threadIdx.x; j < 2 * n; j += blockDim.x) s_h[j] = 0.0;
   __syncthreads();
   const Tube& T = cx.tubes[tube];
   for (int sp = 0; sp < 2; ++sp) {
     const bool lep = sp == 0;
-    const Ctl* ctl = lep ? cx.lc : cx.pc;
-    const long long S = ctl->n_sorted_chunks * CHUNK, tail = ctl->tail;
-    const long long nsq = S / TPB, nq = nsq + (tail + TPB - 1) / TPB;
-    const int32_t* chunk = lep ? cx.lchunk : cx.pchunk;
-    const int32_t* tt = lep ? cx.ltt : cx.ptt;
-    for (long long q = blockIdx.x; q < nq; q += gridDim.x) {
-      uint32_t slot;
-      int tile;
-      piece_slot(q, nsq, S, tail, chunk, tt, &slot, &tile);
-      long long key = -1;
-      double v = 0.0;
-      if (tile >= 0 && cx.tiles[tile].tube == tube) {
-        const float a = lep ? cx.L.w[slot] : cx.P.x[slot];
-        if (a != 0.0f) {
-          const Tile tl = cx.tiles[tile];
-          const uint32_t pos = lep ? cx.L.pos[slot] : cx.P.pos[slot];
-          int cell = tl.base + (int)(pos >> FRAC);
-          if (T.flags & F_PERIODIC) cell = wrap_cell(cell, T.N);
-          cell = min(max(cell, 0), T.N - 1);
-          const double p = lep ? (double)cx.L.u[slot] : (double)a;
-          const int b = spec_bin(s_thr, p * p);
-          const int col = p > 0.0 ? SPEC_NB + b : SPEC_NB - 1 - b;
-          const int s3 = lep ? (a < 0.0f ? 0 : 1) : 2;
-          key = ((long long)s3 * nb + cell / B) * PHASE_NP + col;
-          v = lep ? (double)fabsf(a) : (double)cx.P.w[slot];
+    int lo = -1;                            // first bin of the LDS window (block-uniform)
+    auto flush = [&]() {
+      __syncthreads();
+      if (lo >= 0)
+        for (int j = threadIdx.x; j < (lep ? 2 : 1) * n; j += blockDim.x) {
+          const double v = s_h[j];
+          if (v != 0.0) {
+            const int s = j >= n ? 1 : 0, r = j - s * n;
+            atomicAdd(&acc[((size_t)(lep ? s : 2) * nb + lo) * PHASE_NP + r], v);
+            s_h[j] = 0.0;
+          }
         }
-      }
-      phase_wave_add(key, v, acc);
-    }
+      __syncthreads();
+    };
+    auto add = [&](bool window, int base, uint32_t pos, float a, float b) {
+      if (a == 0.0f) return;
+      int cell = base + (int)(pos >> FRAC);
+      if (T.flags & F_PERIODIC) cell = wrap_cell(cell, T.N);
+      cell = min(max(cell, 0), T.N - 1);
+      const float p = lep ? b : a;
+      const int m = spec_bin(s_thr, p);
+      const int col = p > 0.0f ? SPEC_NB + m : SPEC_NB - 1 - m;
+      const int s = lep && a > 0.0f ? 1 : 0, bin = cell / B;
+      const double v = (double)(lep ? fabsf(a) : b);
+      if (window && bin >= lo && bin - lo < lw) atomicAdd(&s_h[s * n + (bin - lo) * PHASE_NP + col], v);
+      else atomicAdd(&acc[((size_t)(lep ? s : 2) * nb + bin) * PHASE_NP + col], v);
+    };
+    diag_sorted(
+        cx, lep, tube,
+        [&](int base) {
+          const int wl = max(base, 0) / B;
+          if (lw > 0 && wl != lo) {
+            flush();
+            lo = wl;
+          }
+        },
+        [&](int base, uint32_t pos, float a, float b) { add(lw > 0, base, pos, a, b); });
+    diag_tail(cx, lep, tube, [&](int base, uint32_t pos, float a, float b) { add(false, base, pos, a, b); });
+    flush();
   }
 }
 
