@@ -248,10 +248,12 @@ struct gap_t {
   std::vector<Tube> th;
   std::vector<Tile> tiles_h;
   std::vector<LTile> ltiles_h;
+  std::vector<PTile> ptiles_h;
   std::vector<FBlk> fb_h;
   Tube* tubes = nullptr;
   Tile* tiles = nullptr;
   LTile* ltiles = nullptr;
+  PTile* ptiles = nullptr;
   int n_tiles = 0;
   long long total_nodes = 0, total_cells = 0;
   int max_cells = 1;   // largest tube
@@ -294,7 +296,7 @@ struct gap_t {
   double* thresh_p = nullptr;
   double tmin_l = 0.0, tmin_p = 0.0;   // smallest tube threshold of each store
   // conversion queue of the sorted photon pass (one entry per photon slot at
-  // most) and its per-workgroup entry counts
+  // most), and per workgroup of the pass the entries' number and start
   uint4* pq = nullptr;
   // discharge diagnostics: return spectra [n_tubes][RET_N]; profile sums and
   // results for the largest tube at one cell per bin
@@ -315,13 +317,13 @@ struct gap_t {
   double2* fft_buf = nullptr;   // 2 M complex values of the largest tube, allocated on first use
   double* fft_pow = nullptr;
   int* pq_count = nullptr;
+  long long* pq_start = nullptr;
   uint4* bq = nullptr;                 // birth queue of the sorted lepton pass: entries, and per
   int* bq_count = nullptr;             // workgroup of the pass their number and first entry
   long long* bq_start = nullptr;
   int pq_groups = 0;                   // entries of pq_count (bounds the photon grid)
   bool grid_lep_set = false;   // grid_lep was set or tuned
   int grid_lep = 2048, grid_pho = 2048, grid_tail = 1024;   // workgroups of the particle passes
-  int round_conv = 2048;                // one resident round of the conversion draws
   int round_lep = 2048, round_pho = 2048, cus = 256;        // one resident round of each pass; CUs
   int rmax = 64;                                            // longest re-sort interval the tile margin allows
   bool any_periodic = false;
@@ -521,6 +523,7 @@ Ctx make_ctx(gap_t* g) {
   c.tubes = g->tubes;
   c.tiles = g->tiles;
   c.ltiles = g->ltiles;
+  c.ptiles = g->ptiles;
   c.L = g->lep.lep(g->lep.cur);
   c.lc = g->lep.ctl;
   c.lchunk = g->lep.chunk[g->lep.cur];
@@ -542,6 +545,8 @@ Ctx make_ctx(gap_t* g) {
   c.shard = g->shard;
   c.pq = g->pq;
   c.pq_count = g->pq_count;
+  c.pq_start = g->pq_start;
+  c.pq_groups = g->grid_pho;
   c.bq = g->bq;
   c.bq_count = g->bq_count;
   c.bq_start = g->bq_start;
@@ -789,6 +794,9 @@ int tails_grid(const gap_t* g) { return 2 * ((g->grid_tail + 7) / 8 * 8); }
 // workgroups of the tail launch that write the sorted lepton pass's queued
 // photon births: one per CU
 int births_wg(const gap_t* g) { return std::max(16, g->cus); }
+// workgroups that write the pairs of the converted photons (segs: workgroups
+// of the photon pass, each with a queue segment)
+int pairs_wg(const gap_t* g, int segs) { return std::min(std::max(16, g->cus), segs); }
 
 // The particle kernels with the quantum branches only for handles that have
 // quantum tubes.
@@ -801,15 +809,10 @@ void launch_leptons(gap_t* g, const Ctx& cx, hipStream_t s) {
     else k_leptons<false, false><<<cx.bq_groups, TPB, 0, s>>>(cx);
   }
 }
-// The conversion draws: at least one resident round of workgroups, each
-// with CONV_SEGS queue parts (a photon grid that large keeps one part per
-// segment).
+// The pairs of the converted photons.
 void launch_conversions(gap_t* g, const Ctx& cx, hipStream_t s) {
-  const int target = CONV_SEGS * g->round_conv;
-  const int split = std::max(1, (target + g->grid_pho - 1) / g->grid_pho);
-  const int grid = (g->grid_pho * split + CONV_SEGS - 1) / CONV_SEGS;
-  if (g->any_quantum) k_conversions<true><<<grid, TPB, 0, s>>>(cx, g->grid_pho, split);
-  else k_conversions<false><<<grid, TPB, 0, s>>>(cx, g->grid_pho, split);
+  if (g->any_quantum) k_conversions<true><<<pairs_wg(g, cx.pq_groups), TPB, 0, s>>>(cx);
+  else k_conversions<false><<<pairs_wg(g, cx.pq_groups), TPB, 0, s>>>(cx);
 }
 void launch_tails(gap_t* g, const Ctx& cx, hipStream_t s) {
   if (g->any_quantum) {
@@ -830,13 +833,13 @@ void join_photon_side(gap_t* g);
 // enqueue_step.  Under graph capture everything stays on the caller's stream.
 void fork_photon_side(gap_t* g, const Ctx& cx) {
   if (g->capturing) {
-    k_photons<<<g->grid_pho, TPB, 0, g->s>>>(cx);
+    k_photons<<<cx.pq_groups, TPB, 0, g->s>>>(cx);
     launch_conversions(g, cx, g->s);
     return;
   }
   (void)hipEventRecord(g->ev_pre, g->s);
   (void)hipStreamWaitEvent(g->s2, g->ev_pre, 0);
-  k_photons<<<g->grid_pho, TPB, 0, g->s2>>>(cx);
+  k_photons<<<cx.pq_groups, TPB, 0, g->s2>>>(cx);
   launch_conversions(g, cx, g->s2);
   (void)hipEventRecord(g->ev_p, g->s2);
   g->s2_pending = true;
@@ -1163,7 +1166,7 @@ void enqueue_passes(gap_t* g, bool two, bool merged) {
     if (two) hipExtLaunchKernelGGL(k_pre, dim3(1), dim3(pre_threads(g)), 0, ps, nullptr, g->ev_pre, 0, cx, g->n_tubes);
     else k_pre<<<1, pre_threads(g), 0, ps>>>(cx, g->n_tubes);
   }
-  { Timer t(g, KT_PHOTONS, ps); k_photons<<<g->grid_pho, TPB, 0, ps>>>(cx); }
+  { Timer t(g, KT_PHOTONS, ps); k_photons<<<cx.pq_groups, TPB, 0, ps>>>(cx); }
   { Timer t(g, KT_CONV, ps); launch_conversions(g, cx, ps); }
   if (two) {
     (void)hipEventRecord(g->ev_p, g->s2);
@@ -1196,7 +1199,7 @@ bool fused_form(const gap_t* g) {
 template <bool Q, bool A, int V>
 void launch_fused(gap_t* g, const Ctx& cx, bool pre, int gp, int gl, const RestGrid& n) {
   k_sorted<Q, A, V><<<FUSED_PRE + gp + gl, TPB, 0, g->s>>>(cx, pre ? g->n_tubes : -1, gp, gl);
-  k_rest<Q, A, V><<<n.births + n.conv + n.tails + n.protons, TPB, 0, g->s>>>(cx, n);
+  k_rest<Q, A><<<n.births + n.conv + n.tails + n.protons, TPB, 0, g->s>>>(cx, n);
 }
 
 // The particle passes of one step on the caller's stream (pre: the prologue
@@ -1214,11 +1217,10 @@ void enqueue_fused(gap_t* g, Ctx cx, bool pre) {
   };
   const int gl = grid(g->seen_l, lepton_grid(g)), gp = grid(g->seen_p, std::min(g->grid_pho, g->round_pho));
   cx.bq_groups = gl;
+  cx.pq_groups = gp;
   RestGrid n;
   n.births = std::min(births_wg(g), gl);
-  n.nseg = gp;
-  n.split = known && !pieces ? VEC : 1;
-  n.conv = (gp * n.split + CONV_SEGS - 1) / CONV_SEGS;
+  n.conv = pairs_wg(g, gp);
   n.tails = tails_grid(g);
   n.protons = g->any_protons ? std::max(8, g->grid_tail) : 0;
   const int form = (g->any_quantum ? 4 : 0) | (g->any_atm ? 2 : 0) | (pieces ? 1 : 0);
@@ -1392,6 +1394,34 @@ LTile lepton_tile(const Tube& T, const Tile& tl, double xc_floor) {
   return k;
 }
 
+// The sorted photon pass's constants of one tile.
+PTile photon_tile(const Tube& T, const Tile& tl) {
+  PTile k{};
+  k.tube = tl.tube;
+  k.base = tl.base;
+  k.N = T.N;
+  k.dpho = T.dpho;
+  k.flags = (uint32_t)T.flags;
+  const bool per = (T.flags & GAP_PERIODIC) != 0;
+  const int64_t b0 = (int64_t)tl.base * (1 << FRAC), last = 0xFFFFFFFFll;
+  // a photon stays while it is in [0, L) and below H
+  const int64_t top = std::min(T.hfix, (int64_t)T.N << FRAC) - b0 - 1;
+  k.xlo = per || tl.base >= 0 ? 0u : (uint32_t)(-b0);
+  k.xtop = (uint32_t)(per ? last : std::max(std::min(top, last), (int64_t)0));
+  if (!per && top < 0) {                       // every position is above it
+    k.xlo = 1;
+    k.xtop = 0;
+  }
+  k.dt = T.dt;
+  k.inv_rc = T.inv_rc;
+  k.b = T.b;
+  k.conv_k = T.conv_k;
+  k.chi_skip = T.chi_skip;
+  k.hfix = T.hfix;
+  k.seed = T.seed;
+  return k;
+}
+
 int build(gap_t* g, const gap_params* p, int n_tubes) {
   g->n_tubes = n_tubes;
   g->P.assign(p, p + n_tubes);
@@ -1456,6 +1486,7 @@ int build(gap_t* g, const gap_params* p, int n_tubes) {
       tl.ncell = std::min(TILE, q.n_cells - tl.first);
       g->tiles_h.push_back(tl);
       g->ltiles_h.push_back(lepton_tile(T, tl, q.xc_floor));
+      g->ptiles_h.push_back(photon_tile(T, tl));
     }
     const int nb = (q.n_cells + FB_NODES - 1) / FB_NODES;
     const int first = (int)g->fb_h.size();
@@ -1484,9 +1515,6 @@ int build(gap_t* g, const gap_params* p, int n_tubes) {
     HIPCHK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     HIPCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nl, k_leptons<false, false>, TPB, 0));
     HIPCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&np, k_photons, TPB, 0));
-    int nc = 0;
-    HIPCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nc, k_conversions<false>, TPB, 0));
-    g->round_conv = std::max(8, cus * std::max(nc, 1));
     // defaults measured on the production gap (2e7 particles): one resident
     // round for the lepton pass, four for the photon pass (short ranges keep
     // its conversion queue segments small), two workgroups per CU for each
@@ -1504,7 +1532,8 @@ int build(gap_t* g, const gap_params* p, int n_tubes) {
   g->tubes = (Tube*)dalloc(g, sizeof(Tube) * n_tubes);
   g->tiles = (Tile*)dalloc(g, sizeof(Tile) * g->n_tiles);
   g->ltiles = (LTile*)dalloc(g, sizeof(LTile) * g->n_tiles);
-  if (!g->ltiles) return GAP_ENOMEM;
+  g->ptiles = (PTile*)dalloc(g, sizeof(PTile) * g->n_tiles);
+  if (!g->ltiles || !g->ptiles) return GAP_ENOMEM;
   g->rho = (long long*)dalloc(g, sizeof(long long) * g->total_nodes);
   g->rho_last = (long long*)dalloc(g, sizeof(long long) * g->total_nodes);
   g->E = (float*)dalloc(g, sizeof(float) * g->total_cells);
@@ -1534,7 +1563,8 @@ int build(gap_t* g, const gap_params* p, int n_tubes) {
   g->pq_groups = 8 * g->round_pho + 64;   // the autotuner tries grids up to 4 resident rounds
   g->pq = (uint4*)dalloc(g, (size_t)g->pho.capacity * sizeof(uint4));
   g->pq_count = (int*)dalloc(g, (size_t)g->pq_groups * 4);
-  if (!g->pq || !g->pq_count) return GAP_ENOMEM;
+  g->pq_start = (long long*)dalloc(g, (size_t)g->pq_groups * sizeof(long long));
+  if (!g->pq || !g->pq_count || !g->pq_start) return GAP_ENOMEM;
   // at most one entry per slot of the sorted lepton region; a count and a
   // start per workgroup of the largest lepton grid the launch settings allow
   // (4 rounds)
@@ -1620,6 +1650,7 @@ int build(gap_t* g, const gap_params* p, int n_tubes) {
   HIPCHK(hipStreamSynchronize(g->s));
   if ((e = upload_tubes(g))) return e;
   HIPCHK(hipMemcpy(g->tiles, g->tiles_h.data(), sizeof(Tile) * g->n_tiles, hipMemcpyHostToDevice));
+  HIPCHK(hipMemcpy(g->ptiles, g->ptiles_h.data(), sizeof(PTile) * g->n_tiles, hipMemcpyHostToDevice));
   HIPCHK(hipMemcpy(g->ltiles, g->ltiles_h.data(), sizeof(LTile) * g->n_tiles, hipMemcpyHostToDevice));
   HIPCHK(hipMemcpy(g->fb, g->fb_h.data(), sizeof(FBlk) * g->n_fb, hipMemcpyHostToDevice));
   const std::vector<float>& tab = sync_table();

@@ -111,6 +111,16 @@ struct LTile {
   int32_t zone, pad;
 };
 
+// The same for the sorted photon pass.  A non-periodic tube's photon whose new
+// position is below xlo or above xtop has left the QED zone or the box.
+struct PTile {
+  int32_t tube, base, N, dpho;
+  uint32_t flags, xlo, xtop;
+  float dt, inv_rc, b, conv_k, chi_skip;
+  int64_t hfix;
+  uint64_t seed;
+};
+
 // A pointer to memory that no kernel of the launch writes: uniform reads
 // through it are scalar loads.
 template <class T> using CPtr = const T __attribute__((address_space(4)))*;

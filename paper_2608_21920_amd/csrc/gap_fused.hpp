@@ -10,7 +10,7 @@
 // launches and three event calls.  Here the same work is two launches on one
 // stream:
 //   k_sorted   the prologue, both sorted passes
-//   k_rest     the queued photon births, the conversion draws, both tail
+//   k_rest     the queued photon births and conversions' pairs, both tail
 //              passes, the protons
 // and the field update is the third: the same steps take 35 us, one step of
 // the 1024-cell gap with a read of its field and charge 92 us instead of 137,
@@ -46,15 +46,15 @@ __global__ __launch_bounds__(TPB, 6) void k_sorted(Ctx cx, int n_tubes, int gp, 
 }
 
 // Workgroups of k_rest by role, in dispatch order.
-struct RestGrid { int births, conv, tails, protons, nseg, split; };
+struct RestGrid { int births, conv, tails, protons; };
 
-template <bool Q, bool A, int V>
+template <bool Q, bool A>
 __global__ __launch_bounds__(TPB) void k_rest(Ctx cx, RestGrid n) {
   int bx = (int)blockIdx.x;
   if (bx == 0 && threadIdx.x == 0 && cx.pc->cold_steps >= 0) cx.pc->cold_steps -= 1;
   if (bx < n.births) { births_queue<Q>(cx, bx, n.births); return; }
   bx -= n.births;
-  if (bx < n.conv) { conversions<Q, V>(cx, bx, n.nseg, n.split); return; }
+  if (bx < n.conv) { pairs_queue<Q>(cx, bx, n.conv); return; }
   bx -= n.conv;
   if (bx < n.tails) { both_tails<Q, A>(cx, bx, n.tails); return; }
   protons_pass(cx, bx - n.tails, n.protons);

@@ -11,6 +11,7 @@ struct Ctx {
   Tube* tubes;
   const Tile* tiles;
   const LTile* ltiles;
+  const PTile* ptiles;
   // lepton store (current buffers)
   LepBuf L;
   Ctl* lc;
@@ -35,12 +36,13 @@ struct Ctx {
   long long pr_cap;
   int* err;
   long long* shard;       // event counters [tube][NSHARD][C_N], summed by the host
-  // conversion queue of the sorted photon pass: workgroup b of the photon
-  // kernel writes its entries {slot, probability bits, tile, tube} from
-  // entry c0(b) * CHUNK on, c0(b) being the first chunk of its range, and
-  // their number to pq_count[b]
+  // conversions of the sorted photon pass: workgroup b of the pass (pq_groups
+  // of them) wrote pq_count[b] entries {slot, energy bits, Philox word of the
+  // pair split, tile} from entry pq_start[b] on
   uint4* pq;
   int* pq_count;
+  long long* pq_start;
+  int pq_groups;
   // photon births of the sorted lepton pass, queued for the tail launch:
   // entries {slot, post-kick u bits, event mask low word, high word};
   // workgroup b of the pass (bq_groups of them) wrote bq_count[b] entries
@@ -965,7 +967,7 @@ __device__ __forceinline__ void leptons_sorted(const Ctx& cx, int bx, int G) {
           float au = fabsf(upk);
           // (the key is kept from being known ahead of the loop: its twenty
           // round keys would be held in spilled scalar registers)
-          uint32_t k0 = (uint32_t)k.seed, k1 = (uint32_t)(k.seed >> 32);
+          uint32_t k0 = (uint32_t)rfl((int)k.seed), k1 = (uint32_t)rfl((int)(k.seed >> 32));
           for (int q = 0; q < nsub; ++q) {
             asm volatile("" : "+s"(k0), "+s"(k1));
             const u4 rr = philox<true>((uint32_t)id[j], (uint32_t)(id[j] >> 32), (uint32_t)k.step,
@@ -1129,7 +1131,8 @@ __device__ __forceinline__ float photon_chi(int64_t step, float dt, float inv_rc
   *sp_out = sp;
   return fabsf(x) * b * sp;
 }
-__device__ __forceinline__ float photon_prob(const KC& k, float x, int32_t n0) {
+template <class K>
+__device__ __forceinline__ float photon_prob(const K& k, float x, int32_t n0) {
   float sp;
   const float chi = photon_chi(k.step, k.dt, k.inv_rc, k.b, x, n0, &sp);
   const float p = one_minus_exp_neg(k.conv_k * sp * t_bw(chi));
@@ -1232,68 +1235,26 @@ __device__ void photon_one(const Ctx& cx, uint32_t slot, int tile, const KC& ku,
   }
 }
 
-template <int V> struct PhoV { Rec<float, V> x; Rec<uint32_t, V> pos; Rec<int32_t, V> n0; int tile; int hot; uint32_t slot0; };
+template <int V> struct PhoV { Rec<float, V> x; Rec<uint32_t, V> pos; Rec<int32_t, V> n0; };
 
 // The records of V consecutive slots of a sorted chunk for this thread (c
-// counts pieces of V TPB slots).  hot: the piece's leading slots that may
-// draw (all of them without the re-sort's guarantee); a piece with none does
-// not need the birth steps.
+// counts pieces of V TPB slots); a piece none of whose slots may draw (hot <=
+// 0) does not need the birth steps.
 template <int V>
-__device__ __forceinline__ PhoV<V> pho_load(const Ctx& cx, long long c, bool cold_ok) {
-  constexpr int U = V * TPB;
+__device__ __forceinline__ PhoV<V> pho_load(const Ctx& cx, long long c, int hot) {
   PhoV<V> r;
-  r.slot0 = (uint32_t)c * U + V * threadIdx.x;
-  const long long ch = V == VEC ? c : c / (VEC / V);
-  r.tile = cx.pchunk[ch];
-  r.hot = cold_ok ? (int)cx.pchot[ch] - (V == VEC ? 0 : (int)(c & (VEC / V - 1)) * U) : U;
-  r.x = rec_load<float, V>(cx.P.x + r.slot0);
-  r.pos = rec_load<uint32_t, V>(cx.P.pos + r.slot0);
-  if (r.hot > 0) r.n0 = rec_load<int32_t, V>(cx.P.n0 + r.slot0);
+  const uint32_t slot0 = (uint32_t)c * (V * TPB) + V * threadIdx.x;
+  r.x = rec_load<float, V>(cx.P.x + slot0);
+  r.pos = rec_load<uint32_t, V>(cx.P.pos + slot0);
+  if (hot > 0) r.n0 = rec_load<int32_t, V>(cx.P.n0 + slot0);
   else r.n0 = Rec<int32_t, V>{};
   return r;
 }
 
-// Sorted photon pass, first half for one photon: free streaming, exit, and
-// the conversion probability.  Gives the new position, the energy (0 once
-// the photon has left) and whether a conversion draw is due.
-__device__ __forceinline__ void photon_move(const Ctx& cx, const KC& k, float x, uint32_t pos, int32_t n0, bool may_draw,
-                                            LocalCounts& lcn, uint32_t* pos_out, float* x_out, float* p_out,
-                                            bool* eval_out) {
-  const bool alive = x != 0.0f;
-  const uint32_t flags = (uint32_t)k.flags;
-  const bool per = (flags & F_PERIODIC) != 0;
-  // new tile-local position; leaving the 256-cell window (a tile error) is
-  // the 32-bit add or subtract wrapping around
-  const uint32_t d = (uint32_t)k.dpho;
-  const uint32_t np = x >= 0.0f ? pos + d : pos - d;
-  const bool fwd = x >= 0.0f;
-  const bool oob = alive & ((fwd & (np < pos)) | (!fwd & (pos < d)));   // (no short-circuit: no branches)
-  if (__ballot(oob)) {
-    if (oob) atomicOr(cx.err, E_TILE);
-  }
-  bool out;
-  if (per) {
-    const int ncg = wrap_cell(k.base + (int)(np >> FRAC), k.N);
-    out = ((int64_t)ncg << FRAC) + (np & 0xFFFFFFu) >= k.hfix;
-  } else {
-    out = ((int64_t)np < k.xlo) | ((int64_t)np >= k.xhi);
-  }
-  const bool exited = alive & !oob & out;
-  const bool dead = oob | exited;
-  // the probability is taken for every lane of a wave in which one may draw
-  // (0 for an empty slot: chi = 0) and kept for the live ones; a slot that
-  // cannot draw would get p <= 2^-25 and no draw
-  const float pr = __ballot(may_draw) ? photon_prob(k, x, n0) : 0.0f;
-  const float p = (alive & !dead & !(flags & (F_QED_OFF | F_CONV_OFF))) ? pr : 0.0f;
-  const bool eval = p > 2.9802322e-8f;   // below 2^-25 no 24-bit uniform can fall under p
-  *pos_out = np;
-  *x_out = dead ? 0.0f : x;
-  *p_out = p;
-  *eval_out = eval;
-  lcn.v[0] += alive ? 1 : 0;
-  lcn.v[1] += eval ? 1 : 0;
-  lcn.v[4] += exited ? 1 : 0;
-}
+struct PK : PTile {
+  bool per, conv;
+  int64_t step;
+};
 
 // First chunk of the range of workgroup `bx` of a grid of G over nsc chunks
 // (XCD-aware: consecutive ranges go to workgroups of the same XCD).
@@ -1303,14 +1264,19 @@ __device__ __forceinline__ void chunk_range(long long nsc, int G, int bx, long l
   *c1 = nsc * (r + 1) / G;
 }
 
-// Photon pass over the sorted region, first kernel: free streaming, exits
-// and the conversion probability of every photon (a range of chunks per
-// workgroup, VEC slots per thread, the next chunk prefetched).  Only a tenth
-// or so of the photons must draw; they are queued, with their probability,
-// in the workgroup's own segment of the conversion queue (at most one entry
-// per slot of its range, so the segment cannot overflow), and the
-// conversion kernel works through the queue.  No barrier stands between
-// chunks.
+// Photon pass over the sorted region: free streaming, exits, the conversion
+// probability of every photon that may draw and its draw (a range of chunks
+// per workgroup, V slots per thread).  Converted photons are removed and
+// queued in the workgroup's own segment (at most one entry per slot of its
+// range, so the segment cannot overflow); the pair kernel works through the
+// queue.  No barrier stands between chunks.  The phases and the placing of
+// their loads are the lepton pass's (leptons_sorted): phase 1 moves all V
+// records and takes their probabilities, then the ids of those that draw and
+// the next piece's records are loaded, phase 2 draws.
+// Bound by HBM beside the lepton side: 1.27e7 photons of the production gap
+// take 48 us, and their pairs 9.5.  With the drawing photons queued for a
+// second kernel (16 B out and in and a gathered id each) the two took 57 and
+// 33.
 // FUSED: in one launch with the step's prologue, which may not have run yet:
 // the step index is the tubes' own, and the cold guarantee is not yet counted
 // down.
@@ -1318,219 +1284,267 @@ template <int V, bool FUSED>
 __device__ __forceinline__ void photons_sorted(const Ctx& cx, int bx, int G) {
   constexpr int U = V * TPB;
   long long c0, c1;
-  chunk_range(cx.pc->n_sorted_chunks * (CHUNK / U), G, bx, &c0, &c1);
+  chunk_range(rfl64(cx.pc->n_sorted_chunks) * (CHUNK / U), G, bx, &c0, &c1);
   __shared__ long long s_cnt[8];
   __shared__ int q_n;
   if (c0 >= c1) {              // no chunk for this workgroup
-    if (threadIdx.x == 0) cx.pq_count[bx] = 0;
+    if (threadIdx.x == 0) {
+      cx.pq_count[bx] = 0;
+      cx.pq_start[bx] = 0;
+    }
     return;
   }
+  const bool cold_ok = rfl64(cx.pc->cold_steps) >= (FUSED ? 1 : 0);
+  auto tile_of = [&](long long c) { return cptr(cx.pchunk)[V == VEC ? c : c / (VEC / V)]; };
+  // the piece's leading slots that may draw (all without the guarantee)
+  auto hot_of = [&](long long c) {
+    if (!cold_ok) return U;
+    return (int)cx.pchot[V == VEC ? c : c / (VEC / V)] - (V == VEC ? 0 : (int)(c & (VEC / V - 1)) * U);
+  };
   if (threadIdx.x == 0) q_n = 0;
   __syncthreads();
   uint4* const q = cx.pq + c0 * U;
   LocalCounts lcn;
   lcn.clear();
-  int ctube = -1;
-  KC kc;
-  int held = -1;
-  const bool cold_ok = cx.pc->cold_steps >= (FUSED ? 1 : 0);
-  PhoV<V> cur = pho_load<V>(cx, c0, cold_ok);
+  int n_alive = 0, n_eval = 0;   // of the wave (uniform)
+  int hot = rfl(hot_of(c0)), held = -1;
+  PhoV<V> cur = pho_load<V>(cx, c0, hot);
+  PK k;
+  k.tube = -1;
   for (long long c = c0; c < c1; ++c) {
-    PhoV<V> nxt;
-    if (c + 1 < c1) nxt = pho_load<V>(cx, c + 1, cold_ok);
-    if (cur.tile != held) {
-      held = cur.tile;
-      kc = load_kc(cx, held, !FUSED);
-      if (kc.tube != ctube) {
-        if (ctube >= 0) flush_counts<1>(cx.shard, ctube, lcn, s_cnt);
-        ctube = kc.tube;
+    const int tile = tile_of(c);
+    if (tile != held) {
+      held = tile;
+      const int tube = k.tube;
+      struct Words { uint32_t w[sizeof(PTile) / 4]; } raw;
+      const CPtr<uint32_t> src = (CPtr<uint32_t>)(cx.ptiles + tile);
+#pragma unroll
+      for (int i = 0; i < (int)(sizeof(PTile) / 4); ++i) raw.w[i] = src[i];
+      static_cast<PTile&>(k) = __builtin_bit_cast(PTile, raw);
+      k.per = (k.flags & F_PERIODIC) != 0;
+      k.conv = !(k.flags & (F_QED_OFF | F_CONV_OFF));
+      k.step = FUSED ? cptr(cx.tubes)[k.tube].step : cptr(cx.tubes)[k.tube].step_now;
+      if (tube >= 0 && tube != k.tube) {
+        lcn.v[0] = lane_id() == 0 ? n_alive : 0;
+        lcn.v[1] = lane_id() == 0 ? n_eval : 0;
+        n_alive = n_eval = 0;
+        flush_counts<1>(cx.shard, tube, lcn, s_cnt);
       }
     }
-    Rec<float, V> x = cur.x;
+    const uint32_t slot0 = (uint32_t)c * U + V * threadIdx.x;
+    float x[V];
+    uint32_t p[V];
+    int32_t n0[V];
+    rec_get(cur.x, x);
+    rec_get(cur.pos, p);
+    rec_get(cur.n0, n0);
+
+    // ---- phase 1: leaving the 256-cell window (a tile error) is the 32-bit
+    // add or subtract wrapping around
+    const uint32_t d = (uint32_t)k.dpho;
     bool xchg = false;
-    Rec<uint32_t, V> p = cur.pos;
-    Rec<int32_t, V> n0 = cur.n0;
-#pragma unroll 1
+    uint32_t thr[V];
+    uint32_t ev = 0;
+#pragma unroll
     for (int j = 0; j < V; ++j) {
-      uint32_t po;
-      float xo, pr;
-      bool ev;
-      photon_move(cx, kc, rec_first(x), rec_first(p), rec_first(n0), (int)(V * threadIdx.x) + j < cur.hot, lcn, &po, &xo,
-                  &pr, &ev);
-      xchg |= xo != rec_first(x);
-      const uint64_t m = __ballot(ev);
-      if (m) {
-        int base = 0;
-        if (lane_id() == 0) base = atomicAdd(&q_n, (int)__popcll(m));
-        base = __shfl(base, 0);
-        if (ev) q[base + rank_in(m)] = make_uint4(cur.slot0 + j, __float_as_uint(pr), (uint32_t)held, (uint32_t)kc.tube);
+      const bool alive = x[j] != 0.0f, fwd = x[j] >= 0.0f;
+      const uint32_t np = fwd ? p[j] + d : p[j] - d;
+      const bool oob = alive & ((fwd & (np < p[j])) | (!fwd & (p[j] < d)));
+      bool out;
+      if (k.per) {
+        const int ncg = wrap_cell(k.base + (int)(np >> FRAC), k.N);
+        out = ((int64_t)ncg << FRAC) + (np & 0xFFFFFFu) >= k.hfix;
+      } else {
+        out = (np < k.xlo) | (np > k.xtop);
       }
-      rec_rotate(x, xo);
-      rec_rotate(p, po);
-      rec_rotate(n0, rec_first(n0));
+      n_alive += (int)__popcll(__ballot(alive));
+      // the probability is taken for every lane of a wave in which one may
+      // draw; below 2^-25 no 24-bit uniform can fall under it
+      thr[j] = 0;
+      if (k.conv && hot > 0) {
+        const bool may = (int)(V * threadIdx.x) + j < hot;
+        if (__ballot(may)) {
+          const float pr = photon_prob(k, x[j], n0[j]);
+          const bool e = alive & !oob & !out & (pr > 2.9802322e-8f);
+          thr[j] = bern_thr(pr);
+          ev |= e ? 1u << j : 0u;
+          n_eval += (int)__popcll(__ballot(e));
+        }
+      }
+      if (__ballot(alive & (oob | out))) {
+        if (oob) atomicOr(cx.err, E_TILE);
+        if (alive & (oob | out)) {
+          if (!oob) ++lcn.v[4];
+          x[j] = 0.0f;
+          xchg = true;
+        }
+      }
+      p[j] = np;
     }
-    rec_store<uint32_t, V>(cx.P.pos + cur.slot0, p);
-    if (xchg) rec_store<float, V>(cx.P.x + cur.slot0, x);   // only when a photon left
+    uint64_t id[V];
+    if (ev != 0) {
+      if constexpr (V == 4) {
+        const ulonglong2 a = *reinterpret_cast<const ulonglong2*>(cx.P.id + slot0);
+        const ulonglong2 b = *reinterpret_cast<const ulonglong2*>(cx.P.id + slot0 + 2);
+        id[0] = a.x; id[1] = a.y; id[2] = b.x; id[3] = b.y;
+      } else {
+        id[0] = cx.P.id[slot0];
+      }
+    }
+    // (the last piece loads itself again, see leptons_sorted)
+    const long long cn = c + 1 < c1 ? c + 1 : c;
+    hot = rfl(hot_of(cn));
+    const PhoV<V> nxt = pho_load<V>(cx, cn, hot);
+
+    // ---- phase 2
+    if (__ballot(ev != 0)) {
+#pragma unroll
+      for (int j = 0; j < V; ++j) {
+        const bool e = (ev >> j) & 1u;
+        bool conv = false;
+        uint32_t split = 0;
+        if (__ballot(e)) {
+          if (e) {
+            // (the key as in leptons_sorted)
+            uint32_t k0 = (uint32_t)rfl((int)k.seed), k1 = (uint32_t)rfl((int)(k.seed >> 32));
+            asm volatile("" : "+s"(k0), "+s"(k1));
+            const u4 r = philox<true>((uint32_t)id[j], (uint32_t)(id[j] >> 32), (uint32_t)k.step, T_CONV << 16, k0, k1);
+            conv = bern_t(r.a, thr[j]);
+            split = r.b;
+          }
+          const uint64_t m = __ballot(conv);
+          if (m) {
+            int base = 0;
+            if (lane_id() == 0) base = atomicAdd(&q_n, (int)__popcll(m));
+            base = __builtin_amdgcn_readfirstlane(base);
+            if (conv) {
+              q[base + rank_in(m)] = make_uint4(slot0 + j, __float_as_uint(x[j]), split, (uint32_t)held);
+              x[j] = 0.0f;
+              xchg = true;
+            }
+          }
+        }
+      }
+    }
+    rec_put(cur.pos, p);
+    rec_store<uint32_t, V>(cx.P.pos + slot0, cur.pos);
+    if (xchg) {                               // only when a photon left or converted
+      rec_put(cur.x, x);
+      rec_store<float, V>(cx.P.x + slot0, cur.x);
+    }
     cur = nxt;
   }
-  flush_counts<1>(cx.shard, ctube, lcn, s_cnt);
-  __syncthreads();
-  if (threadIdx.x == 0) cx.pq_count[bx] = q_n;
+  lcn.v[0] = lane_id() == 0 ? n_alive : 0;
+  lcn.v[1] = lane_id() == 0 ? n_eval : 0;
+  flush_counts<1>(cx.shard, k.tube, lcn, s_cnt);
+  // (flush_counts ends with a barrier: every wave has queued its conversions)
+  if (threadIdx.x == 0) {
+    cx.pq_count[bx] = q_n;
+    cx.pq_start[bx] = c0 * U;
+  }
 }
 
 __global__ __launch_bounds__(TPB) void k_photons(Ctx cx) { photons_sorted<VEC, false>(cx, blockIdx.x, gridDim.x); }
 
-// Photon pass, second kernel: the conversion draws of the queued photons and
-// the pairs they create: e- and e+ at the photon's new position, gamma = x/2
-// each, moving along the photon; the converted photon is removed.
-// The queue segment that workgroup k of the photon kernel (a grid of nseg)
-// wrote is cut into `split` parts by rounds of TPB entries (part p takes
-// rounds p, p + split, ...), so that the number of parts can fill the chip
-// whatever the photon grid; workgroup b takes parts CONV_SEGS b .. CONV_SEGS
-// b + CONV_SEGS - 1, one entry of each per thread and round, with all loads
-// issued before the draws.  (With the segment as the unit, a photon grid of
-// 768 left 384 workgroups to walk 4e7 entries, 1.7 ms per step.)
-constexpr int CONV_SEGS = 2;
-//
-// The pairs take lepton tail slots from a block per wave (LDS state, one
-// entry per wave): a new block is reserved with one atomic on the lepton
-// tail counter only when the block cannot hold the iteration's pairs, which
-// then fill the old block and continue in the new one.  The first block
-// holds exactly the wave's first pairs; each later one is at least twice the
-// last, up to PAIR_BLOCK_MAX.  The unused end of a wave's last block is
-// written as dead leptons (weight 0, tile 0), which every pass skips and the
-// re-sort drops.  (One atomic per wave and conversion iteration, on the one
-// counter every reservation updates, cost a cascade of 1e5 conversions per
-// step about a millisecond.)
-constexpr int PAIR_BLOCK_MAX = 128;
-
-// V: the photon pass's slots per thread and piece (its ranges are in pieces
-// of V TPB slots).
-template <bool Q, int V>
-__device__ __forceinline__ void conversions(const Ctx& cx, int bx, int nseg, int split) {
-  constexpr int U = V * TPB;
-  const Room lroom = load_room(cx.lc);
-  const long long nsc = cx.pc->n_sorted_chunks * (CHUNK / U);
-  __shared__ long long s_blk[TPB / WAVE][3];    // per wave: next slot, block end, next block size
-  long long* blk = s_blk[threadIdx.x / WAVE];
-  if (lane_id() == 0) { blk[0] = 0; blk[1] = 0; blk[2] = 2; }
-  long long q0[CONV_SEGS];
-  int n[CONV_SEGS];
-  int nmax = 0;
-#pragma unroll
-  for (int j = 0; j < CONV_SEGS; ++j) {
-    const int v = bx * CONV_SEGS + j;
-    const int sg = v / split;
-    long long c0 = 0, c1 = 0;
-    n[j] = 0;
-    if (sg < nseg) {
-      chunk_range(nsc, nseg, sg, &c0, &c1);
-      n[j] = __builtin_amdgcn_readfirstlane(cx.pq_count[sg]);
-    }
-    // rounds part, part + split, ... of the segment
-    const int part = v - sg * split;
-    q0[j] = c0 * U + (long long)part * TPB;
-    n[j] -= part * TPB;
-    nmax = max(nmax, n[j]);
-  }
-  const int stride = split * TPB;
-  for (int i0 = 0; i0 < nmax; i0 += stride) {
+// The entries of the queue segments b0, b0 + nb, ... of ns that one workgroup
+// works through, TPB segments at a time: their counts are read together and
+// scanned in LDS, and the entries of all of them are taken in dense pieces of
+// TPB (a lane finds its segment by a binary search over the scan), so that a
+// workgroup with few entries in many segments pays one chain of dependent
+// loads, not one per segment.  each(valid, index of the entry in the queue) is
+// called by every lane.
+template <class Each>
+__device__ __forceinline__ void queue_entries(const int* count, const long long* start, int ns, int b0, int nb, Each each) {
+  __shared__ int s_pre[TPB + 1];
+  __shared__ long long s_st[TPB];
+  __shared__ int s_wsum[TPB / WAVE];
+  const int mine = b0 < ns ? (ns - b0 + nb - 1) / nb : 0;
+  for (int i0 = 0; i0 < mine; i0 += TPB) {
     const int i = i0 + (int)threadIdx.x;
-    uint4 e[CONV_SEGS];
-    uint64_t id[CONV_SEGS], seed[CONV_SEGS];
-    int64_t step[CONV_SEGS];
-    bool act[CONV_SEGS];
-#pragma unroll
-    for (int j = 0; j < CONV_SEGS; ++j) {
-      act[j] = i < n[j];
-      e[j] = act[j] ? cx.pq[q0[j] + i] : make_uint4(0, 0, 0, 0);
+    const int sg = b0 + i * nb;
+    const int c = i < mine ? count[sg] : 0;
+    s_st[threadIdx.x] = i < mine ? start[sg] : 0;
+    int wt;
+    const int ex = wave_excl_scan(c, &wt);
+    if (lane_id() == 0) s_wsum[threadIdx.x / WAVE] = wt;
+    __syncthreads();
+    int before = 0, total = 0;
+    for (int w = 0; w < TPB / WAVE; ++w) {
+      if (w < (int)threadIdx.x / WAVE) before += s_wsum[w];
+      total += s_wsum[w];
     }
-#pragma unroll
-    for (int j = 0; j < CONV_SEGS; ++j) {
-      id[j] = act[j] ? cx.P.id[e[j].x] : 0;
-      seed[j] = act[j] ? cx.tubes[e[j].w].seed : 0;
-      step[j] = act[j] ? cx.tubes[e[j].w].step_now : 0;
-    }
-#pragma unroll
-    for (int j = 0; j < CONV_SEGS; ++j) {
-      bool conv = false;
-      uint32_t rsplit = 0;
-      if (act[j]) {
-        const u4 r = draw<true>(seed[j], id[j], step[j], T_CONV, 0);
-        conv = bern(r.a, __uint_as_float(e[j].y));
-        rsplit = r.b;
+    s_pre[threadIdx.x] = before + ex;
+    if (threadIdx.x == 0) s_pre[TPB] = total;
+    __syncthreads();
+    for (int p = 0; p < total; p += TPB) {
+      const int e = p + (int)threadIdx.x;
+      // last segment whose first entry is at or before e (empty ones repeat
+      // their successor's start, so the search lands on a segment that has e)
+      int lo = 0, hi = TPB;
+      while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (s_pre[mid] <= e) lo = mid; else hi = mid;
       }
-      const uint64_t cm = __ballot(conv);
-      if (cm) {
-        const uint32_t slot = e[j].x;
-        const int tube = conv ? (int)e[j].w : -1;
-        // this lane's pair takes the wave's pair slots ex and ex + 1
-        const long long total = 2 * __popcll(cm);
-        const long long ex = 2 * rank_in(cm);
-        const long long next = rfl64(blk[0]);
-        const long long rem = rfl64(blk[1]) - next;
-        long long nb = 0;
-        if (total > rem) {
-          const long long need = total - rem;
-          const long long req = max(need, rfl64(blk[2]));
-          long long base = 0;
-          if (lane_id() == WAVE - 1) {
-            base = (long long)atomicAdd((unsigned long long*)&cx.lc->tail, (unsigned long long)req);
-            const long long room = lroom.L > lroom.S ? lroom.L - lroom.S : 0;
-            if (base + req > room) atomicMin((unsigned long long*)&cx.lc->tail, (unsigned long long)room);
-          }
-          nb = lroom.S + rfl64(__shfl(base, WAVE - 1));
-          if (lane_id() == 0) { blk[0] = nb + need; blk[1] = nb + req; blk[2] = min(2 * req, (long long)PAIR_BLOCK_MAX); }
-        } else if (lane_id() == 0) {
-          blk[0] = next + total;
-        }
-        int dropped = 0;
-        if (conv) {
-          const float x = cx.P.x[slot], w = cx.P.w[slot];
-          const uint32_t np = cx.P.pos[slot];
-          const Tube& T = cx.tubes[e[j].w];
-          const uint32_t tflags = (uint32_t)T.flags;
-          float chi = 0.0f, sp;
-          if (Q && (tflags & F_QUANTUM)) chi = photon_chi(step[j], T.dt, T.inv_rc, T.b, x, cx.P.n0[slot], &sp);
-          float ue, upo;
-          pair_momenta<Q>(cx, tflags, rsplit, chi, x, &ue, &upo);
-          for (int b = 0; b < 2; ++b) {
-            const long long g = ex + b;
-            const long long sl = g < rem ? next + g : nb + (g - rem);
-            if (sl >= lroom.L) {
-              ++dropped;
-            } else {
-              const uint32_t s32 = (uint32_t)sl;
-              cx.L.pos[s32] = np;
-              cx.L.u[s32] = b == 0 ? ue : upo;
-              cx.L.w[s32] = b == 0 ? -w : w;
-              cx.L.id[s32] = child_id(seed[j], id[j], step[j], (uint32_t)b);
-              cx.ltt[s32] = (int32_t)e[j].z;
-            }
-          }
-          cx.P.x[slot] = 0.0f;
-        }
-        if (dropped) atomicOr(cx.err, E_CAP);
-        count_by_tube(cx.shard, tube, C_CONV, 1);
-        if (__ballot(dropped != 0)) count_by_tube(cx.shard, dropped ? tube : -1, C_DROPPED, dropped);
-      }
+      each(e < total, s_st[lo] + (e - s_pre[lo]));
     }
-  }
-  // the unused end of the wave's last block: dead leptons
-  const long long bend = min(rfl64(blk[1]), lroom.L);
-  for (long long sl = rfl64(blk[0]) + lane_id(); sl < bend; sl += WAVE) {
-    const uint32_t s32 = (uint32_t)sl;
-    cx.L.pos[s32] = 0;
-    cx.L.u[s32] = 0.0f;
-    cx.L.w[s32] = 0.0f;
-    cx.L.id[s32] = 0;
-    cx.ltt[s32] = 0;
+    __syncthreads();                  // (s_pre and s_st are rewritten by the next batch)
   }
 }
 
+// The pairs of the photons that the sorted pass converted: e- and e+ at the
+// photon's new position, gamma = x/2 each, moving along the photon.  A lane
+// takes one entry of the queue and the wave reserves lepton tail slots once
+// for all its lanes (one atomic per wave with few conversions each, on the
+// one counter every reservation updates, cost a cascade of 1e5 conversions
+// per step about a millisecond).
 template <bool Q>
-__global__ __launch_bounds__(TPB) void k_conversions(Ctx cx, int nseg, int split) {
-  conversions<Q, VEC>(cx, (int)blockIdx.x, nseg, split);
+__device__ __forceinline__ void pairs_queue(const Ctx& cx, int b0, int nb) {
+  const Room lroom = load_room(cx.lc);
+  queue_entries(cx.pq_count, cx.pq_start, cx.pq_groups, b0, nb, [&](bool valid, long long at) {
+    const uint4 q = valid ? cx.pq[at] : make_uint4(0u, 0u, 0u, 0u);
+    const uint32_t slot = q.x;
+    const float x = __uint_as_float(q.y);
+    const Tile tl = cx.tiles[q.w];
+    const Tube& T = cx.tubes[tl.tube];
+    const uint64_t seed = T.seed;
+    const int64_t step = T.step_now;
+    const uint32_t tflags = (uint32_t)T.flags;
+    uint64_t id = 0;
+    float w = 0.0f;
+    uint32_t np = 0;
+    if (valid) {
+      id = cx.P.id[slot];
+      w = cx.P.w[slot];
+      np = cx.P.pos[slot];
+    }
+    int dropped = 0;
+    const long long first = reserve_tail(cx.lc, lroom, valid ? 2 : 0, &dropped);
+    if (valid) {
+      float chi = 0.0f, sp;
+      if (Q && (tflags & F_QUANTUM)) chi = photon_chi(step, T.dt, T.inv_rc, T.b, x, cx.P.n0[slot], &sp);
+      float ue, upo;
+      pair_momenta<Q>(cx, tflags, q.z, chi, x, &ue, &upo);
+      for (int e = 0; e < 2; ++e) {
+        const long long sl = first + e;
+        if (sl < lroom.L) {
+          const uint32_t s32 = (uint32_t)sl;
+          cx.L.pos[s32] = np;
+          cx.L.u[s32] = e == 0 ? ue : upo;
+          cx.L.w[s32] = e == 0 ? -w : w;
+          cx.L.id[s32] = child_id(seed, id, step, (uint32_t)e);
+          cx.ltt[s32] = (int32_t)q.w;
+        }
+      }
+    }
+    if (dropped) atomicOr(cx.err, E_CAP);
+    count_by_tube(cx.shard, valid ? tl.tube : -1, C_CONV, 1);
+    if (__ballot(dropped != 0)) count_by_tube(cx.shard, dropped ? tl.tube : -1, C_DROPPED, dropped);
+  });
+}
+
+template <bool Q>
+__global__ __launch_bounds__(TPB) void k_conversions(Ctx cx) {
+  pairs_queue<Q>(cx, (int)blockIdx.x, (int)gridDim.x);
 }
 
 template <bool Q>
@@ -1561,111 +1575,74 @@ __device__ __forceinline__ void photons_tail(const Ctx& cx, int bid, int nblk) {
 // once for all its lanes.  The lepton's position after its drift, weight and
 // id are read from its slot (the pass has stored them); the step index is
 // still the pass's, since the field update runs after this launch.
-// Workgroup b0 takes the segments b0, b0 + nb, ..., TPB segments at a time:
-// their counts are read together and scanned in LDS, and the entries of all
-// of them are taken in dense pieces of TPB (a lane finds its segment by a
-// binary search over the scan), so that a workgroup with few entries in many
-// segments pays one chain of dependent loads, not one per segment.
 template <bool Q>
 __device__ __forceinline__ void births_queue(const Ctx& cx, int b0, int nb) {
-  __shared__ int s_pre[TPB + 1];
-  __shared__ long long s_st[TPB];
-  __shared__ int s_wsum[TPB / WAVE];
   const Room proom = load_room(cx.pc);
   const long long lim = proom.L;
-  const int ns = b0 < cx.bq_groups ? (cx.bq_groups - b0 + nb - 1) / nb : 0;
-  for (int i0 = 0; i0 < ns; i0 += TPB) {
-    const int i = i0 + (int)threadIdx.x;
-    const int sg = b0 + i * nb;
-    const int c = i < ns ? cx.bq_count[sg] : 0;
-    s_st[threadIdx.x] = i < ns ? cx.bq_start[sg] : 0;
-    int wt;
-    const int ex = wave_excl_scan(c, &wt);
-    if (lane_id() == 0) s_wsum[threadIdx.x / WAVE] = wt;
-    __syncthreads();
-    int before = 0, total = 0;
-    for (int w = 0; w < TPB / WAVE; ++w) {
-      if (w < (int)threadIdx.x / WAVE) before += s_wsum[w];
-      total += s_wsum[w];
+  queue_entries(cx.bq_count, cx.bq_start, cx.bq_groups, b0, nb, [&](bool valid, long long at) {
+    const uint4 q = valid ? cx.bq[at] : make_uint4(0u, 0u, 0u, 0u);
+    const uint32_t slot = q.x;
+    const int tile = valid ? cx.lchunk[slot / CHUNK] : 0;
+    const KC k = lane_kc(cx, tile, false);
+    const uint32_t flags = (uint32_t)k.flags;
+    const float upk = __uint_as_float(q.y);
+    const uint64_t evmask = (uint64_t)q.z | ((uint64_t)q.w << 32);
+    uint64_t id = 0;
+    float aw = 0.0f;
+    uint32_t npl = 0;
+    if (valid) {
+      id = cx.L.id[slot];
+      aw = fabsf(cx.L.w[slot]);
+      npl = cx.L.pos[slot];
     }
-    s_pre[threadIdx.x] = before + ex;
-    if (threadIdx.x == 0) s_pre[TPB] = total;
-    __syncthreads();
-    for (int p = 0; p < total; p += TPB) {
-      const int e = p + (int)threadIdx.x;
-      const bool valid = e < total;
-      // last segment whose first entry is at or before e (empty ones repeat
-      // their successor's start, so the search lands on a segment that has e)
-      int lo = 0, hi = TPB;
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (s_pre[mid] <= e) lo = mid; else hi = mid;
+    float g, chi;
+    const float xc = emit_xc(upk, k.lr, &g, &chi);
+    int nst = 0;
+    {
+      float au = fabsf(upk);
+      uint64_t m = evmask;
+      while (m) {
+        const int j = __ffsll((long long)m) - 1;
+        m &= m - 1;
+        const u4 r = draw(k.seed, id, k.step, T_EMIT, (uint32_t)j);
+        const float x = fminf(photon_energy<Q>(cx, flags, r.b, xc, upk, k.lr), au);
+        au -= x;
+        if (x >= k.x_thr || (flags & F_TRACK_ALL)) ++nst;
       }
-      const uint4 q = valid ? cx.bq[s_st[lo] + (e - s_pre[lo])] : make_uint4(0u, 0u, 0u, 0u);
-      const uint32_t slot = q.x;
-      const int tile = valid ? cx.lchunk[slot / CHUNK] : 0;
-      const KC k = lane_kc(cx, tile, false);
-      const uint32_t flags = (uint32_t)k.flags;
-      const float upk = __uint_as_float(q.y);
-      const uint64_t evmask = (uint64_t)q.z | ((uint64_t)q.w << 32);
-      uint64_t id = 0;
-      float aw = 0.0f;
-      uint32_t npl = 0;
-      if (valid) {
-        id = cx.L.id[slot];
-        aw = fabsf(cx.L.w[slot]);
-        npl = cx.L.pos[slot];
-      }
-      float g, chi;
-      const float xc = emit_xc(upk, k.lr, &g, &chi);
-      int nst = 0;
-      {
-        float au = fabsf(upk);
-        uint64_t m = evmask;
-        while (m) {
-          const int j = __ffsll((long long)m) - 1;
-          m &= m - 1;
-          const u4 r = draw(k.seed, id, k.step, T_EMIT, (uint32_t)j);
-          const float x = fminf(photon_energy<Q>(cx, flags, r.b, xc, upk, k.lr), au);
-          au -= x;
-          if (x >= k.x_thr || (flags & F_TRACK_ALL)) ++nst;
-        }
-      }
-      int dropped = 0;
-      const long long first = reserve_tail(cx.pc, proom, nst, &dropped);
-      if (nst > 0) {
-        float au = fabsf(upk);
-        const float dir = upk >= 0.0f ? 1.0f : -1.0f;
-        long long qq = first;
-        uint64_t m = evmask;
-        while (m) {
-          const int j = __ffsll((long long)m) - 1;
-          m &= m - 1;
-          const u4 r = draw(k.seed, id, k.step, T_EMIT, (uint32_t)j);
-          const float x = fminf(photon_energy<Q>(cx, flags, r.b, xc, upk, k.lr), au);
-          au -= x;
-          if (x >= k.x_thr || (flags & F_TRACK_ALL)) {
-            if (qq < lim) {
-              const uint32_t kk = (uint32_t)qq;
-              cx.P.pos[kk] = npl;
-              cx.P.x[kk] = dir * x;
-              cx.P.w[kk] = aw;
-              cx.P.n0[kk] = (int32_t)(k.step + 1);
-              cx.P.id[kk] = child_id(k.seed, id, k.step, 2u + (uint32_t)j);
-              cx.ptt[kk] = tile;
-            }
-            ++qq;
+    }
+    int dropped = 0;
+    const long long first = reserve_tail(cx.pc, proom, nst, &dropped);
+    if (nst > 0) {
+      float au = fabsf(upk);
+      const float dir = upk >= 0.0f ? 1.0f : -1.0f;
+      long long qq = first;
+      uint64_t m = evmask;
+      while (m) {
+        const int j = __ffsll((long long)m) - 1;
+        m &= m - 1;
+        const u4 r = draw(k.seed, id, k.step, T_EMIT, (uint32_t)j);
+        const float x = fminf(photon_energy<Q>(cx, flags, r.b, xc, upk, k.lr), au);
+        au -= x;
+        if (x >= k.x_thr || (flags & F_TRACK_ALL)) {
+          if (qq < lim) {
+            const uint32_t kk = (uint32_t)qq;
+            cx.P.pos[kk] = npl;
+            cx.P.x[kk] = dir * x;
+            cx.P.w[kk] = aw;
+            cx.P.n0[kk] = (int32_t)(k.step + 1);
+            cx.P.id[kk] = child_id(k.seed, id, k.step, 2u + (uint32_t)j);
+            cx.ptt[kk] = tile;
           }
+          ++qq;
         }
       }
-      if (__ballot(dropped != 0)) {
-        if (dropped) atomicOr(cx.err, E_CAP);
-        count_by_tube(cx.shard, dropped ? k.tube : -1, C_DROPPED, dropped);
-      }
-      if (__ballot(nst - dropped != 0)) count_by_tube(cx.shard, nst - dropped != 0 ? k.tube : -1, C_PHO_BORN, nst - dropped);
     }
-    __syncthreads();                  // (s_pre and s_st are rewritten by the next batch)
-  }
+    if (__ballot(dropped != 0)) {
+      if (dropped) atomicOr(cx.err, E_CAP);
+      count_by_tube(cx.shard, dropped ? k.tube : -1, C_DROPPED, dropped);
+    }
+    if (__ballot(nst - dropped != 0)) count_by_tube(cx.shard, nst - dropped != 0 ? k.tube : -1, C_PHO_BORN, nst - dropped);
+  });
 }
 
 // Both tail passes in one launch.  They touch disjoint data: each reads its
