@@ -2114,12 +2114,6 @@ template <class B> __device__ __forceinline__ bool rec_alive(const B& b, long lo
 template <> __device__ __forceinline__ bool rec_alive<LepBuf>(const LepBuf& b, long long i) { return b.w[i] != 0.0f; }
 template <> __device__ __forceinline__ bool rec_alive<PhoBuf>(const PhoBuf& b, long long i) { return b.x[i] != 0.0f; }
 
-__device__ __forceinline__ void rec_copy(const LepBuf& s, long long i, const LepBuf& d, long long j, uint32_t pos) {
-  d.pos[j] = pos; d.u[j] = s.u[i]; d.w[j] = s.w[i]; d.id[j] = s.id[i];
-}
-__device__ __forceinline__ void rec_copy(const PhoBuf& s, long long i, const PhoBuf& d, long long j, uint32_t pos) {
-  d.pos[j] = pos; d.x[j] = s.x[i]; d.w[j] = s.w[i]; d.n0[j] = s.n0[i]; d.id[j] = s.id[i];
-}
 __device__ __forceinline__ void rec_kill(const LepBuf& d, long long j) { d.w[j] = 0.0f; }
 __device__ __forceinline__ void rec_kill(const PhoBuf& d, long long j) { d.x[j] = 0.0f; }
 
@@ -2145,7 +2139,7 @@ struct RbCtx {
   int window;            // steps until the next re-sort
   long long* chunks_seen;  // the new layout's chunk count + 1, for the host
   long long* tchunk;     // first chunk of each tile in the new layout (n_tiles + 1)
-  int32_t* wh;           // [grid][RB_HW][N]: each count workgroup's window counts by tile and class
+  int32_t* wh;           // [grid][window][N]: each count workgroup's window counts by tile and class
   int n_tiles;
 };
 
@@ -2166,16 +2160,35 @@ template <> struct RbClasses<LepBuf> { static constexpr int N = 4; };
 
 // The loads of one slot of a re-sort row, issued before any use, so that a
 // group of rows keeps its loads in flight together.  a: the field that marks
-// a live record (photon x, lepton w); b: lepton u; n0: photon birth step;
-// cls: the class the count kernel decided (scatter).
-struct RbIn { long long slot; int tile; uint32_t pos; float a, b; uint32_t n0; int cls; };
+// a live record (photon x, lepton w); b: lepton u (scatter: photon w); n0:
+// photon birth step; cls: the class the count kernel decided and id (scatter).
+struct RbIn { long long slot; int tile; uint32_t pos; float a, b; uint32_t n0; int cls; uint64_t id; };
+
+__device__ __forceinline__ void rec_place(const LepBuf& d, long long j, uint32_t pos, const RbIn& r) {
+  d.pos[j] = pos; d.u[j] = r.b; d.w[j] = r.a; d.id[j] = r.id;
+}
+__device__ __forceinline__ void rec_place(const PhoBuf& d, long long j, uint32_t pos, const RbIn& r) {
+  d.pos[j] = pos; d.x[j] = r.a; d.w[j] = r.b; d.n0[j] = (int32_t)r.n0; d.id[j] = r.id;
+}
+
+// sin(a) for |a| < 1.5 (relative truncation a^8/362880 < 2e-8 up to 0.55;
+// sinf beyond, in waves that hold one).
+__device__ __forceinline__ float sin_mid(float a) {
+  const float a2 = a * a;
+  float s = a * (1.0f - a2 * (1.0f / 6.0f) * (1.0f - a2 * (1.0f / 20.0f) * (1.0f - a2 * (1.0f / 42.0f))));
+  const bool big = !(fabsf(a) < 0.55f);
+  if (__ballot(big)) {
+    if (big) s = sinf(a);
+  }
+  return s;
+}
 
 __device__ __forceinline__ bool rb_hot(const RbCtx<PhoBuf>& cx, const Tube& T, float x, uint32_t n0) {
   const int32_t a1 = (int32_t)((uint32_t)T.step + 1u - n0);
   const int32_t a2 = (int32_t)((uint32_t)T.step + (uint32_t)cx.window - n0);
   if (a2 < a1) return true;                 // the 32-bit age wraps inside the window
   const float s1 = (float)a1 * T.dt * T.inv_rc, s2 = (float)a2 * T.dt * T.inv_rc;
-  const float sp = fmaxf(fabsf(s1), fabsf(s2)) < 1.5f ? fmaxf(fabsf(sinf(s1)), fabsf(sinf(s2))) : 1.0f;
+  const float sp = fmaxf(fabsf(s1), fabsf(s2)) < 1.5f ? fmaxf(fabsf(sin_mid(s1)), fabsf(sin_mid(s2))) : 1.0f;
   const float chi = fabsf(x) * T.b * sp;
   return T.conv_k * sp * t_bw(chi) > 7.4505806e-9f;   // 2^-27
 }
@@ -2233,6 +2246,7 @@ __device__ __forceinline__ void rb_load(const RbCtx<B>& cx, bool have, long long
   r.b = 0.0f;
   r.n0 = 0;
   r.cls = 0;
+  r.id = 0;
   if (!have) return;
   uint32_t s32;
   piece_slot(q, nsq, S, tail, cx.chunk_old, cx.tt, &s32, &r.tile);
@@ -2240,12 +2254,16 @@ __device__ __forceinline__ void rb_load(const RbCtx<B>& cx, bool have, long long
   r.pos = cx.src.pos[s32];
   if constexpr (std::is_same<B, PhoBuf>::value) {
     r.a = cx.src.x[s32];
-    if (decide) r.n0 = (uint32_t)cx.src.n0[s32];
+    r.n0 = (uint32_t)cx.src.n0[s32];
+    if (!decide) r.b = cx.src.w[s32];
   } else {
     r.a = cx.src.w[s32];
-    if (decide) r.b = cx.src.u[s32];
+    r.b = cx.src.u[s32];
   }
-  if (!decide) r.cls = cx.cls[s32];
+  if (!decide) {
+    r.cls = cx.cls[s32];
+    r.id = cx.src.id[s32];
+  }
 }
 constexpr int RB_U = 4;   // rows whose loads a thread keeps in flight together
 
@@ -2255,8 +2273,14 @@ constexpr int RB_U = 4;   // rows whose loads a thread keeps in flight together
 // global atomics, aggregated per wave.  A store of at most RB_HW tiles puts
 // the window at tile 0, so that every tile is in it and the tail rows, whose
 // tiles are in no order, need no global atomics either (the production
-// gap's re-sort 0.83 -> 0.65 ms).
-constexpr int RB_HW = 1024;
+// gap's re-sort 0.83 -> 0.65 ms; with 1024 tiles in the window the 2048 of
+// the full-scale gap were not all in it, and its photons' count took 1.1 ms).
+// With more tiles the window slides: a range reaches few tiles, and a wide
+// window is only work to clear and store (a re-sort of a 32-tube scan, 2300
+// tiles: 0.91 ms with 2048).
+constexpr int RB_HW = 2048;
+constexpr int RB_SLIDE = 64;
+__host__ __device__ inline int rb_window(int n_tiles) { return n_tiles <= RB_HW ? n_tiles : RB_SLIDE; }
 
 __device__ __forceinline__ void rb_range(long long nch, long long* c0, long long* c1) {
   const int G = gridDim.x, bx = blockIdx.x;
@@ -2278,40 +2302,46 @@ __device__ __forceinline__ long long rb_row(long long i, long long c0, long long
   return i < c1 - c0 ? c0 + i : nsq + (long long)blockIdx.x + (i - (c1 - c0)) * (long long)gridDim.x;
 }
 
-// Wave-aggregated add of 1 per lane to bin `k` (k < 0: no-op).  `lds`: bins
-// are LDS entries relative to dlo, else global tile counters.  Returns this
-// lane's rank-based position (old value + rank) when `ret` is set.
-__device__ __forceinline__ int rb_wave_add(int k, int* lds_bins, int dlo, int* gbins, bool lds, bool ret) {
+// Adds 1 to bins[k] for every lane with k >= 0; RET: returns this lane's place
+// (the bin's old value plus its rank).  Lanes that share a bin are added
+// together, bin after bin.  LDS bins: two rounds of that (a row of a sorted
+// chunk goes to one tile and a class or two), then what is left adds one by
+// one (the lanes of a tail row can all go to different tiles: a round for
+// each made those rows the longest part of a re-sort).  Global bins: to the
+// end (neighbours in a tail mostly share tiles, and each atomic saved counts:
+// a 32-tube scan's re-sort takes 0.55 ms, 0.99 with single adds after two rounds).
+template <bool RET, bool LDS>
+__device__ __forceinline__ int rb_wave_add(int k, int* bins) {
   int out = -1;
-  while (true) {
-    uint64_t m = __ballot(k >= 0);
-    if (!m) break;
+  for (int round = 0; !LDS || round < 2; ++round) {
+    const uint64_t m = __ballot(k >= 0);
+    if (!m) return out;
     const int lead = __ffsll((long long)m) - 1;
-    const int kk = __shfl(k, lead);
+    const int kk = __builtin_amdgcn_readlane(k, lead);
     const uint64_t mk = __ballot(k == kk);
     int base = 0;
-    if (lane_id() == lead) {
-      if (lds) base = atomicAdd(&lds_bins[kk - dlo], (int)__popcll(mk));
-      else base = atomicAdd(&gbins[kk], (int)__popcll(mk));
+    if (lane_id() == lead) base = atomicAdd(&bins[kk], (int)__popcll(mk));
+    if (RET) base = __builtin_amdgcn_readlane(base, lead);
+    if (k == kk) {
+      out = base + rank_in(mk);
+      k = -1;
     }
-    if (ret) base = __shfl(base, lead);
-    if (k == kk) { out = base + rank_in(mk); k = -1; }
   }
+  if (LDS && k >= 0) out = atomicAdd(&bins[k], 1);
   return out;
 }
 
 template <class B>
 __global__ __launch_bounds__(TPB) void k_rb_count(RbCtx<B> cx) {
   constexpr int NC = RbClasses<B>::N;
-  __shared__ int s_h[RB_HW];
-  __shared__ int s_c[RB_HW * (NC - 1)];     // (tile - dlo) (NC - 1) + class, classes 0 .. NC - 2
+  __shared__ int s_c[RB_HW * NC];            // (tile - dlo) NC + class
   const long long nsc = cx.ctl->n_sorted_chunks, S = nsc * CHUNK, tail = cx.ctl->tail;
   const long long nsq = S / TPB, nq = nsq + (tail + TPB - 1) / TPB;
   long long c0, c1;
   rb_range(nsq, &c0, &c1);
   const long long nrow = rb_nrows(c0, c1, nsq, nq);
-  for (int j = threadIdx.x; j < RB_HW; j += blockDim.x) s_h[j] = 0;
-  for (int j = threadIdx.x; j < RB_HW * (NC - 1); j += blockDim.x) s_c[j] = 0;
+  const int hw = rb_window(cx.n_tiles), nbin = hw * NC;
+  for (int j = threadIdx.x; j < nbin; j += blockDim.x) s_c[j] = 0;
   __syncthreads();
   const int dlo = cx.n_tiles <= RB_HW ? 0 : (c0 < nsq ? cx.chunk_old[c0 / PPC] - 1 : -(1 << 30));
   for (long long i0 = 0; i0 < nrow; i0 += RB_U) {
@@ -2323,31 +2353,29 @@ __global__ __launch_bounds__(TPB) void k_rb_count(RbCtx<B> cx) {
     for (int u = 0; u < RB_U; ++u) {
       int cell; uint32_t frac; int k;
       const int nt = rb_locate(cx, in[u], &cell, &frac, &k, true);
-      const bool inw = nt >= 0 && nt - dlo >= 0 && nt - dlo < RB_HW;
-      rb_wave_add(inw ? nt : -1, s_h, dlo, cx.tcount, true, false);
-      rb_wave_add((nt >= 0 && !inw) ? nt : -1, s_h, dlo, cx.tcount, false, false);
-      const bool ck = nt >= 0 && k < NC - 1;
-      rb_wave_add((ck && inw) ? (nt - dlo) * (NC - 1) + k : -1, s_c, 0, nullptr, true, false);
-      rb_wave_add((ck && !inw) ? k * cx.n_tiles + nt : -1, nullptr, 0, cx.ccount, false, false);
+      const bool inw = nt >= 0 && nt - dlo >= 0 && nt - dlo < hw;
+      rb_wave_add<false, true>(inw ? (nt - dlo) * NC + k : -1, s_c);
+      const bool outw = nt >= 0 && !inw;
+      if (__ballot(outw)) {
+        rb_wave_add<false, false>(outw ? nt : -1, cx.tcount);
+        rb_wave_add<false, false>(outw && k < NC - 1 ? k * cx.n_tiles + nt : -1, cx.ccount);
+      }
     }
   }
   __syncthreads();
   // the window counts by (tile, class) for the scatter, whose workgroup b
   // takes the same rows as this one
-  int32_t* wh = cx.wh + (long long)blockIdx.x * (RB_HW * NC);
-  for (int j = threadIdx.x; j < RB_HW; j += blockDim.x) {
-    int rest = s_h[j];
-    for (int k = 0; k < NC - 1; ++k) {
-      const int c = s_c[j * (NC - 1) + k];
-      wh[j * NC + k] = c;
-      rest -= c;
+  int32_t* wh = cx.wh + (long long)blockIdx.x * nbin;
+  for (int j = threadIdx.x; j < nbin; j += blockDim.x) wh[j] = s_c[j];
+  for (int j = threadIdx.x; j < nbin / NC; j += blockDim.x) {
+    int n = 0;
+    for (int k = 0; k < NC; ++k) {
+      const int c = s_c[j * NC + k];
+      if (c > 0 && k < NC - 1) atomicAdd(&cx.ccount[k * cx.n_tiles + dlo + j], c);
+      n += c;
     }
-    wh[j * NC + NC - 1] = rest;
+    if (n > 0) atomicAdd(&cx.tcount[dlo + j], n);
   }
-  for (int j = threadIdx.x; j < RB_HW; j += blockDim.x)
-    if (s_h[j] > 0) atomicAdd(&cx.tcount[dlo + j], s_h[j]);
-  for (int j = threadIdx.x; j < RB_HW * (NC - 1); j += blockDim.x)
-    if (s_c[j] > 0) atomicAdd(&cx.ccount[(j % (NC - 1)) * cx.n_tiles + dlo + j / (NC - 1)], s_c[j]);
 }
 
 // Exclusive scan of the chunk counts of the tiles (one workgroup of
@@ -2432,33 +2460,29 @@ __device__ __forceinline__ long long rb_class_start(const RbCtx<B>& cx, int t, i
 template <class B>
 __global__ __launch_bounds__(TPB) void k_rb_scatter(RbCtx<B> cx) {
   constexpr int NC = RbClasses<B>::N;
-  __shared__ int s_h[RB_HW * NC];            // (tile - dlo) NC + class
-  __shared__ uint32_t s_base[RB_HW * NC];
+  __shared__ int s_at[RB_HW * NC];           // (tile - dlo) NC + class: next slot of this workgroup
   const long long nsc = cx.ctl->n_sorted_chunks, S = nsc * CHUNK, tail = cx.ctl->tail;
   const long long nsq = S / TPB, nq = nsq + (tail + TPB - 1) / TPB;
   long long c0, c1;
   rb_range(nsq, &c0, &c1);
   const long long nrow = rb_nrows(c0, c1, nsq, nq);
+  const int hw = rb_window(cx.n_tiles), nbin = hw * NC;
   const int dlo = cx.n_tiles <= RB_HW ? 0 : (c0 < nsq ? cx.chunk_old[c0 / PPC] - 1 : -(1 << 30));
-  // how many of this range go to each window tile and class: counted by the
-  // count kernel's workgroup of the same index, which took the same rows
-  // with the same window
+  // how many of this range go to each window tile and class, counted by the
+  // count kernel's workgroup of the same index, which took the same rows with
+  // the same window: one reservation per (workgroup, tile, class)
   {
-    const int32_t* wh = cx.wh + (long long)blockIdx.x * (RB_HW * NC);
-    for (int j = threadIdx.x; j < RB_HW * NC; j += blockDim.x) s_h[j] = wh[j];
-  }
-  __syncthreads();
-  // one reservation per (workgroup, tile, class)
-  for (int j = threadIdx.x; j < RB_HW * NC; j += blockDim.x) {
-    const int n = s_h[j];
-    if (n > 0) {
-      const int t = dlo + j / NC, k = j % NC;
-      s_base[j] = (uint32_t)(rb_class_start(cx, t, k) + atomicAdd(&cx.ccur[k * cx.n_tiles + t], n));
-      s_h[j] = 0;
+    const int32_t* wh = cx.wh + (long long)blockIdx.x * nbin;
+    for (int j = threadIdx.x; j < nbin; j += blockDim.x) {
+      const int n = wh[j];
+      if (n > 0) {
+        const int t = dlo + j / NC, k = j % NC;
+        s_at[j] = (int)(rb_class_start(cx, t, k) + atomicAdd(&cx.ccur[k * cx.n_tiles + t], n));
+      }
     }
   }
   __syncthreads();
-  // pass B: place the records
+  // place the records
   for (long long i0 = 0; i0 < nrow; i0 += RB_U) {
     RbIn in[RB_U];
 #pragma unroll
@@ -2468,13 +2492,15 @@ __global__ __launch_bounds__(TPB) void k_rb_scatter(RbCtx<B> cx) {
     for (int u = 0; u < RB_U; ++u) {
       int cell = 0, k; uint32_t frac = 0;
       const int nt = rb_locate(cx, in[u], &cell, &frac, &k, false);
-      const bool inw = nt >= 0 && nt - dlo >= 0 && nt - dlo < RB_HW;
-      const int ri = rb_wave_add(inw ? (nt - dlo) * NC + k : -1, s_h, 0, nullptr, true, true);
-      const int ro = rb_wave_add((nt >= 0 && !inw) ? k * cx.n_tiles + nt : -1, nullptr, 0, cx.ccur, false, true);
+      const bool inw = nt >= 0 && nt - dlo >= 0 && nt - dlo < hw;
+      const bool outw = nt >= 0 && !inw;
+      const int ri = rb_wave_add<true, true>(inw ? (nt - dlo) * NC + k : -1, s_at);
+      int ro = 0;
+      if (__ballot(outw)) ro = rb_wave_add<true, false>(outw ? k * cx.n_tiles + nt : -1, cx.ccur);
       if (nt >= 0) {
-        const long long dst = inw ? (long long)s_base[(nt - dlo) * NC + k] + ri : rb_class_start(cx, nt, k) + ro;
+        const long long dst = inw ? (long long)(uint32_t)ri : rb_class_start(cx, nt, k) + ro;
         const Tile tl = cx.tiles[nt];
-        rec_copy(cx.src, in[u].slot, cx.dst, dst, ((uint32_t)(cell - tl.base) << FRAC) | frac);
+        rec_place(cx.dst, dst, ((uint32_t)(cell - tl.base) << FRAC) | frac, in[u]);
       }
     }
   }
