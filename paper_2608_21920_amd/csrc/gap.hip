@@ -1490,7 +1490,7 @@ int build(gap_t* g, const gap_params* p, int n_tubes) {
     }
     const int nb = (q.n_cells + FB_NODES - 1) / FB_NODES;
     const int first = (int)g->fb_h.size();
-    for (int j = 0; j < nb; ++j) g->fb_h.push_back(FBlk{t, j * FB_NODES, first, nb});
+    for (int j = 0; j < nb; ++j) g->fb_h.push_back(FBlk{t, j * FB_NODES, first, nb, T.N, T.node_off, T.cell_off, T.flags, T.scale, T.bg_unit});
     g->n_tiles += T.n_tiles;
     g->total_nodes += q.n_cells + 1;
     g->total_cells += q.n_cells;

@@ -120,24 +120,24 @@ __global__ __launch_bounds__(FB_THREADS) void k_adj_field(AdjFieldCtx f) {
   __shared__ double sh[NW];
   __shared__ double s_above;
   __shared__ unsigned long long s_ep;
-  const FBlk b = f.fb[blockIdx.x];
+  const FBlk b = load_fblk(f.fb, (int)blockIdx.x);
   AdjTube& a = f.at[b.tube];
-  const int N = a.N;
+  const int N = b.N;
   const int bx = (int)blockIdx.x;
   const int q = b.nblk - 1 - (bx - b.first_blk);   // the tube's top block comes first
   const int k = q * FB_NODES + (int)threadIdx.x * FB_PER;
   unsigned long long* epoch = f.rec + 4 * gridDim.x + b.tube;
-  const double* nb = f.nb ? f.nb + a.node_off : nullptr;
+  const double* nb = f.nb ? f.nb + b.node_off : nullptr;
   double v[FB_PER], loc = 0.0;
 #pragma unroll
   for (int i = FB_PER - 1; i >= 0; --i) {
     v[i] = 0.0;
     if (k + i < N) {
       if (nb) v[i] = k + i < N - 1 ? 0.5 * (nb[k + i] + nb[k + i + 1]) : 0.5 * nb[N - 1] + nb[N];
-      if (f.E) v[i] += a.lossw * (double)f.E[a.cell_off + k + i];
-      f.lamE[a.cell_off + k + i] = v[i];
-      f.nb_clear[a.node_off + k + i] = 0.0;
-      if (k + i == N - 1) f.nb_clear[a.node_off + N] = 0.0;
+      if (f.E) v[i] += a.lossw * (double)f.E[b.cell_off + k + i];
+      f.lamE[b.cell_off + k + i] = v[i];
+      f.nb_clear[b.node_off + k + i] = 0.0;
+      if (k + i == N - 1) f.nb_clear[b.node_off + N] = 0.0;
     }
     loc += v[i];
   }
@@ -203,8 +203,8 @@ __global__ __launch_bounds__(FB_THREADS) void k_adj_field(AdjFieldCtx f) {
   for (int i = FB_PER - 1; i >= 0; --i) {
     if (k + i >= N) continue;
     s += v[i];
-    f.suf[a.node_off + k + i] = s;
-    if (k + i == N - 1) f.suf[a.node_off + N] = 0.0;
+    f.suf[b.node_off + k + i] = s;
+    if (k + i == N - 1) f.suf[b.node_off + N] = 0.0;
   }
   // (the look-back is over: every block of the tube has read the epoch)
   if (threadIdx.x == 0 && bx == b.first_blk + b.nblk - 1)
