@@ -1189,11 +1189,12 @@ constexpr int64_t FUSED_PHO_CHUNKS = 4096;
 
 // Whether the next step takes the fused form.  A store's chunk count, read
 // back at every synchronising call, holds until the next re-sort, and is
-// taken as a sign of its size for the period after that; a longer run
+// taken as a sign of its size for three periods after that; a longer run
 // without such a call may have grown the store, and goes over to the general
-// form.  (No result depends on it.)
+// form.  (No result depends on it.  With one period after it the tiny gap's
+// 500-step cascade takes 18.5 ms instead of 18.1.)
 bool fused_form(const gap_t* g) {
-  return !g->timing && g->seen_l >= 0 && g->seen_p >= 0 && g->seen_p <= FUSED_PHO_CHUNKS && g->rb_seen <= 1;
+  return !g->timing && g->seen_l >= 0 && g->seen_p >= 0 && g->seen_p <= FUSED_PHO_CHUNKS && g->rb_seen <= 3;
 }
 
 template <bool Q, bool A, int V>
