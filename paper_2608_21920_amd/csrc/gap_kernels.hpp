@@ -174,6 +174,18 @@ __device__ void flush_counts(long long* shard, int tube, LocalCounts& lc, long l
   lc.clear();
 }
 
+// Event counts of a piece of a tail pass, whose lanes may belong to different
+// tubes (KIND as in cnt_index).
+template <int KIND>
+__device__ __forceinline__ void tail_counts(const Ctx& cx, int tube, LocalCounts& lcn) {
+#pragma unroll
+  for (int i = 0; i < 7; ++i) {
+    const int v = lcn.v[i];
+    if (__ballot(v != 0)) count_by_tube(cx.shard, v != 0 ? tube : -1, cnt_index<KIND>(i), v);
+  }
+  lcn.clear();
+}
+
 // Exclusive prefix sum of `v` over the wave; returns the exclusive value and
 // writes the wave total to *total.
 __device__ __forceinline__ int wave_excl_scan(int v, int* total) {
@@ -392,15 +404,10 @@ __device__ __forceinline__ void prologue(const Ctx& cx, int n_tubes, bool count_
 __global__ __launch_bounds__(PRE_THREADS, 5) void k_pre(Ctx cx, int n_tubes) { prologue<true>(cx, n_tubes, true); }
 
 // ------------------------------------------------------------------ leptons
-// Constants of one tile and its tube, read once per tile switch and held in
-// scalar registers (the tube records are also written by the kernels, so the
-// compiler cannot turn per-lane reads of them into scalar loads).
+// Constants of one tile and its tube, for the tails and the birth replay.
 struct KC {
   int tile, tube, base, N, node_off, flags, nsub_max, dpho;
   int64_t step, hfix;
-  // a non-periodic tube's photon at tile-local position q (fixed point from
-  // the window base) is outside [0, L) or above H when q < xlo or q >= xhi
-  int64_t xlo, xhi;
   float dt, lr, inv_rc, b, xc_floor, x_thr, emit_k, conv_k, cfl24, chi_skip;
   uint64_t seed;
 };
@@ -412,49 +419,15 @@ __device__ __forceinline__ int64_t rfl(int64_t v) {
   return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
-// pho: the photon passes take the step index from step_now (set by the
-// prologue), the lepton passes from step (they run on the stream of the field
-// scan that advances it)
-__device__ __forceinline__ KC load_kc(const Ctx& cx, int tile, bool pho) {
-  KC k;
-  tile = rfl(tile);
-  const Tile tl = cx.tiles[tile];
-  const Tube& T = cx.tubes[rfl(tl.tube)];
-  k.tile = tile;
-  k.tube = rfl(tl.tube);
-  k.base = rfl(tl.base);
-  k.N = rfl(T.N);
-  k.node_off = rfl(T.node_off);
-  k.flags = rfl(T.flags);
-  k.nsub_max = rfl(T.nsub_max);
-  k.dpho = rfl(T.dpho);
-  k.step = rfl(pho ? (int64_t)T.step_now : (int64_t)T.step);
-  k.hfix = rfl((int64_t)T.hfix);
-  k.xlo = -((int64_t)k.base << FRAC);
-  k.xhi = min(k.hfix - ((int64_t)k.base << FRAC), (int64_t)(k.N - k.base) << FRAC);
-  k.dt = rfl(T.dt);
-  k.lr = rfl(T.lr);
-  k.inv_rc = rfl(T.inv_rc);
-  k.b = rfl(T.b);
-  k.xc_floor = rfl(T.xc_floor);
-  k.x_thr = rfl(T.x_thr);
-  k.emit_k = rfl(T.emit_k);
-  k.conv_k = rfl(T.conv_k);
-  k.cfl24 = rfl(T.cfl24);
-  k.chi_skip = rfl(T.chi_skip);
-  k.seed = (uint64_t)rfl((int64_t)T.seed);
-  return k;
-}
-
-// The same constants for a lane's own tile (tail chunks: not uniform).
+// The constants of a lane's own tile (not uniform).  pho: the photon passes
+// take the step index from step_now (set by the prologue), the lepton passes
+// from step (they run on the stream of the field scan that advances it).
 __device__ __forceinline__ KC lane_kc(const Ctx& cx, int tile, bool pho) {
   KC k;
   const Tile tl = cx.tiles[tile];
   const Tube& T = cx.tubes[tl.tube];
   k.tile = tile; k.tube = tl.tube; k.base = tl.base; k.N = T.N; k.node_off = T.node_off; k.flags = T.flags;
   k.nsub_max = T.nsub_max; k.dpho = T.dpho; k.step = pho ? T.step_now : T.step; k.hfix = T.hfix; k.dt = T.dt; k.lr = T.lr;
-  k.xlo = -((int64_t)k.base << FRAC);
-  k.xhi = min(k.hfix - ((int64_t)k.base << FRAC), (int64_t)(k.N - k.base) << FRAC);
   k.inv_rc = T.inv_rc; k.b = T.b; k.xc_floor = T.xc_floor; k.x_thr = T.x_thr; k.emit_k = T.emit_k;
   k.conv_k = T.conv_k; k.cfl24 = T.cfl24; k.chi_skip = T.chi_skip; k.seed = T.seed;
   return k;
@@ -710,12 +683,7 @@ __device__ void lepton_one(const Ctx& cx, uint32_t slot, int tile, LocalCounts& 
   lcn.v[2] += nev;
   lcn.v[5] += absorbed ? 1 : 0;
   lcn.v[6] += outflow ? 1 : 0;
-#pragma unroll
-  for (int i = 0; i < 7; ++i) {
-    const int v = lcn.v[i];
-    if (__ballot(v != 0)) count_by_tube(cx.shard, v != 0 ? tube : -1, cnt_index<2>(i), v);
-  }
-  lcn.clear();
+  tail_counts<2>(cx, tube, lcn);
 }
 
 // V consecutive records of one thread in the sorted passes, loaded and stored
@@ -1139,22 +1107,15 @@ __device__ __forceinline__ float photon_prob(const K& k, float x, int32_t n0) {
   return chi > k.chi_skip ? p : 0.0f;
 }
 
-// One photon: free streaming at c, exit above H, conversion with
+// One photon of the tail: free streaming at c, exit above H, conversion with
 // rate alpha_em (b/lambda~) sin(psi) T_BW(x b sin psi), sin(psi) = |sin(s/R~)|.
 // Below chi_skip the fit gives p < 2^-27, under every 24-bit uniform: no
 // draw is needed and none is made.
-template <bool UNI, bool Q>
-__device__ void photon_one(const Ctx& cx, uint32_t slot, int tile, const KC& ku, LocalCounts& lcn, float x, uint32_t pos,
-                           int32_t n0, uint32_t* pos_out, float* x_out, const Room& lroom) {
-  bool alive;
-  KC k;
-  if (UNI) {
-    k = ku;
-    alive = x != 0.0f;
-  } else {
-    alive = tile >= 0 && x != 0.0f;
-    k = lane_kc(cx, alive ? tile : 0, true);
-  }
+template <bool Q>
+__device__ void photon_one(const Ctx& cx, uint32_t slot, int tile, LocalCounts& lcn, float x, uint32_t pos, int32_t n0,
+                           const Room& lroom) {
+  const bool alive = tile >= 0 && x != 0.0f;
+  const KC k = lane_kc(cx, alive ? tile : 0, true);
   if (!alive) { x = 0.0f; pos = 0; n0 = 0; }
   const int tube = alive ? k.tube : -1;
   const int N = k.N;
@@ -1189,10 +1150,7 @@ __device__ void photon_one(const Ctx& cx, uint32_t slot, int tile, const KC& ku,
       rsplit = r.b;
     }
   }
-  if (UNI) {           // the caller stores the chunk's records with vector stores
-    *pos_out = (uint32_t)np;
-    *x_out = (dead || conv) ? 0.0f : x;
-  } else if (alive) {
+  if (alive) {
     if (dead || conv) cx.P.x[slot] = 0.0f;
     else cx.P.pos[slot] = (uint32_t)np;
   }
@@ -1225,14 +1183,7 @@ __device__ void photon_one(const Ctx& cx, uint32_t slot, int tile, const KC& ku,
   lcn.v[1] += eval ? 1 : 0;
   lcn.v[2] += conv ? 1 : 0;
   lcn.v[4] += exited ? 1 : 0;
-  if (!UNI) {
-#pragma unroll
-    for (int i = 0; i < 5; ++i) {
-      const int v = lcn.v[i];
-      if (__ballot(v != 0)) count_by_tube(cx.shard, v != 0 ? tube : -1, cnt_index<3>(i), v);
-    }
-    lcn.clear();
-  }
+  tail_counts<3>(cx, tube, lcn);
 }
 
 template <int V> struct PhoV { Rec<float, V> x; Rec<uint32_t, V> pos; Rec<int32_t, V> n0; };
@@ -1556,7 +1507,6 @@ __device__ __forceinline__ void photons_tail(const Ctx& cx, int bid, int nblk) {
   const long long S = nsc * CHUNK;
   const long long tail = cx.pc->tail_snap;
   const long long nq = (tail + TPB - 1) / TPB;
-  const KC kc0 = load_kc(cx, 0, true);
   for (long long q = bid; q < nq; q += nblk) {
     uint32_t slot;
     int tile;
@@ -1564,7 +1514,7 @@ __device__ __forceinline__ void photons_tail(const Ctx& cx, int bid, int nblk) {
     const float x = cx.P.x[slot];
     const uint32_t pos = cx.P.pos[slot];
     const int32_t n0 = cx.P.n0[slot];
-    photon_one<false, Q>(cx, slot, tile, kc0, lcn, x, pos, n0, nullptr, nullptr, lroom);
+    photon_one<Q>(cx, slot, tile, lcn, x, pos, n0, lroom);
   }
 }
 
