@@ -270,6 +270,8 @@ struct gap_t {
   // error bits, and each store's chunk count + 1 as its last re-sort left it
   struct Status { int err, pad; long long chunks[2]; };
   Status* status = nullptr;
+  uint32_t* stage = nullptr;       // device staging of the small reads, and their host side
+  std::vector<char> stage_h;
   // what the last such call found (chunks -1: not known), and the re-sorts
   // enqueued since
   int64_t seen_l = -1, seen_p = -1;
@@ -278,7 +280,8 @@ struct gap_t {
   float* qs = nullptr;     // quantum photon-spectrum table (tubes with GAP_QUANTUM)
   float* qb = nullptr;     // quantum pair-split table
   int* err = nullptr;
-  long long* live = nullptr;
+  long long* live = nullptr;     // live leptons, then photons, per tube
+  long long* counts = nullptr;   // one tube's counters, gathered for the host
   long long* shard = nullptr;   // [tube][NSHARD][C_N] event counters
   Store lep, pho;
   // per-kernel event timing (eager steps only)
@@ -606,6 +609,30 @@ FieldCtx make_fctx(gap_t* g, int mode) {
 }
 
 __global__ void k_cold_off(Ctl* c) { c->cold_steps = -1; }
+// A tube's counters as GAP_DIAG_COUNTS gives them: its own and its shards', live
+// particles and steps (the error code is the host's).  One wave.
+__global__ void k_counts(const Tube* tubes, int tube, int n_tubes, const long long* shard, const long long* live,
+                         long long* out) {
+  __shared__ long long s_o[C_N];
+  const int i = (int)threadIdx.x;
+  if (i < C_N) {
+    long long v = tubes[tube].cnt[i];
+    for (int k = 0; k < NSHARD; ++k) v += shard[((long long)tube * NSHARD + k) * C_N + i];
+    s_o[i] = v;
+  }
+  __syncthreads();
+  if (i >= C_N) return;
+  long long v = s_o[i];
+  // totals include the tail passes (the *_TAIL slots hold that part)
+  if (i == C_LEP_STEPS) v += s_o[C_LEP_STEPS_TAIL];
+  if (i == C_EMIT_EVAL) v += s_o[C_EMIT_EVAL_TAIL];
+  if (i == C_PHO_STEPS) v += s_o[C_PHO_STEPS_TAIL];
+  if (i == C_CONV_EVAL) v += s_o[C_CONV_EVAL_TAIL];
+  if (i == C_LEPTONS) v = live[tube];
+  if (i == C_PHOTONS) v = live[n_tubes + tube];
+  if (i == C_STEP) v = tubes[tube].step;
+  out[i] = v;
+}
 __global__ void k_raise(int* err, int bits) { atomicOr(err, bits); }
 
 __global__ void k_fill_i32(int32_t* p, long long n, int32_t v) {
@@ -1292,9 +1319,7 @@ void enqueue_step(gap_t* g, bool more) {
   ++g->host_step;
 }
 
-int read_err(gap_t* g) {
-  gap_t::Status st{};
-  if (hipMemcpy(&st, g->status, sizeof(st), hipMemcpyDeviceToHost) != hipSuccess) return GAP_EDEVICE;
+int take_status(gap_t* g, const gap_t::Status& st) {
   const int e = st.err;
   g->seen_l = st.chunks[0] - 1;
   g->seen_p = st.chunks[1] - 1;
@@ -1306,10 +1331,51 @@ int read_err(gap_t* g) {
   return g->sticky;
 }
 
+int read_err(gap_t* g) {
+  gap_t::Status st{};
+  if (hipMemcpy(&st, g->status, sizeof(st), hipMemcpyDeviceToHost) != hipSuccess) return GAP_EDEVICE;
+  return take_status(g, st);
+}
+
 int sync_and_err(gap_t* g) {
   if (hipStreamSynchronize(g->s) != hipSuccess) return GAP_EDEVICE;
   if (hipGetLastError() != hipSuccess) return GAP_EDEVICE;
   return read_err(g);
+}
+
+// Reads `bytes` device bytes into host memory behind all queued work, together
+// with the status words: one kernel gathers both, so that one copy and one
+// wait do (the copies of a few bytes cost what a wait does: a step of the tiny
+// gap with a read of its field and its charge took 87 us with two waits and
+// two copies per read).  Results past the staging buffer take their own copy.
+constexpr size_t kStageBytes = 4 << 20;
+constexpr size_t kStageHead = 64;
+static_assert(sizeof(gap_t::Status) <= kStageHead, "");
+
+__global__ void k_gather(const uint32_t* status, const uint32_t* src, long long words, uint32_t* out) {
+  const long long i0 = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i0 < (long long)(sizeof(gap_t::Status) / 4)) out[i0] = status[i0];
+  for (long long i = i0; i < words; i += (long long)gridDim.x * blockDim.x) out[kStageHead / 4 + i] = src[i];
+}
+
+int read_back(gap_t* g, const void* src, size_t bytes, void* host) {
+  if (bytes + kStageHead > kStageBytes || bytes % 4 != 0) {
+    const int e = sync_and_err(g);
+    if (e == GAP_EDEVICE) return e;
+    HIPCHK(hipMemcpy(host, src, bytes, hipMemcpyDeviceToHost));
+    return GAP_OK;
+  }
+  const long long words = (long long)(bytes / 4);
+  g->stage_h.resize(kStageHead + bytes);
+  k_gather<<<std::max(1, (int)std::min<long long>(256, (words + 255) / 256)), 256, 0, g->s>>>(
+      (const uint32_t*)g->status, (const uint32_t*)src, words, g->stage);
+  HIPCHK(hipMemcpyAsync(g->stage_h.data(), g->stage, kStageHead + bytes, hipMemcpyDeviceToHost, g->s));
+  HIPCHK(hipStreamSynchronize(g->s));
+  if (hipGetLastError() != hipSuccess) return GAP_EDEVICE;
+  gap_t::Status st;
+  std::memcpy(&st, g->stage_h.data(), sizeof(st));
+  std::memcpy(host, g->stage_h.data() + kStageHead, bytes);
+  return take_status(g, st) == GAP_EDEVICE ? GAP_EDEVICE : GAP_OK;
 }
 
 Ctl read_ctl(const Store& st) {
@@ -1552,7 +1618,11 @@ int build(gap_t* g, const gap_params* p, int n_tubes) {
   g->status = (gap_t::Status*)dalloc(g, sizeof(gap_t::Status));
   if (!g->status) return GAP_ENOMEM;
   g->err = &g->status->err;
-  g->live = (long long*)dalloc(g, sizeof(long long) * n_tubes);
+  g->stage = (uint32_t*)dalloc(g, kStageBytes);
+  if (!g->stage) return GAP_ENOMEM;
+  g->live = (long long*)dalloc(g, sizeof(long long) * 2 * n_tubes);
+  g->counts = (long long*)dalloc(g, sizeof(long long) * C_N);
+  if (!g->counts) return GAP_ENOMEM;
   g->shard = (long long*)dalloc(g, sizeof(long long) * n_tubes * NSHARD * C_N);
   if (!g->shard) return GAP_ENOMEM;
   if (!g->tubes || !g->tiles || !g->rho || !g->rho_last || !g->E || !g->ebar || !g->fb || !g->part || !g->part2 || !g->fscan ||
@@ -1972,8 +2042,13 @@ int gap_sync(gap_t* g) {
 
 int gap_diag(gap_t* g, int32_t kind, int32_t tube, void* host_buf, size_t buf_bytes, size_t* bytes_written) {
   if (!g || tube < 0 || tube >= g->n_tubes || (!host_buf && buf_bytes)) return GAP_EINVAL;
-  int e = sync_and_err(g);
-  if (e == GAP_EDEVICE) return e;
+  int e = GAP_OK;
+  // (the other kinds wait where they read)
+  if (kind == GAP_DIAG_LEPTONS || kind == GAP_DIAG_PHOTONS || kind == GAP_DIAG_PROTONS || kind == GAP_DIAG_RETURN ||
+      kind == GAP_DIAG_WATERFALL || kind == GAP_DIAG_TIMING || kind == GAP_DIAG_LAUNCH || kind == GAP_DIAG_DERIVED) {
+    e = sync_and_err(g);
+    if (e == GAP_EDEVICE) return e;
+  }
   const Tube& Th = g->th[tube];
   const int N = g->P[tube].n_cells;
   size_t need = 0;
@@ -1985,57 +2060,29 @@ int gap_diag(gap_t* g, int32_t kind, int32_t tube, void* host_buf, size_t buf_by
   switch (kind) {
     case GAP_DIAG_COUNTS: {
       if (!fits(sizeof(int64_t) * 32)) return GAP_EINVAL;
-      if ((e = download_tubes(g))) return e;
+      k_fill_i64<<<1, 256, 0, g->s>>>(g->live, 2 * g->n_tubes, 0);
+      k_count_live<LepBuf><<<kGrid, TPB, 0, g->s>>>(g->lep.lep(g->lep.cur), g->lep.ctl, g->lep.chunk[g->lep.cur], g->lep.tt,
+                                                  g->tiles, g->live, g->n_tubes);
+      k_count_live<PhoBuf><<<kGrid, TPB, 0, g->s>>>(g->pho.pho(g->pho.cur), g->pho.ctl, g->pho.chunk[g->pho.cur], g->pho.tt,
+                                                  g->tiles, g->live + g->n_tubes, g->n_tubes);
+      k_counts<<<1, 64, 0, g->s>>>(g->tubes, tube, g->n_tubes, g->shard, g->live, g->counts);
+      if ((e = read_back(g, g->counts, sizeof(int64_t) * 32, host_buf))) return e;
       int64_t* o = (int64_t*)host_buf;
-      for (int i = 0; i < 32; ++i) o[i] = g->th[tube].cnt[i];
-      {
-        std::vector<long long> sh((size_t)NSHARD * C_N);
-        HIPCHK(hipMemcpy(sh.data(), g->shard + (size_t)tube * NSHARD * C_N, sizeof(long long) * sh.size(),
-                         hipMemcpyDeviceToHost));
-        for (int k = 0; k < NSHARD; ++k)
-          for (int i = 0; i < 32; ++i) o[i] += sh[(size_t)k * C_N + i];
-        // totals include the tail passes (the *_TAIL slots hold that part)
-        o[GAP_C_LEP_STEPS] += o[GAP_C_LEP_STEPS_TAIL];
-        o[GAP_C_EMIT_EVAL] += o[GAP_C_EMIT_EVAL_TAIL];
-        o[GAP_C_PHO_STEPS] += o[GAP_C_PHO_STEPS_TAIL];
-        o[GAP_C_CONV_EVAL] += o[GAP_C_CONV_EVAL_TAIL];
-      }
-      long long lv[2] = {0, 0};
-      const int grid = kGrid;
-      k_fill_i64<<<1, 256, 0, g->s>>>(g->live, g->n_tubes, 0);
-      { const Ctl* c = g->lep.ctl;
-        k_count_live<LepBuf><<<grid, TPB, 0, g->s>>>(g->lep.lep(g->lep.cur), c, g->lep.chunk[g->lep.cur], g->lep.tt, g->tiles, g->live, g->n_tubes); }
-      HIPCHK(hipStreamSynchronize(g->s));
-      HIPCHK(hipMemcpy(&lv[0], g->live + tube, 8, hipMemcpyDeviceToHost));
-      k_fill_i64<<<1, 256, 0, g->s>>>(g->live, g->n_tubes, 0);
-      { const Ctl* c = g->pho.ctl;
-        k_count_live<PhoBuf><<<grid, TPB, 0, g->s>>>(g->pho.pho(g->pho.cur), c, g->pho.chunk[g->pho.cur], g->pho.tt, g->tiles, g->live, g->n_tubes); }
-      HIPCHK(hipStreamSynchronize(g->s));
-      HIPCHK(hipMemcpy(&lv[1], g->live + tube, 8, hipMemcpyDeviceToHost));
-      o[GAP_C_LEPTONS] = lv[0];
-      o[GAP_C_PHOTONS] = lv[1];
-      o[GAP_C_STEP] = g->th[tube].step;
       o[GAP_C_ERR] = g->sticky;
       return GAP_OK;
     }
     case GAP_DIAG_FIELD:
       if (!fits(sizeof(float) * N)) return GAP_EINVAL;
-      HIPCHK(hipMemcpy(host_buf, g->E + Th.cell_off, sizeof(float) * N, hipMemcpyDeviceToHost));
-      return GAP_OK;
+      return read_back(g, g->E + Th.cell_off, sizeof(float) * N, host_buf);
     case GAP_DIAG_NODE_E:
       if (!fits(sizeof(float) * (N + 1))) return GAP_EINVAL;
-      HIPCHK(hipMemcpy(host_buf, g->ebar + Th.node_off, sizeof(float) * (N + 1), hipMemcpyDeviceToHost));
-      return GAP_OK;
+      return read_back(g, g->ebar + Th.node_off, sizeof(float) * (N + 1), host_buf);
     case GAP_DIAG_RHO:
       if (!fits(sizeof(int64_t) * (N + 1))) return GAP_EINVAL;
-      HIPCHK(hipMemcpy(host_buf, g->rho_last + Th.node_off, sizeof(int64_t) * (N + 1), hipMemcpyDeviceToHost));
-      return GAP_OK;
-    case GAP_DIAG_ES: {
+      return read_back(g, g->rho_last + Th.node_off, sizeof(int64_t) * (N + 1), host_buf);
+    case GAP_DIAG_ES:
       if (!fits(sizeof(double))) return GAP_EINVAL;
-      if ((e = download_tubes(g))) return e;
-      std::memcpy(host_buf, &g->th[tube].Es, sizeof(double));
-      return GAP_OK;
-    }
+      return read_back(g, &g->tubes[tube].Es, sizeof(double), host_buf);
     case GAP_DIAG_PROFILE:
     case GAP_DIAG_PEAK: {
       const int B = g->prof_bin;
@@ -2050,15 +2097,13 @@ int gap_diag(gap_t* g, int32_t kind, int32_t tube, void* host_buf, size_t buf_by
       if (kind == GAP_DIAG_PROFILE) {
         k_profile_finish<<<std::max(1, std::min(1024, (nb * PROF_G + 255) / 256)), 256, 0, g->s>>>(g->prof_acc, nb,
                                                                                                  bppc, g->prof_out);
-        HIPCHK(hipStreamSynchronize(g->s));
-        HIPCHK(hipMemcpy(host_buf, g->prof_out, sizeof(double) * 3 * PROF_G * (size_t)nb, hipMemcpyDeviceToHost));
+        if ((e = read_back(g, g->prof_out, sizeof(double) * 3 * PROF_G * (size_t)nb, host_buf))) return e;
       } else {
         k_profile_peak<<<1, PEAK_T, 0, g->s>>>(g->prof_acc, nb, B, g->P[tube].dx, g->D[tube].H, bppc,
                                             g->E + Th.cell_off, N, g->prof_out);
-        HIPCHK(hipStreamSynchronize(g->s));
-        HIPCHK(hipMemcpy(host_buf, g->prof_out, sizeof(double) * 6, hipMemcpyDeviceToHost));
+        if ((e = read_back(g, g->prof_out, sizeof(double) * 6, host_buf))) return e;
       }
-      return sync_and_err(g);
+      return g->sticky;
     }
     case GAP_DIAG_RETURN: {
       // double[RET_N]; reading resets the tube's record
@@ -2111,17 +2156,15 @@ int gap_diag(gap_t* g, int32_t kind, int32_t tube, void* host_buf, size_t buf_by
       const int lw = phase_window(B);
       k_phase<<<kDiagGrid, TPB, sizeof(double) * 2 * lw * PHASE_NP, g->s>>>(make_ctx(g), tube, B, nb, g->spec_thr,
                                                                            g->phase_acc, lw);
-      HIPCHK(hipStreamSynchronize(g->s));
-      HIPCHK(hipMemcpy(host_buf, g->phase_acc, sizeof(double) * n, hipMemcpyDeviceToHost));
-      return sync_and_err(g);
+      if ((e = read_back(g, g->phase_acc, sizeof(double) * n, host_buf))) return e;
+      return g->sticky;
     }
     case GAP_DIAG_SPECTRA: {
       if (!fits(sizeof(double) * 3 * SPEC_NB)) return GAP_EINVAL;
       k_fill_i64<<<1, 256, 0, g->s>>>((long long*)g->spec_acc, 3 * SPEC_NB, 0);
       k_spectra<<<kDiagGrid, TPB, 0, g->s>>>(make_ctx(g), tube, g->spec_thr, g->spec_acc);
-      HIPCHK(hipStreamSynchronize(g->s));
-      HIPCHK(hipMemcpy(host_buf, g->spec_acc, sizeof(double) * 3 * SPEC_NB, hipMemcpyDeviceToHost));
-      return sync_and_err(g);
+      if ((e = read_back(g, g->spec_acc, sizeof(double) * 3 * SPEC_NB, host_buf))) return e;
+      return g->sticky;
     }
     case GAP_DIAG_ESPECTRUM: {
       // double[M/2 + 1], M the next power of two >= N
@@ -2144,9 +2187,8 @@ int gap_diag(gap_t* g, int32_t kind, int32_t tube, void* host_buf, size_t buf_by
         std::swap(x, y);
       }
       k_fft_power<<<grid, 256, 0, g->s>>>(x, M, g->fft_pow);
-      HIPCHK(hipStreamSynchronize(g->s));
-      HIPCHK(hipMemcpy(host_buf, g->fft_pow, sizeof(double) * (size_t)(M / 2 + 1), hipMemcpyDeviceToHost));
-      return sync_and_err(g);
+      if ((e = read_back(g, g->fft_pow, sizeof(double) * (size_t)(M / 2 + 1), host_buf))) return e;
+      return g->sticky;
     }
     case GAP_DIAG_TIMING: {
       // double[2 * KT_N]: launches and summed milliseconds per kernel group
