@@ -1808,6 +1808,23 @@ int build(gap_t* g, const gap_params* p, int n_tubes) {
   return sync_and_err(g);
 }
 
+// Transform of E zero-padded to M cells; x and y hold M values each, the
+// returned one the result.
+double2* fft(gap_t* g, const float* E, int N, int M, double2* x, double2* y) {
+  const int grid = std::max(1, std::min(1024, (M + 255) / 256));
+  k_fft_load<<<grid, 256, 0, g->s>>>(E, N, M, x);
+  int Ns = 1;
+  for (; 4 * Ns <= M; Ns *= 4) {
+    k_fft_stage4<<<grid, 256, 0, g->s>>>(x, y, M, Ns);
+    std::swap(x, y);
+  }
+  if (Ns < M) {                      // M is an odd power of two
+    k_fft_stage<<<grid, 256, 0, g->s>>>(x, y, M, Ns);
+    std::swap(x, y);
+  }
+  return x;
+}
+
 // Copy a store to the host and decode the live records of tube `tube`.
 struct HostRec { int32_t cell; uint32_t frac; float a; float w; int32_t n0; uint64_t id; };
 
@@ -2179,13 +2196,7 @@ int gap_diag(gap_t* g, int32_t kind, int32_t tube, void* host_buf, size_t buf_by
         if (!g->fft_buf || !g->fft_pow) return GAP_ENOMEM;
       }
       const int grid = std::max(1, std::min(1024, (M + 255) / 256));
-      double2* x = g->fft_buf;
-      double2* y = g->fft_buf + M;
-      k_fft_load<<<grid, 256, 0, g->s>>>(g->E + Th.cell_off, N, M, x);
-      for (int Ns = 1; Ns < M; Ns *= 2) {
-        k_fft_stage<<<grid, 256, 0, g->s>>>(x, y, M, Ns);
-        std::swap(x, y);
-      }
+      const double2* x = fft(g, g->E + Th.cell_off, N, M, g->fft_buf, g->fft_buf + M);
       k_fft_power<<<grid, 256, 0, g->s>>>(x, M, g->fft_pow);
       if ((e = read_back(g, g->fft_pow, sizeof(double) * (size_t)(M / 2 + 1), host_buf))) return e;
       return g->sticky;
@@ -2632,13 +2643,7 @@ int gap_e_spectrum_noalloc(gap_t* g, int32_t tube, double* power, int64_t power_
   // static workspace (every entry is written before it is read) and the
   // result in the caller's buffer; nothing is allocated, nothing waits
   const int grid = std::max(1, std::min(1024, (M + 255) / 256));
-  double2* x = g->scratch;
-  double2* y = g->scratch + M;
-  k_fft_load<<<grid, 256, 0, g->s>>>(g->E + g->th[tube].cell_off, N, M, x);
-  for (int Ns = 1; Ns < M; Ns *= 2) {
-    k_fft_stage<<<grid, 256, 0, g->s>>>(x, y, M, Ns);
-    std::swap(x, y);
-  }
+  const double2* x = fft(g, g->E + g->th[tube].cell_off, N, M, g->scratch, g->scratch + M);
   k_fft_power<<<grid, 256, 0, g->s>>>(x, M, power);
   return hipGetLastError() == hipSuccess ? GAP_OK : GAP_EDEVICE;
 }
