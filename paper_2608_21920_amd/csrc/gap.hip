@@ -9,6 +9,7 @@
 #include "gap_qtab.hpp"
 #include "gap_protons.hpp"
 #include "gap_fused.hpp"
+#include "gap_records.hpp"
 
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
@@ -305,6 +306,7 @@ struct gap_t {
   // results for the largest tube at one cell per bin
   double* ret = nullptr;
   double* ret_thr = nullptr;           // [RET_NB]: lower bin edges in u^2
+  int64_t* rec_count = nullptr;        // record counts of the export's blocks, allocated on first use
   double* prof_acc = nullptr;
   double* prof_out = nullptr;
   int prof_bin = 64;                   // cells per profile bin
@@ -1825,40 +1827,38 @@ double2* fft(gap_t* g, const float* E, int N, int M, double2* x, double2* y) {
   return x;
 }
 
-// Copy a store to the host and decode the live records of tube `tube`.
-struct HostRec { int32_t cell; uint32_t frac; float a; float w; int32_t n0; uint64_t id; };
-
-int export_store(gap_t* g, const Store& st, bool photon, int tube, std::vector<HostRec>& out) {
-  const Ctl c = read_ctl(st);
-  const long long S = c.n_sorted_chunks * CHUNK, n = S + c.tail;
-  std::vector<uint32_t> pos(n);
-  std::vector<float> a(n), w(n);
-  std::vector<int32_t> n0(photon ? n : 0), chunk(c.n_sorted_chunks), tt(n);
-  std::vector<uint64_t> id(n);
-  const int b = st.cur;
-  if (n > 0) {
-    HIPCHK(hipMemcpy(pos.data(), st.pos[b], 4 * n, hipMemcpyDeviceToHost));
-    HIPCHK(hipMemcpy(a.data(), st.a[b], 4 * n, hipMemcpyDeviceToHost));
-    HIPCHK(hipMemcpy(w.data(), st.w[b], 4 * n, hipMemcpyDeviceToHost));
-    HIPCHK(hipMemcpy(id.data(), st.id[b], 8 * n, hipMemcpyDeviceToHost));
-    if (photon) HIPCHK(hipMemcpy(n0.data(), st.n0[b], 4 * n, hipMemcpyDeviceToHost));
-    HIPCHK(hipMemcpy(tt.data(), st.tt, 4 * n, hipMemcpyDeviceToHost));
+// The live records of tube `tube` into host_buf in slot order (*need: their
+// bytes; nothing is copied when they do not fit).  The pieces are packed in
+// the birth queue, which only a step uses.
+int export_store(gap_t* g, bool photon, int tube, void* host_buf, size_t buf_bytes, size_t* need) {
+  const int64_t slots = std::max(g->lep.capacity, g->pho.capacity);
+  if (!g->rec_count) {
+    g->rec_count = (int64_t*)dalloc(g, sizeof(int64_t) * (size_t)(slots / REC_BLOCK + 2));   // kept until the handle ends
+    if (!g->rec_count) return GAP_ENOMEM;
   }
-  if (c.n_sorted_chunks > 0) HIPCHK(hipMemcpy(chunk.data(), st.chunk[b], 4 * c.n_sorted_chunks, hipMemcpyDeviceToHost));
-  out.clear();
-  for (long long i = 0; i < n; ++i) {
-    const int tile = i < S ? chunk[i / CHUNK] : tt[i];
-    if (tile < 0 || tile >= g->n_tiles) continue;
-    const bool alive = photon ? (a[i] != 0.0f) : (w[i] != 0.0f);
-    if (!alive) continue;
-    const Tile& tl = g->tiles_h[tile];
-    if (tl.tube != tube) continue;
-    int cell = tl.base + (int)(pos[i] >> FRAC);
-    const int N = g->P[tube].n_cells;
-    if (g->P[tube].flags & GAP_PERIODIC) cell = cell < 0 ? cell + N : (cell >= N ? cell - N : cell);
-    out.push_back(HostRec{cell, pos[i] & 0xFFFFFFu, a[i], w[i], photon ? n0[i] : 0, id[i]});
+  RecCtx r;
+  r.cx = make_ctx(g);
+  r.tube = tube;
+  r.n_tiles = g->n_tiles;
+  r.lep = photon ? 0 : 1;
+  r.count = g->rec_count;
+  r.total = g->counts;
+  k_rec_count<<<kGrid, TPB, 0, g->s>>>(r);
+  k_rec_scan<<<1, REC_SCAN_T, 0, g->s>>>(r);
+  long long n = 0;
+  int e = read_back(g, g->counts, sizeof(n), &n);
+  if (e) return e;
+  const size_t rs = photon ? REC_PHO : REC_LEP;
+  *need = rs * (size_t)n;
+  if (*need > buf_bytes) return GAP_OK;
+  const long long piece = (long long)(g->lep.capacity * sizeof(uint4) / REC_PHO);
+  for (long long lo = 0; lo < n; lo += piece) {
+    const long long hi = std::min(n, lo + piece);
+    k_rec_pack<<<kGrid, TPB, 0, g->s>>>(r, lo, hi, (uint2*)g->bq);
+    HIPCHK(hipMemcpyAsync((char*)host_buf + rs * (size_t)lo, g->bq, rs * (size_t)(hi - lo), hipMemcpyDeviceToHost, g->s));
   }
-  return GAP_OK;
+  HIPCHK(hipStreamSynchronize(g->s));
+  return hipGetLastError() == hipSuccess ? GAP_OK : GAP_EDEVICE;
 }
 
 int graph_capture(gap_t* g, int64_t n) {
@@ -2265,28 +2265,9 @@ int gap_diag(gap_t* g, int32_t kind, int32_t tube, void* host_buf, size_t buf_by
     }
     case GAP_DIAG_LEPTONS:
     case GAP_DIAG_PHOTONS: {
-      const bool ph = kind == GAP_DIAG_PHOTONS;
-      std::vector<HostRec> recs;
-      if ((e = export_store(g, ph ? g->pho : g->lep, ph, tube, recs))) return e;
-      const size_t rs = ph ? 32 : 24;
-      if (!fits(rs * recs.size())) return GAP_EINVAL;
-      char* o = (char*)host_buf;
-      for (const HostRec& r : recs) {
-        std::memcpy(o, &r.cell, 4);
-        std::memcpy(o + 4, &r.frac, 4);
-        std::memcpy(o + 8, &r.a, 4);
-        std::memcpy(o + 12, &r.w, 4);
-        if (ph) {
-          int32_t pad = 0;
-          std::memcpy(o + 16, &r.n0, 4);
-          std::memcpy(o + 20, &pad, 4);
-          std::memcpy(o + 24, &r.id, 8);
-        } else {
-          std::memcpy(o + 16, &r.id, 8);
-        }
-        o += rs;
-      }
-      return GAP_OK;
+      size_t n = 0;
+      if ((e = export_store(g, kind == GAP_DIAG_PHOTONS, tube, host_buf, buf_bytes, &n))) return e;
+      return fits(n) ? GAP_OK : GAP_EINVAL;
     }
     default:
       (void)need;
@@ -2416,39 +2397,33 @@ int gap_set_state(gap_t* g, int32_t kind, int32_t tube, const void* host_buf, si
       std::memcpy(&np, b + 8, 8);
       if (nl < 0 || np < 0 || bytes < 16 + (size_t)nl * 24 + (size_t)np * 32) return GAP_EINVAL;
       if (nl > g->lep.limit || np > g->pho.limit) return GAP_ECAP;
+      // every record is looked at before anything changes
+      for (int sp = 0; sp < 2; ++sp) {
+        const bool ph = sp == 1;
+        const size_t rs = ph ? REC_PHO : REC_LEP;
+        const char* r = ph ? b + 16 + nl * REC_LEP : b + 16;
+        for (int64_t i = 0; i < (ph ? np : nl); ++i, r += rs) {
+          int32_t cell; uint32_t frac; float mark;
+          std::memcpy(&cell, r, 4);
+          std::memcpy(&frac, r + 4, 4);
+          std::memcpy(&mark, r + (ph ? 8 : 12), 4);
+          if (cell < 0 || cell >= N || frac >= (1u << FRAC) || mark == 0.0f) return GAP_EINVAL;
+        }
+      }
       for (int sp = 0; sp < 2; ++sp) {
         const bool ph = sp == 1;
         Store& st = ph ? g->pho : g->lep;
         const int64_t n = ph ? np : nl;
-        const char* r = ph ? b + 16 + nl * 24 : b + 16;
-        const size_t rs = ph ? 32 : 24;
-        std::vector<uint32_t> pos(n);
-        std::vector<float> a(n), w(n);
-        std::vector<int32_t> n0(n), tt(n);
-        std::vector<uint64_t> id(n);
-        for (int64_t i = 0; i < n; ++i, r += rs) {
-          int32_t cell; uint32_t frac;
-          std::memcpy(&cell, r, 4);
-          std::memcpy(&frac, r + 4, 4);
-          std::memcpy(&a[i], r + 8, 4);
-          std::memcpy(&w[i], r + 12, 4);
-          if (ph) { std::memcpy(&n0[i], r + 16, 4); std::memcpy(&id[i], r + 24, 8); }
-          else std::memcpy(&id[i], r + 16, 8);
-          if (cell < 0 || cell >= N || frac >= (1u << FRAC)) return GAP_EINVAL;
-          if (ph ? a[i] == 0.0f : w[i] == 0.0f) return GAP_EINVAL;
-          const int tile = T.tile_first + cell / TILE;
-          tt[i] = tile;
-          pos[i] = ((uint32_t)(cell - g->tiles_h[tile].base) << FRAC) | frac;
+        const char* r = ph ? b + 16 + nl * REC_LEP : b + 16;
+        const size_t rs = ph ? REC_PHO : REC_LEP;
+        const int64_t piece = (int64_t)(g->lep.capacity * sizeof(uint4) / REC_PHO);
+        for (int64_t lo = 0; lo < n; lo += piece) {
+          const int64_t m = std::min(n - lo, piece);
+          HIPCHK(hipMemcpyAsync(g->bq, r + rs * (size_t)lo, rs * (size_t)m, hipMemcpyHostToDevice, g->s));
+          k_rec_unpack<<<(int)std::min<int64_t>(kGrid, (m + TPB - 1) / TPB), TPB, 0, g->s>>>(
+              make_ctx(g), ph ? 0 : 1, T.tile_first, (const uint2*)g->bq, lo, m);
         }
-        const int c = st.cur;
-        if (n > 0) {
-          HIPCHK(hipMemcpy(st.pos[c], pos.data(), 4 * n, hipMemcpyHostToDevice));
-          HIPCHK(hipMemcpy(st.a[c], a.data(), 4 * n, hipMemcpyHostToDevice));
-          HIPCHK(hipMemcpy(st.w[c], w.data(), 4 * n, hipMemcpyHostToDevice));
-          HIPCHK(hipMemcpy(st.id[c], id.data(), 8 * n, hipMemcpyHostToDevice));
-          if (ph) HIPCHK(hipMemcpy(st.n0[c], n0.data(), 4 * n, hipMemcpyHostToDevice));
-          HIPCHK(hipMemcpy(st.tt, tt.data(), 4 * n, hipMemcpyHostToDevice));
-        }
+        HIPCHK(hipStreamSynchronize(g->s));
         Ctl cc = read_ctl(st);
         cc.n_sorted_chunks = 0;
         cc.tail = n;

@@ -240,10 +240,10 @@ class Gap:
         return dict(d_cm=v[0], lam=v[1], rc=v[2], dt=v[3], H=v[4], w0=v[5], s_co=v[6], N=int(v[7]))
 
     def leptons(self, tube=0) -> np.ndarray:
-        return self._diag(DIAG_LEPTONS, tube, 0).view(LEPTON_DTYPE).copy()
+        return self._diag(DIAG_LEPTONS, tube, 0).view(LEPTON_DTYPE)
 
     def photons(self, tube=0) -> np.ndarray:
-        return self._diag(DIAG_PHOTONS, tube, 0).view(PHOTON_DTYPE).copy()
+        return self._diag(DIAG_PHOTONS, tube, 0).view(PHOTON_DTYPE)
 
     def protons(self, tube=0) -> np.ndarray:
         """The tube's live protons, records as the leptons' (u = gamma beta)."""
