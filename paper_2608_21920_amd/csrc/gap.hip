@@ -1235,14 +1235,19 @@ void launch_fused(gap_t* g, const Ctx& cx, bool pre, int gp, int gl, const RestG
 // The particle passes of one step on the caller's stream (pre: the prologue
 // with them).
 void enqueue_fused(gap_t* g, Ctx cx, bool pre) {
-  // Known counts: a workgroup per chunk up to the usual grids, and a store of
-  // fewer chunks than CUs in pieces of a quarter chunk.  Else, and in a graph
-  // that will be replayed on other counts, one resident round.
-  const bool known = g->rb_seen == 0 && !g->capturing;
-  const bool pieces = known && g->seen_l < g->cus && g->seen_p < g->cus;
+  // A workgroup per chunk up to the usual grids, and a store of fewer chunks
+  // than CUs in pieces of a quarter chunk.  After a re-sort the counts are a
+  // sign only, and the grids twice what they say and at least some per tile:
+  // a store may have grown since.  In a graph, which will be replayed on other
+  // counts, one resident round.  (With one round also after a re-sort the tiny
+  // gap's 500-step cascade takes 13.8 ms instead of 11.7, 200 steps of the
+  // production gap's start 6.25 instead of 5.97; with pieces up to a resident
+  // round of them the latter takes 6.35.  No result depends on it.)
+  const bool exact = g->rb_seen == 0;
+  const bool pieces = !g->capturing && g->seen_l < g->cus && g->seen_p < g->cus;
   auto grid = [&](int64_t chunks, int most) {
-    if (!known) return most;
-    const int64_t n = (pieces ? PPC : 1) * chunks;
+    if (g->capturing) return most;
+    const int64_t n = (pieces ? PPC : 1) * (exact ? chunks : 2 * std::max<int64_t>(chunks, 16 + g->n_tiles / 8));
     return (int)std::max<int64_t>(8, std::min<int64_t>((n + 7) / 8 * 8, most));
   };
   const int gl = grid(g->seen_l, lepton_grid(g)), gp = grid(g->seen_p, std::min(g->grid_pho, g->round_pho));
