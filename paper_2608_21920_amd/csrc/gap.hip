@@ -232,7 +232,7 @@ struct gap_t {
   int n_tubes = 0;
   hipStream_t s = nullptr;
   // second stream: the photon side of each step (prologue, sorted photon
-  // pass, conversion draws) runs on it beside the lepton side.  ev_l: the
+  // pass, pairs) runs on it beside the lepton side.  ev_l: the
   // caller's stream up to the start of a step; ev_pre: the prologue done;
   // ev_p: the photon side of the last enqueued step done.
   hipStream_t s2 = nullptr;
@@ -357,6 +357,8 @@ namespace {
 
 int from_hip(hipError_t e) { return e == hipSuccess ? GAP_OK : GAP_EDEVICE; }
 #define HIPCHK(x) do { hipError_t _e = (x); if (_e != hipSuccess) return GAP_EDEVICE; } while (0)
+
+size_t up256(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
 
 void* dalloc(gap_t* g, size_t bytes) {
   bytes = (bytes + 255) & ~(size_t)255;
@@ -855,7 +857,7 @@ void launch_tails(gap_t* g, const Ctx& cx, hipStream_t s) {
 
 void join_photon_side(gap_t* g);
 
-// The photon side of a window step (photon pass, conversion draws), forked
+// The photon side of a window step (photon pass, pairs), forked
 // onto the second stream once the caller's stream has done the prologue; the
 // caller joins it at the end of the step (join_photon_side), before the next
 // prologue takes the pairs it made.  The two sides touch disjoint data, as in
@@ -1221,7 +1223,7 @@ constexpr int64_t FUSED_PHO_CHUNKS = 4096;
 // taken as a sign of its size for three periods after that; a longer run
 // without such a call may have grown the store, and goes over to the general
 // form.  (No result depends on it.  With one period after it the tiny gap's
-// 500-step cascade takes 18.5 ms instead of 18.1.)
+// 500-step cascade took 2 % longer.)
 bool fused_form(const gap_t* g) {
   return !g->timing && g->seen_l >= 0 && g->seen_p >= 0 && g->seen_p <= FUSED_PHO_CHUNKS && g->rb_seen <= 3;
 }
@@ -1272,7 +1274,7 @@ void enqueue_fused(gap_t* g, Ctx cx, bool pre) {
 }
 
 // One step.  Photon side (second stream): prologue (injection, lepton tail
-// snapshot, step index), sorted photon pass, conversion draws.  Lepton side
+// snapshot, step index), sorted photon pass, pairs.  Lepton side
 // (caller's stream): sorted lepton pass, then, once the prologue is done,
 // the lepton and photon tail passes, the field update (which also takes the
 // photon tail snapshot of the next step) and the re-sort when due.  The
@@ -1604,10 +1606,16 @@ int build(gap_t* g, const gap_params* p, int n_tubes) {
   if (g->total_nodes > (1LL << 30)) return GAP_EINVAL;
 
   g->tubes = (Tube*)dalloc(g, sizeof(Tube) * n_tubes);
-  g->tiles = (Tile*)dalloc(g, sizeof(Tile) * g->n_tiles);
-  g->ltiles = (LTile*)dalloc(g, sizeof(LTile) * g->n_tiles);
-  g->ptiles = (PTile*)dalloc(g, sizeof(PTile) * g->n_tiles);
-  if (!g->ltiles || !g->ptiles) return GAP_ENOMEM;
+  // the tiles and both passes' constants of them: one allocation, one copy
+  const size_t tiles_at[4] = {0, up256(sizeof(Tile) * (size_t)g->n_tiles),
+                              up256(sizeof(Tile) * (size_t)g->n_tiles) + up256(sizeof(LTile) * (size_t)g->n_tiles),
+                              up256(sizeof(Tile) * (size_t)g->n_tiles) + up256(sizeof(LTile) * (size_t)g->n_tiles) +
+                                  up256(sizeof(PTile) * (size_t)g->n_tiles)};
+  char* tiles_d = (char*)dalloc(g, tiles_at[3]);
+  if (!tiles_d) return GAP_ENOMEM;
+  g->tiles = (Tile*)tiles_d;
+  g->ltiles = (LTile*)(tiles_d + tiles_at[1]);
+  g->ptiles = (PTile*)(tiles_d + tiles_at[2]);
   g->rho = (long long*)dalloc(g, sizeof(long long) * g->total_nodes);
   g->rho_last = (long long*)dalloc(g, sizeof(long long) * g->total_nodes);
   g->E = (float*)dalloc(g, sizeof(float) * g->total_cells);
@@ -1622,14 +1630,13 @@ int build(gap_t* g, const gap_params* p, int n_tubes) {
     if (!g->E0 || !g->Du) return GAP_ENOMEM;
   }
   g->tab = (float*)dalloc(g, sizeof(float) * 2 * (NTAB + 1));
-  g->status = (gap_t::Status*)dalloc(g, sizeof(gap_t::Status));
-  if (!g->status) return GAP_ENOMEM;
+  char* read_d = (char*)dalloc(g, up256(sizeof(gap_t::Status)) + up256(sizeof(long long) * C_N) + kStageBytes);
+  if (!read_d) return GAP_ENOMEM;
+  g->status = (gap_t::Status*)read_d;
   g->err = &g->status->err;
-  g->stage = (uint32_t*)dalloc(g, kStageBytes);
-  if (!g->stage) return GAP_ENOMEM;
+  g->counts = (long long*)(read_d + up256(sizeof(gap_t::Status)));
+  g->stage = (uint32_t*)(read_d + up256(sizeof(gap_t::Status)) + up256(sizeof(long long) * C_N));
   g->live = (long long*)dalloc(g, sizeof(long long) * 2 * n_tubes);
-  g->counts = (long long*)dalloc(g, sizeof(long long) * C_N);
-  if (!g->counts) return GAP_ENOMEM;
   g->shard = (long long*)dalloc(g, sizeof(long long) * n_tubes * NSHARD * C_N);
   if (!g->shard) return GAP_ENOMEM;
   if (!g->tubes || !g->tiles || !g->rho || !g->rho_last || !g->E || !g->ebar || !g->fb || !g->part || !g->part2 || !g->fscan ||
@@ -1640,9 +1647,9 @@ int build(gap_t* g, const gap_params* p, int n_tubes) {
   if ((e = alloc_store(g, g->pho, cap_p, true))) return e;
   g->pq_groups = 8 * g->round_pho + 64;   // the autotuner tries grids up to 4 resident rounds
   g->pq = (uint4*)dalloc(g, (size_t)g->pho.capacity * sizeof(uint4));
-  g->pq_count = (int*)dalloc(g, (size_t)g->pq_groups * 4);
-  g->pq_start = (long long*)dalloc(g, (size_t)g->pq_groups * sizeof(long long));
-  if (!g->pq || !g->pq_count || !g->pq_start) return GAP_ENOMEM;
+  g->pq_start = (long long*)dalloc(g, (size_t)g->pq_groups * (sizeof(long long) + sizeof(int)));
+  if (!g->pq || !g->pq_start) return GAP_ENOMEM;
+  g->pq_count = (int*)(g->pq_start + g->pq_groups);
   // at most one entry per slot of the sorted lepton region; a count and a
   // start per workgroup of the largest lepton grid the launch settings allow
   // (4 rounds)
@@ -1727,9 +1734,13 @@ int build(gap_t* g, const gap_params* p, int n_tubes) {
   }
   HIPCHK(hipStreamSynchronize(g->s));
   if ((e = upload_tubes(g))) return e;
-  HIPCHK(hipMemcpy(g->tiles, g->tiles_h.data(), sizeof(Tile) * g->n_tiles, hipMemcpyHostToDevice));
-  HIPCHK(hipMemcpy(g->ptiles, g->ptiles_h.data(), sizeof(PTile) * g->n_tiles, hipMemcpyHostToDevice));
-  HIPCHK(hipMemcpy(g->ltiles, g->ltiles_h.data(), sizeof(LTile) * g->n_tiles, hipMemcpyHostToDevice));
+  {
+    std::vector<char> all(tiles_at[3]);
+    std::memcpy(all.data(), g->tiles_h.data(), sizeof(Tile) * (size_t)g->n_tiles);
+    std::memcpy(all.data() + tiles_at[1], g->ltiles_h.data(), sizeof(LTile) * (size_t)g->n_tiles);
+    std::memcpy(all.data() + tiles_at[2], g->ptiles_h.data(), sizeof(PTile) * (size_t)g->n_tiles);
+    HIPCHK(hipMemcpy(g->tiles, all.data(), all.size(), hipMemcpyHostToDevice));
+  }
   HIPCHK(hipMemcpy(g->fb, g->fb_h.data(), sizeof(FBlk) * g->n_fb, hipMemcpyHostToDevice));
   const std::vector<float>& tab = sync_table();
   HIPCHK(hipMemcpy(g->tab, tab.data(), sizeof(float) * tab.size(), hipMemcpyHostToDevice));
