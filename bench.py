@@ -215,8 +215,8 @@ def measure_gap(g, torch, cfg, steps, warmup, grow_to, max_grow, graph=False, re
     for name, (byt, byt_min) in units.items():
         n, tms = tim[name]
         if name == "photons":
-            # the sorted photon pass is two launches: streaming, then the
-            # conversion draws of the photons it queued
+            # the sorted photon pass is two launches: streaming and draws,
+            # then the pairs of the photons that convert
             tms += tim["conversions"][1]
         per = tms / max(n, 1)
         kern[name] = dict(launches=n, avg_ms=per, bytes_per_launch=byt / max(n, 1),

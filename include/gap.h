@@ -180,7 +180,7 @@ int gap_sync(gap_t* g);
 #define GAP_DIAG_TIMING   8  /* double[16]: (launches, summed ms) of the lepton pass, photon
                                 pass, field, re-sort, prologue, tail passes of both
                                 species (one launch), the merge check (and merge, when due) and
-                                conversion draws since timing was enabled or last read
+                                pairs of converted photons since timing was enabled or last read
                                 (tube ignored; resets the record)                           */
 /* Discharge diagnostics (Sect. 5: Fig. 3 rows 5-7, Fig. 5, Fig. 7).  Bins are
  * GAP_STATE_PROFILE_BIN cells wide (default 64), nb = ceil(N / bin).  Groups,

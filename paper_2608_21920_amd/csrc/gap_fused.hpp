@@ -12,9 +12,10 @@
 //   k_sorted   the prologue, both sorted passes
 //   k_rest     the queued photon births and conversions' pairs, both tail
 //              passes, the protons
-// and the field update is the third: the same steps take 35 us, one step of
-// the 1024-cell gap with a read of its field and charge 92 us instead of 137,
-// and 64 steps of a 1000-cell periodic box 1.67 ms instead of 3.35.  The roles inside a launch touch
+// and the field update is the third: the same steps took 35 us then, and take
+// 25 to 30 now; one step of the 1024-cell gap with a read of its field and
+// charge 62 us instead of 137, 64 steps of a 1000-cell periodic box 1.42 ms
+// instead of 3.35.  The roles inside a launch touch
 // disjoint data for the reasons the two streams do: each pass reads its own
 // store up to a tail snapshot, births go past the snapshots, only leptons
 // and protons deposit charge, and the prologue changes the surface charge
