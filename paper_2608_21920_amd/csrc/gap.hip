@@ -743,7 +743,6 @@ bool field_pass(gap_t* g, const FieldCtx& f, hipEvent_t done = nullptr) {
     // sums before any output: two passes
     k_field_a<<<g->n_fb, FB_THREADS, 0, g->s>>>(f);
     k_field_b<<<g->n_fb, FB_THREADS, 0, g->s>>>(f);
-    k_field_periodic_ends<<<(g->n_tubes + 63) / 64, 64, 0, g->s>>>(f, g->n_tubes);
   }
   if (filt) k_filter<<<dim3((g->max_cells + FLT_CELLS - 1) / FLT_CELLS, g->n_tubes), FLT_CELLS, 0, g->s>>>(f);
   return bound;

@@ -14,7 +14,7 @@
 //              passes, the protons
 // and the field update is the third: the same steps took 35 us then, and take
 // 25 to 30 now; one step of the 1024-cell gap with a read of its field and
-// charge 62 us instead of 137, 64 steps of a 1000-cell periodic box 1.42 ms
+// charge 62 us instead of 137, 64 steps of a 1000-cell periodic box 1.34 ms
 // instead of 3.35.  The roles inside a launch touch
 // disjoint data for the reasons the two streams do: each pass reads its own
 // store up to a tail snapshot, births go past the snapshots, only leptons

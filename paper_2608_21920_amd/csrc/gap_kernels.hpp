@@ -1780,9 +1780,11 @@ __global__ __launch_bounds__(FB_THREADS) void k_field_b(FieldCtx f) {
   // carry from the tube's earlier blocks
   const long long carry = wave_range_sum(f.part, b.first_blk, (int)blockIdx.x);
   double mean = 0.0;
+  long long total = 0;   // periodic, first block: the whole tube's charge
   if (per) {
     const long long s2 = wave_range_sum(f.part2, b.first_blk, b.first_blk + b.nblk);
     mean = ((double)s2 + (double)T.bg_unit * 0.5 * (double)N * (double)N) / (double)N;
+    if (b.k0 == 0) total = wave_range_sum(f.part, b.first_blk, b.first_blk + b.nblk);
   }
   const int k = b.k0 + threadIdx.x * FB_PER;
   long long r[FB_PER];
@@ -1816,26 +1818,36 @@ __global__ __launch_bounds__(FB_THREADS) void k_field_b(FieldCtx f) {
   long long run = carry + sh[wv] + (incl - loc);   // sum of rho over cells < k
   const double Es = T.Es;
   const long long bgu = T.bg_unit;
+  // E_{j+1/2} from the charge up to node j
+  auto field = [&](long long sum, int j) {
+    const long long eint = sum + bgu * (long long)j + bgu / 2;
+    return per ? ((double)eint - mean) * T.scale + Es : (double)eint * T.scale + Es;
+  };
   // E_{k-1/2} for the node field
   double eprev;
   if (k == 0) eprev = per ? 0.0 : Es;
-  else {
-    long long eint = run + bgu * (long long)(k - 1) + bgu / 2;
-    eprev = per ? ((double)eint - mean) * T.scale + Es : (double)eint * T.scale + Es;
-  }
+  else eprev = field(run, k - 1);
 #pragma unroll
   for (int i = 0; i < FB_PER; ++i) {
     const int kk = k + i;
     if (kk >= N) break;
     run += r[i];
-    const long long eint = run + bgu * (long long)kk + bgu / 2;
-    const double e = per ? ((double)eint - mean) * T.scale + Es : (double)eint * T.scale + Es;
+    const double e = field(run, kk);
     if (!frozen) {
       if (filt && f.mode == 0) {
         f.Du[T.cell_off + kk] = e - f.E0[T.cell_off + kk];
       } else {
         f.E[T.cell_off + kk] = (float)e;
-        if (kk > 0 || !per) f.ebar[T.node_off + kk] = (float)(0.5 * (eprev + e));
+        if (kk > 0 || !per) {
+          f.ebar[T.node_off + kk] = (float)(0.5 * (eprev + e));
+        } else {
+          // periodic node 0 (= node N): the average of E_{N-1/2} and E_{1/2}
+          // as stored; the first from the whole tube's charge (a launch of
+          // its own after this one cost 1.2 of a periodic step's 22 us)
+          const float v = 0.5f * ((float)field(total, N - 1) + (float)e);
+          f.ebar[T.node_off] = v;
+          f.ebar[T.node_off + N] = v;
+        }
         if (filt) f.E0[T.cell_off + kk] = e;
       }
       if (!isfinite(e)) atomicOr(f.err, E_NAN);
@@ -2052,17 +2064,6 @@ __global__ __launch_bounds__(FB_THREADS) void k_field_1p(FieldCtx f) {
   // (the look-back is over: every block of the tube has read the epoch)
   if (threadIdx.x == 0 && (int)blockIdx.x == b.first_blk + b.nblk - 1)
     __hip_atomic_store(epoch, s_ep + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Periodic node 0 (= node N): average of E_{N-1/2} and E_{1/2}; runs after k_field_b.
-__global__ void k_field_periodic_ends(FieldCtx f, int n_tubes) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n_tubes) return;
-  Tube& T = f.tubes[t];
-  if (!(T.flags & F_PERIODIC) || (T.flags & F_FIELD_FROZEN)) return;
-  const float v = 0.5f * (f.E[T.cell_off + T.N - 1] + f.E[T.cell_off]);
-  f.ebar[T.node_off] = v;
-  f.ebar[T.node_off + T.N] = v;
 }
 
 // The digital filter of the current (Sect. 6.1), for tubes with F_FILTER,
