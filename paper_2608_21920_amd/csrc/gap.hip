@@ -271,7 +271,8 @@ struct gap_t {
   // error bits, and each store's chunk count + 1 as its last re-sort left it
   struct Status { int err, pad; long long chunks[2]; };
   Status* status = nullptr;
-  uint32_t* stage = nullptr;       // device staging of the small reads, and their host side
+  uint32_t* stage = nullptr;       // device staging of the small reads (the birth queue, which only a step
+  size_t stage_bytes = 0;          // uses), its size, and their host side
   std::vector<char> stage_h;
   // what the last such call found (chunks -1: not known), and the re-sorts
   // enqueued since
@@ -1355,7 +1356,8 @@ int sync_and_err(gap_t* g) {
 // with the status words: one kernel gathers both, so that one copy and one
 // wait do (the copies of a few bytes cost what a wait does: a step of the tiny
 // gap with a read of its field and its charge took 87 us with two waits and
-// two copies per read).  Results past the staging buffer take their own copy.
+// two copies per read).  Results past the staging buffer, for which the birth
+// queue serves, take their own copy.
 constexpr size_t kStageBytes = 4 << 20;
 constexpr size_t kStageHead = 64;
 static_assert(sizeof(gap_t::Status) <= kStageHead, "");
@@ -1367,7 +1369,7 @@ __global__ void k_gather(const uint32_t* status, const uint32_t* src, long long 
 }
 
 int read_back(gap_t* g, const void* src, size_t bytes, void* host) {
-  if (bytes + kStageHead > kStageBytes || bytes % 4 != 0) {
+  if (bytes + kStageHead > g->stage_bytes || bytes % 4 != 0) {
     const int e = sync_and_err(g);
     if (e == GAP_EDEVICE) return e;
     HIPCHK(hipMemcpy(host, src, bytes, hipMemcpyDeviceToHost));
@@ -1629,12 +1631,11 @@ int build(gap_t* g, const gap_params* p, int n_tubes) {
     if (!g->E0 || !g->Du) return GAP_ENOMEM;
   }
   g->tab = (float*)dalloc(g, sizeof(float) * 2 * (NTAB + 1));
-  char* read_d = (char*)dalloc(g, up256(sizeof(gap_t::Status)) + up256(sizeof(long long) * C_N) + kStageBytes);
+  char* read_d = (char*)dalloc(g, up256(sizeof(gap_t::Status)) + sizeof(long long) * C_N);
   if (!read_d) return GAP_ENOMEM;
   g->status = (gap_t::Status*)read_d;
   g->err = &g->status->err;
   g->counts = (long long*)(read_d + up256(sizeof(gap_t::Status)));
-  g->stage = (uint32_t*)(read_d + up256(sizeof(gap_t::Status)) + up256(sizeof(long long) * C_N));
   g->live = (long long*)dalloc(g, sizeof(long long) * 2 * n_tubes);
   g->shard = (long long*)dalloc(g, sizeof(long long) * n_tubes * NSHARD * C_N);
   if (!g->shard) return GAP_ENOMEM;
@@ -1656,6 +1657,8 @@ int build(gap_t* g, const gap_params* p, int n_tubes) {
   g->bq_count = (int*)dalloc(g, (size_t)(4 * g->round_lep + 64) * sizeof(int));
   g->bq_start = (long long*)dalloc(g, (size_t)(4 * g->round_lep + 64) * sizeof(long long));
   if (!g->bq || !g->bq_count || !g->bq_start) return GAP_ENOMEM;
+  g->stage = (uint32_t*)g->bq;
+  g->stage_bytes = std::min(kStageBytes, (size_t)g->lep.capacity * sizeof(uint4));
   if (g->any_protons) {
     const size_t n = (size_t)g->pr_cap;
     for (int b = 0; b < 2; ++b) {
