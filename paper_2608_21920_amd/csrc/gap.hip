@@ -271,7 +271,7 @@ struct gap_t {
   // error bits, and each store's chunk count + 1 as its last re-sort left it
   struct Status { int err, pad; long long chunks[2]; };
   Status* status = nullptr;
-  uint32_t* stage = nullptr;       // device staging of the small reads (the birth queue, which only a step
+  uint32_t* stage = nullptr;       // device staging of the small reads (the conversion queue, which only a step
   size_t stage_bytes = 0;          // uses), its size, and their host side
   std::vector<char> stage_h;
   // what the last such call found (chunks -1: not known), and the re-sorts
@@ -1356,8 +1356,9 @@ int sync_and_err(gap_t* g) {
 // with the status words: one kernel gathers both, so that one copy and one
 // wait do (the copies of a few bytes cost what a wait does: a step of the tiny
 // gap with a read of its field and its charge took 87 us with two waits and
-// two copies per read).  Results past the staging buffer, for which the birth
-// queue serves, take their own copy.
+// two copies per read).  Results past the staging buffer, for which the
+// conversion queue serves (every call joins the photon side before it
+// returns), take their own copy.
 constexpr size_t kStageBytes = 4 << 20;
 constexpr size_t kStageHead = 64;
 static_assert(sizeof(gap_t::Status) <= kStageHead, "");
@@ -1650,6 +1651,8 @@ int build(gap_t* g, const gap_params* p, int n_tubes) {
   g->pq_start = (long long*)dalloc(g, (size_t)g->pq_groups * (sizeof(long long) + sizeof(int)));
   if (!g->pq || !g->pq_start) return GAP_ENOMEM;
   g->pq_count = (int*)(g->pq_start + g->pq_groups);
+  g->stage = (uint32_t*)g->pq;
+  g->stage_bytes = std::min(kStageBytes, (size_t)g->pho.capacity * sizeof(uint4));
   // at most one entry per slot of the sorted lepton region; a count and a
   // start per workgroup of the largest lepton grid the launch settings allow
   // (4 rounds)
@@ -1657,8 +1660,6 @@ int build(gap_t* g, const gap_params* p, int n_tubes) {
   g->bq_count = (int*)dalloc(g, (size_t)(4 * g->round_lep + 64) * sizeof(int));
   g->bq_start = (long long*)dalloc(g, (size_t)(4 * g->round_lep + 64) * sizeof(long long));
   if (!g->bq || !g->bq_count || !g->bq_start) return GAP_ENOMEM;
-  g->stage = (uint32_t*)g->bq;
-  g->stage_bytes = std::min(kStageBytes, (size_t)g->lep.capacity * sizeof(uint4));
   if (g->any_protons) {
     const size_t n = (size_t)g->pr_cap;
     for (int b = 0; b < 2; ++b) {
