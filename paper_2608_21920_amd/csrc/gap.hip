@@ -1679,21 +1679,9 @@ int build(gap_t* g, const gap_params* p, int n_tubes) {
   for (int t = 0; t < n_tubes; ++t) max_n = std::max(max_n, p[t].n_cells);
   g->ret = (double*)dalloc(g, sizeof(double) * RET_N * (size_t)n_tubes);
   g->ret_thr = (double*)dalloc(g, sizeof(double) * RET_NB);
-  if (g->ret_thr) {
-    // bin b: gamma in [10^(b/8), 10^((b+1)/8)), i.e. u^2 = gamma^2 - 1 from 10^(b/4) - 1
-    std::vector<double> thr(RET_NB);
-    for (int b = 0; b < RET_NB; ++b) thr[b] = std::pow(10.0, b / 4.0) - 1.0;
-    HIPCHK(hipMemcpy(g->ret_thr, thr.data(), sizeof(double) * RET_NB, hipMemcpyHostToDevice));
-  }
   g->spec_thr = (double*)dalloc(g, sizeof(double) * SPEC_EDGES);
   g->spec_acc = (double*)dalloc(g, sizeof(double) * 3 * SPEC_NB);
-  if (!g->spec_thr || !g->spec_acc) return GAP_ENOMEM;
-  {
-    // edge b at 10^(-2 + b/8) in |u| or |x|, compared as squares
-    std::vector<double> thr(SPEC_EDGES);
-    for (int b = 0; b < SPEC_EDGES; ++b) thr[b] = std::pow(10.0, 2.0 * (-2.0 + b / 8.0));
-    HIPCHK(hipMemcpy(g->spec_thr, thr.data(), sizeof(double) * SPEC_EDGES, hipMemcpyHostToDevice));
-  }
+  if (!g->ret_thr || !g->spec_thr || !g->spec_acc) return GAP_ENOMEM;
   g->prof_acc = (double*)dalloc(g, sizeof(double) * PROF_G * PROF_M * (size_t)max_n);
   g->prof_out = (double*)dalloc(g, sizeof(double) * PROF_G * 3 * (size_t)max_n);
   if (!g->ret || !g->prof_acc || !g->prof_out) return GAP_ENOMEM;
@@ -1735,8 +1723,22 @@ int build(gap_t* g, const gap_params* p, int n_tubes) {
     HIPCHK(hipMemcpy(g->thresh_l, tl.data(), sizeof(double) * n_tubes, hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(g->thresh_p, tp.data(), sizeof(double) * n_tubes, hipMemcpyHostToDevice));
   }
+  // (every buffer is cleared by a fill on the caller's stream, which a plain
+  // copy does not wait for when that stream is a non-blocking one)
   HIPCHK(hipStreamSynchronize(g->s));
   if ((e = upload_tubes(g))) return e;
+  {
+    // return spectrum, bin b: gamma in [10^(b/8), 10^((b+1)/8)), i.e. u^2 = gamma^2 - 1 from 10^(b/4) - 1
+    std::vector<double> thr(RET_NB);
+    for (int b = 0; b < RET_NB; ++b) thr[b] = std::pow(10.0, b / 4.0) - 1.0;
+    HIPCHK(hipMemcpy(g->ret_thr, thr.data(), sizeof(double) * RET_NB, hipMemcpyHostToDevice));
+  }
+  {
+    // momentum spectra, edge b at 10^(-2 + b/8) in |u| or |x|, compared as squares
+    std::vector<double> thr(SPEC_EDGES);
+    for (int b = 0; b < SPEC_EDGES; ++b) thr[b] = std::pow(10.0, 2.0 * (-2.0 + b / 8.0));
+    HIPCHK(hipMemcpy(g->spec_thr, thr.data(), sizeof(double) * SPEC_EDGES, hipMemcpyHostToDevice));
+  }
   {
     std::vector<char> all(tiles_at[3]);
     std::memcpy(all.data(), g->tiles_h.data(), sizeof(Tile) * (size_t)g->n_tiles);

@@ -1,0 +1,80 @@
+"""What libgap's host code asks of the HIP runtime, without a GPU: the library's
+host side linked with a stand-in for the runtime (``host_harness/launches.cpp``)
+that records launches, allocations and host copies.  No kernel runs."""
+import ctypes as C
+import os
+import subprocess
+
+import pytest
+
+from paper_2608_21920_amd import gap as G
+from paper_2608_21920_amd import workloads
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HERE = os.path.join(ROOT, "tests", "host_harness")
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+CLANG = "/opt/rocm/llvm/bin/clang++"
+
+pytestmark = pytest.mark.skipif(not (os.path.exists(HIPCC) and os.path.exists(CLANG) and os.path.exists(HERE)),
+                                reason="no ROCm toolchain, or no host harness")
+
+
+class Host:
+    """The C ABI of a host-only build, with the recorder's questions."""
+
+    def __init__(self, path):
+        self.lib = lib = C.CDLL(path)
+        for n, res, args in (("rec_stream", C.c_void_p, []), ("rec_count", C.c_longlong, []),
+                             ("rec_name", C.c_char_p, [C.c_longlong]), ("rec_grid", C.c_longlong, [C.c_longlong]),
+                             ("rec_allocs", C.c_longlong, []), ("rec_races", C.c_longlong, []),
+                             ("rec_race", C.c_char_p, [C.c_longlong]),
+                             ("rec_set_chunks", None, [C.c_longlong, C.c_longlong])):
+            getattr(lib, n).restype, getattr(lib, n).argtypes = res, args
+        lib.gap_init.argtypes = [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.POINTER(C.c_void_p)]
+        lib.gap_step.argtypes = lib.gap_step_graph.argtypes = [C.c_void_p, C.c_int64]
+        lib.gap_sync.argtypes = lib.gap_free.argtypes = [C.c_void_p]
+        lib.gap_diag.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_void_p, C.c_size_t, C.POINTER(C.c_size_t)]
+        lib.gap_set_state.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_void_p, C.c_size_t]
+        lib.gap_autotune.argtypes = [C.c_void_p, C.c_int32, C.c_void_p]
+        self.stream = lib.rec_stream()
+
+    def init(self, *cfgs):
+        p = (G.GapParams * len(cfgs))(*[G.make_params(c) for c in cfgs])
+        h = C.c_void_p()
+        assert self.lib.gap_init(p, len(cfgs), self.stream, None, C.byref(h)) == 0
+        return h
+
+    def launches(self):
+        """[(kernel, workgroups)] since the last call."""
+        out = [(self.lib.rec_name(i).decode(), self.lib.rec_grid(i)) for i in range(self.lib.rec_count())]
+        self.lib.rec_clear()
+        return out
+
+    def races(self):
+        return [self.lib.rec_race(i).decode() for i in range(self.lib.rec_races())]
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    d = str(tmp_path_factory.mktemp("host"))
+    obj, so = os.path.join(d, "gap.o"), os.path.join(d, "libgap_host.so")
+    subprocess.run([HIPCC, "-c", "--cuda-host-only", "--offload-arch=gfx950", "-O1", "-std=c++17", "-fPIC",
+                    "-I" + os.path.join(ROOT, "include"), os.path.join(ROOT, "paper_2608_21920_amd", "csrc", "gap.hip"),
+                    "-o", obj], check=True, capture_output=True)
+    # (there is no device code: the symbol it would have stays without a value)
+    und = subprocess.run(["nm", "-u", obj], check=True, capture_output=True, text=True).stdout
+    fat = [w for w in und.split() if w.startswith("__hip_fatbin")]
+    subprocess.run([CLANG, "-shared", "-fPIC", "-O1", "-std=c++17", "-Wno-unused-value", "-D__HIP_PLATFORM_AMD__",
+                    "-I/opt/rocm/include", os.path.join(HERE, "launches.cpp"), obj, "-o", so, "-Wl,-Bsymbolic"]
+                   + ["-Wl,--defsym=%s=0" % s for s in fat], check=True, capture_output=True)
+    return Host(so)
+
+
+def test_no_host_copy_runs_ahead_of_queued_fills(host):
+    # a handle on a non-blocking stream, every kind of initial state and table
+    for cfg in (workloads.TINY, dict(workloads.PAPER, n_cells=300, cap_leptons=1 << 16, cap_photons=1 << 16),
+                dict(workloads.PRODUCTION, n_cells=300, cap_leptons=1 << 16, cap_photons=1 << 16)):
+        h = host.init(dict(cfg, cap_leptons=1 << 16, cap_photons=1 << 16))
+        assert host.lib.gap_step(h, 3) == 0
+        host.lib.gap_free(h)
+    assert host.races() == []
