@@ -85,7 +85,17 @@ __device__ __forceinline__ long long* shard_at(long long* sh, int tube, int idx)
   return sh + ((long long)tube * NSHARD + (blockIdx.x % NSHARD)) * C_N + idx;
 }
 
-__device__ __forceinline__ int wrap_cell(int c, int N) { return c < 0 ? c + N : (c >= N ? c - N : c); }
+// A periodic tube's cell (or node) from its place in a tile's window: one turn,
+// or several in a tube shorter than the 64 cells that a particle can leave it
+// by between re-sorts.
+__host__ __device__ __forceinline__ int wrap_cell(int c, int N) {
+  c = c < 0 ? c + N : (c >= N ? c - N : c);
+  if ((unsigned)c >= (unsigned)N) {
+    c %= N;
+    if (c < 0) c += N;
+  }
+  return c;
+}
 
 // Add `v` to counter `idx` of the tube `t` of each lane (t < 0: no-op), one
 // atomic per distinct tube in the wave.
