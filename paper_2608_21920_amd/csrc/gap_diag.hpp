@@ -385,14 +385,18 @@ __global__ void k_fft_power(const double2* X, int M, double* P) {
 constexpr int SPEC_EDGES = 89;
 constexpr int SPEC_NB = SPEC_EDGES + 1;
 
-// (A guess from the FP32 logarithm, off by at most one bin, settled by the
-// exact comparisons with its two edges.)
+// Edges at or below |p| by its FP32 logarithm, at least one: edge b is at
+// log2 |p| = (b - 16) log2(10) / 8.  (Clamped before the conversion: an
+// infinite |p| has every edge below it.)
+__host__ __device__ __forceinline__ int spec_guess(float log2p) {
+  return (int)fminf(fmaxf(floorf(log2p * (8.0f * 0.30102999566398120f)) + 17.0f, 1.0f), (float)SPEC_EDGES);
+}
+// (The guess is off by at most one bin, settled by the exact comparisons with
+// its two edges.)
 __device__ __forceinline__ int spec_bin(const double* thr, float p) {
   const double p2 = (double)p * (double)p;
   if (!(p2 >= thr[0])) return 0;
-  // edges at log2 |p| = (b - 16) log2(10) / 8
-  const int c = (int)floorf(__log2f(fabsf(p)) * (8.0f * 0.30102999566398120f)) + 17;
-  int n = min(max(c, 1), SPEC_EDGES);
+  int n = spec_guess(__log2f(fabsf(p)));
   if (n < SPEC_EDGES && thr[n] <= p2) ++n;
   else if (thr[n - 1] > p2) --n;
   return n;

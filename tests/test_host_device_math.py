@@ -39,3 +39,19 @@ def test_wrap_cell_of_boxes_shorter_than_the_margin(math):
     for n in list(range(2, 70)) + [127, 128, 129, 255, 1000]:
         for c in range(-64, n + 256):
             assert f(c, n) == c % n, (c, n)
+
+
+def test_spectrum_bin_guess(math):
+    # the momentum spectra's first guess is the true count of edges or one
+    # beside it, and every edge lies below an infinite momentum
+    f = C.CDLL(math).dm_spec_guess
+    f.argtypes = [C.c_float]
+    thr = np.array([10.0 ** (2.0 * (-2.0 + b / 8.0)) for b in range(89)])
+    edges = np.sqrt(thr).astype(np.float32)
+    p = np.concatenate([edges, np.nextafter(edges, np.float32(0)), np.nextafter(edges, np.float32(np.inf)),
+                        np.geomspace(1e-2, 3.4e38, 20000).astype(np.float32)])
+    p = p[p.astype(np.float64) ** 2 >= thr[0]]
+    want = np.searchsorted(thr, p.astype(np.float64) ** 2, side="right")
+    got = np.array([f(float(x)) for x in np.log2(p)])
+    assert np.abs(got - want).max() <= 1 and got.min() >= 1 and got.max() == 89
+    assert f(float("inf")) == 89 and f(-float("inf")) == 1
