@@ -1385,8 +1385,9 @@ int read_back(gap_t* g, const void* src, size_t bytes, void* host) {
   if (hipGetLastError() != hipSuccess) return GAP_EDEVICE;
   gap_t::Status st;
   std::memcpy(&st, g->stage_h.data(), sizeof(st));
+  if (take_status(g, st) == GAP_EDEVICE) return GAP_EDEVICE;
   std::memcpy(host, g->stage_h.data() + kStageHead, bytes);
-  return take_status(g, st) == GAP_EDEVICE ? GAP_EDEVICE : GAP_OK;
+  return GAP_OK;
 }
 
 Ctl read_ctl(const Store& st) {
@@ -2095,9 +2096,11 @@ int gap_diag(gap_t* g, int32_t kind, int32_t tube, void* host_buf, size_t buf_by
     if (bytes_written) *bytes_written = n;
     return n <= buf_bytes;
   };
+  // a read that is refused waits and takes notice of errors like any other
+  auto refused = [&]() { return sync_and_err(g) == GAP_EDEVICE ? GAP_EDEVICE : GAP_EINVAL; };
   switch (kind) {
     case GAP_DIAG_COUNTS: {
-      if (!fits(sizeof(int64_t) * 32)) return GAP_EINVAL;
+      if (!fits(sizeof(int64_t) * 32)) return refused();
       k_fill_i64<<<1, 256, 0, g->s>>>(g->live, 2 * g->n_tubes, 0);
       k_count_live<LepBuf><<<kGrid, TPB, 0, g->s>>>(g->lep.lep(g->lep.cur), g->lep.ctl, g->lep.chunk[g->lep.cur], g->lep.tt,
                                                   g->tiles, g->live, g->n_tubes);
@@ -2110,23 +2113,23 @@ int gap_diag(gap_t* g, int32_t kind, int32_t tube, void* host_buf, size_t buf_by
       return GAP_OK;
     }
     case GAP_DIAG_FIELD:
-      if (!fits(sizeof(float) * N)) return GAP_EINVAL;
+      if (!fits(sizeof(float) * N)) return refused();
       return read_back(g, g->E + Th.cell_off, sizeof(float) * N, host_buf);
     case GAP_DIAG_NODE_E:
-      if (!fits(sizeof(float) * (N + 1))) return GAP_EINVAL;
+      if (!fits(sizeof(float) * (N + 1))) return refused();
       return read_back(g, g->ebar + Th.node_off, sizeof(float) * (N + 1), host_buf);
     case GAP_DIAG_RHO:
-      if (!fits(sizeof(int64_t) * (N + 1))) return GAP_EINVAL;
+      if (!fits(sizeof(int64_t) * (N + 1))) return refused();
       return read_back(g, g->rho_last + Th.node_off, sizeof(int64_t) * (N + 1), host_buf);
     case GAP_DIAG_ES:
-      if (!fits(sizeof(double))) return GAP_EINVAL;
+      if (!fits(sizeof(double))) return refused();
       return read_back(g, &g->tubes[tube].Es, sizeof(double), host_buf);
     case GAP_DIAG_PROFILE:
     case GAP_DIAG_PEAK: {
       const int B = g->prof_bin;
       const int nb = (N + B - 1) / B;
       if (kind == GAP_DIAG_PROFILE ? !fits(sizeof(double) * 3 * PROF_G * (size_t)nb) : !fits(sizeof(double) * 6))
-        return GAP_EINVAL;
+        return refused();
       const long long nacc = (long long)nb * PROF_G * PROF_M;
       k_fill_i64<<<std::max(1, (int)std::min<long long>(1024, (nacc + 255) / 256)), 256, 0, g->s>>>(
           (long long*)g->prof_acc, nacc, 0);
@@ -2183,7 +2186,7 @@ int gap_diag(gap_t* g, int32_t kind, int32_t tube, void* host_buf, size_t buf_by
       const int B = g->prof_bin;
       const int nb = (N + B - 1) / B;
       const size_t n = (size_t)3 * nb * PHASE_NP;
-      if (!fits(sizeof(double) * n)) return GAP_EINVAL;
+      if (!fits(sizeof(double) * n)) return refused();
       if (g->phase_cap < n) {
         g->phase_acc = (double*)dalloc(g, sizeof(double) * n);   // kept until the handle ends
         if (!g->phase_acc) return GAP_ENOMEM;
@@ -2198,7 +2201,7 @@ int gap_diag(gap_t* g, int32_t kind, int32_t tube, void* host_buf, size_t buf_by
       return g->sticky;
     }
     case GAP_DIAG_SPECTRA: {
-      if (!fits(sizeof(double) * 3 * SPEC_NB)) return GAP_EINVAL;
+      if (!fits(sizeof(double) * 3 * SPEC_NB)) return refused();
       k_fill_i64<<<1, 256, 0, g->s>>>((long long*)g->spec_acc, 3 * SPEC_NB, 0);
       k_spectra<<<kDiagGrid, TPB, 0, g->s>>>(make_ctx(g), tube, g->spec_thr, g->spec_acc);
       if ((e = read_back(g, g->spec_acc, sizeof(double) * 3 * SPEC_NB, host_buf))) return e;
@@ -2208,7 +2211,7 @@ int gap_diag(gap_t* g, int32_t kind, int32_t tube, void* host_buf, size_t buf_by
       // double[M/2 + 1], M the next power of two >= N
       int M = 1;
       while (M < N) M *= 2;
-      if (!fits(sizeof(double) * (size_t)(M / 2 + 1))) return GAP_EINVAL;
+      if (!fits(sizeof(double) * (size_t)(M / 2 + 1))) return refused();
       if (!g->fft_buf) {
         int Mmax = 1;
         while (Mmax < g->max_cells) Mmax *= 2;
@@ -2292,7 +2295,7 @@ int gap_diag(gap_t* g, int32_t kind, int32_t tube, void* host_buf, size_t buf_by
     }
     default:
       (void)need;
-      return GAP_EINVAL;
+      return refused();
   }
 }
 

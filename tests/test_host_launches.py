@@ -78,3 +78,37 @@ def test_no_host_copy_runs_ahead_of_queued_fills(host):
         assert host.lib.gap_step(h, 3) == 0
         host.lib.gap_free(h)
     assert host.races() == []
+
+
+def _diag(host, h, kind, n):
+    buf, wr = (C.c_char * max(n, 1))(), C.c_size_t(0)
+    return host.lib.gap_diag(h, kind, 0, buf, n, C.byref(wr)), wr.value, bytes(buf)[:n]
+
+
+@pytest.mark.parametrize("kind", [G.DIAG_COUNTS, G.DIAG_FIELD, G.DIAG_ES, G.DIAG_RHO, G.DIAG_NODE_E, G.DIAG_PROFILE,
+                                  G.DIAG_PEAK, G.DIAG_SPECTRA, G.DIAG_PHASE, G.DIAG_ESPECTRUM, G.DIAG_DERIVED,
+                                  G.DIAG_RETURN, G.DIAG_LEPTONS, G.DIAG_PROTONS, 99])
+def test_a_refused_read_takes_notice_of_device_errors(host, kind):
+    # a read that is refused (short buffer, unknown kind) waits like any
+    # other: a device error comes before the refusal, and any other error
+    # stops the run
+    cfg = dict(workloads.TINY, n_cells=300, cap_leptons=1 << 14, cap_photons=1 << 14)
+    for bits, want, after in ((8, -6, -6), (4, -1, -5), (0, -1, 0)):
+        h = host.init(cfg)
+        assert host.lib.gap_set_state(h, G.STATE_RAISE, 0, C.byref(C.c_int32(bits)), 4) == 0
+        code, need, _ = _diag(host, h, kind, 1)
+        if kind in (G.DIAG_LEPTONS, G.DIAG_PROTONS) and want == -1:
+            assert code == 0 and need == 0       # (an empty store is not refused)
+        else:
+            assert code == want
+        assert host.lib.gap_step(h, 1) == after
+        host.lib.gap_free(h)
+
+
+def test_a_read_that_fails_leaves_the_buffer_alone(host):
+    h = host.init(dict(workloads.TINY, n_cells=300, cap_leptons=1 << 14, cap_photons=1 << 14))
+    assert host.lib.gap_set_state(h, G.STATE_RAISE, 0, C.byref(C.c_int32(8)), 4) == 0
+    buf, wr = (C.c_char * 1200)(*(b"x" * 1200)), C.c_size_t(0)
+    assert host.lib.gap_diag(h, G.DIAG_FIELD, 0, buf, 1200, C.byref(wr)) == -6
+    assert bytes(buf) == b"x" * 1200
+    host.lib.gap_free(h)
