@@ -307,7 +307,6 @@ struct gap_t {
   // results for the largest tube at one cell per bin
   double* ret = nullptr;
   double* ret_thr = nullptr;           // [RET_NB]: lower bin edges in u^2
-  int64_t* rec_count = nullptr;        // record counts of the export's blocks, allocated on first use
   double* prof_acc = nullptr;
   double* prof_out = nullptr;
   int prof_bin = 64;                   // cells per profile bin
@@ -1851,19 +1850,16 @@ double2* fft(gap_t* g, const float* E, int N, int M, double2* x, double2* y) {
 
 // The live records of tube `tube` into host_buf in slot order (*need: their
 // bytes; nothing is copied when they do not fit).  The pieces are packed in
-// the birth queue, which only a step uses.
+// the birth queue, which only a step uses, and the blocks' record counts (8 B
+// per 1024 slots) stand in the store's classes (1 B per slot), which only a
+// re-sort uses: a read allocates nothing.
 int export_store(gap_t* g, bool photon, int tube, void* host_buf, size_t buf_bytes, size_t* need) {
-  const int64_t slots = std::max(g->lep.capacity, g->pho.capacity);
-  if (!g->rec_count) {
-    g->rec_count = (int64_t*)dalloc(g, sizeof(int64_t) * (size_t)(slots / REC_BLOCK + 2));   // kept until the handle ends
-    if (!g->rec_count) return GAP_ENOMEM;
-  }
   RecCtx r;
   r.cx = make_ctx(g);
   r.tube = tube;
   r.n_tiles = g->n_tiles;
   r.lep = photon ? 0 : 1;
-  r.count = g->rec_count;
+  r.count = (int64_t*)(photon ? g->pho : g->lep).cls;
   r.total = g->counts;
   k_rec_count<<<kGrid, TPB, 0, g->s>>>(r);
   k_rec_scan<<<1, REC_SCAN_T, 0, g->s>>>(r);

@@ -112,3 +112,14 @@ def test_a_read_that_fails_leaves_the_buffer_alone(host):
     assert host.lib.gap_diag(h, G.DIAG_FIELD, 0, buf, 1200, C.byref(wr)) == -6
     assert bytes(buf) == b"x" * 1200
     host.lib.gap_free(h)
+
+
+def test_reading_particles_allocates_nothing(host):
+    # (callers whose allocator is closed once a handle stands)
+    cfg = dict(workloads.TINY, n_cells=300, cap_leptons=1 << 14, cap_photons=1 << 10)
+    h = host.init(cfg)
+    before = host.lib.rec_allocs()
+    assert _diag(host, h, G.DIAG_LEPTONS, 0)[0] == 0
+    assert _diag(host, h, G.DIAG_PHOTONS, 0)[0] == 0
+    assert host.lib.rec_allocs() == before
+    host.lib.gap_free(h)
