@@ -275,7 +275,7 @@ struct gap_t {
   size_t stage_bytes = 0;          // uses), its size, and their host side
   std::vector<char> stage_h;
   // what the last such call found (chunks -1: not known), and the re-sorts
-  // enqueued since
+  // enqueued since, by steps or within replayed graphs
   int64_t seen_l = -1, seen_p = -1;
   int rb_seen = 0;
   float* tab = nullptr;
@@ -349,6 +349,7 @@ struct gap_t {
   hipGraphExec_t gexec = nullptr;
   int64_t gsteps = -1;
   bool graph_fused = false;   // the captured steps take the fused form
+  int graph_rb = 0;           // re-sorts among them
   int gs_l = -1, gs_p = -1, ge_l = -1, ge_p = -1, gs_r = -1, ge_r = -1;
   int64_t gs_since = -1, ge_since = -1, gs_step = -1;
 };
@@ -712,6 +713,9 @@ void join_stores(gap_t* g, hipStream_t ps) {
   (void)hipStreamWaitEvent(g->s, g->ev_j, 0);
 }
 
+// (the count stops far above the few that matter)
+void count_resorts(gap_t* g, int n) { g->rb_seen = std::min(g->rb_seen + n, 1 << 20); }
+
 void rebucket_all(gap_t* g) {
   join_photon_side(g);
   rebucket_clear(g, g->pho);
@@ -725,7 +729,7 @@ void rebucket_all(gap_t* g) {
     g->pr_cur ^= 1;
   }
   join_stores(g, ps);
-  g->rb_seen = std::min(g->rb_seen + 1, 1 << 20);
+  count_resorts(g, 1);
 }
 
 // With `done`, the single-pass kernel's own completion is recorded into that
@@ -1883,15 +1887,19 @@ int graph_capture(gap_t* g, int64_t n) {
   drop_graph(g);
   g->graph_fused = fused_form(g);
   g->gs_l = g->lep.cur; g->gs_p = g->pho.cur; g->gs_r = g->pr_cur; g->gs_since = g->since_rb; g->gs_step = g->host_step;
+  const int rb_seen = g->rb_seen;
   hipGraph_t graph = nullptr;
   HIPCHK(hipStreamBeginCapture(g->s, hipStreamCaptureModeThreadLocal));
+  g->rb_seen = 0;
   g->capturing = true;
   for (int64_t i = 0; i < n; ++i) enqueue_step(g, i + 1 < n);
   g->capturing = false;
   hipError_t e = hipStreamEndCapture(g->s, &graph);
   g->ge_l = g->lep.cur; g->ge_p = g->pho.cur; g->ge_r = g->pr_cur; g->ge_since = g->since_rb;
+  g->graph_rb = g->rb_seen;
   // nothing ran yet: back to the start state
   g->lep.cur = g->gs_l; g->pho.cur = g->gs_p; g->pr_cur = g->gs_r; g->since_rb = g->gs_since; g->host_step = g->gs_step;
+  g->rb_seen = rb_seen;
   if (e != hipSuccess) return GAP_EDEVICE;
   e = hipGraphInstantiate(&g->gexec, graph, nullptr, nullptr, 0);
   (void)hipGraphDestroy(graph);
@@ -2067,6 +2075,7 @@ int gap_step_graph(gap_t* g, int64_t n_steps) {
   HIPCHK(hipGraphLaunch(g->gexec, g->s));
   g->lep.cur = g->ge_l; g->pho.cur = g->ge_p; g->pr_cur = g->ge_r; g->since_rb = g->ge_since;
   g->host_step += n_steps;
+  count_resorts(g, g->graph_rb);
   return g->sticky;
 }
 

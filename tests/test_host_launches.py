@@ -123,3 +123,67 @@ def test_reading_particles_allocates_nothing(host):
     assert _diag(host, h, G.DIAG_PHOTONS, 0)[0] == 0
     assert host.lib.rec_allocs() == before
     host.lib.gap_free(h)
+
+
+def _chunky(host, lep, pho, **more):
+    """A handle whose stores had `lep` and `pho` chunks at the last read."""
+    h = host.init(dict(workloads.TINY, cap_leptons=1 << 16, cap_photons=1 << 16, **more))
+    host.lib.rec_set_chunks(lep, pho)
+    assert host.lib.gap_sync(h) == 0
+    host.launches()
+    return h
+
+
+def _kernels(host, names=("k_sorted", "k_rest", "k_leptons", "k_photons", "k_tails", "k_pre")):
+    """The particle kernels launched since the last call: (name, workgroups)."""
+    return [(k, g) for n, g in host.launches() for k in names if k in n]
+
+
+GENERAL = {"k_leptons", "k_photons", "k_tails", "k_pre"}
+FUSED = {"k_sorted", "k_rest"}
+
+
+def test_graph_replays_count_their_resorts(host):
+    # 1024 cells are 8 tiles.  400 and 100 chunks: after a read a workgroup per
+    # chunk (and 8 before them); once stores were re-sorted twice that many
+    h = _chunky(host, 400, 100, rebucket_every=20)
+    exact, loose = 8 + 400 + 104, 8 + 800 + 200
+    step = lambda n: host.lib.gap_step(h, n)
+    graph = lambda n: host.lib.gap_step_graph(h, n)
+    assert step(1) == 0
+    assert dict(_kernels(host))["k_sorted"] == exact
+    assert step(19) == 0                           # the 20th step re-sorts
+    host.launches()
+    assert step(1) == 0
+    assert dict(_kernels(host))["k_sorted"] == loose
+    assert step(19) == 0
+    # a replay of two re-sorts (capture and first replay in one call)
+    assert graph(40) == 0
+    assert host.lib.gap_sync(h) == 0
+    host.launches()
+    assert graph(40) == 0                          # a replay alone
+    assert _kernels(host) == []
+    assert step(1) == 0
+    assert dict(_kernels(host))["k_sorted"] == loose
+    assert step(19) == 0
+    # three re-sorts since the last read: still the fused form; four: the general one
+    assert host.lib.gap_sync(h) == 0
+    assert step(20) == 0
+    assert graph(40) == 0
+    host.launches()
+    assert step(1) == 0
+    assert dict(_kernels(host))["k_sorted"] == loose
+    assert step(19) == 0
+    host.launches()
+    assert step(1) == 0
+    assert {k for k, _ in _kernels(host)} == GENERAL
+    host.lib.gap_free(h)
+
+
+def test_a_capture_and_its_replay_count_once(host):
+    h = _chunky(host, 400, 100, rebucket_every=20)
+    assert host.lib.gap_step_graph(h, 60) == 0     # three re-sorts, as many as the fused form is taken after
+    host.launches()
+    assert host.lib.gap_step(h, 1) == 0
+    assert {k for k, _ in _kernels(host)} == FUSED
+    host.lib.gap_free(h)
