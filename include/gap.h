@@ -181,7 +181,10 @@ int gap_sync(gap_t* g);
                                 pass, field, re-sort, prologue, tail passes of both
                                 species (one launch), the merge check (and merge, when due) and
                                 pairs of converted photons since timing was enabled or last read
-                                (tube ignored; resets the record)                           */
+                                (tube ignored; resets the record).  While timing is on, each of
+                                these passes is a launch of its own; otherwise a handle with few
+                                photons takes several of them in one launch, which is faster:
+                                the times are the passes', not parts of such a step's         */
 /* Discharge diagnostics (Sect. 5: Fig. 3 rows 5-7, Fig. 5, Fig. 7).  Bins are
  * GAP_STATE_PROFILE_BIN cells wide (default 64), nb = ceil(N / bin).  Groups,
  * in order: electrons moving up (u > 0), electrons moving down, positrons up,
@@ -274,7 +277,10 @@ int gap_diag(gap_t* g, int32_t kind, int32_t tube, void* host_buf, size_t buf_by
 #define GAP_STATE_FIELD     2  /* float E[N] then double E_s (for GAP_FIELD_FROZEN runs)       */
 #define GAP_STATE_INJECTION 3  /* double accumulator, then uint64 injected count              */
 #define GAP_STATE_TIMING    4  /* int32 on/off: HIP-event timing of each kernel group of
-                                  eager gap_step calls (not of graph replays)                  */
+                                  eager gap_step calls (not of graph replays).  On: steps (and
+                                  graphs captured from then on) launch every particle pass by
+                                  itself, also on handles that otherwise take several in one
+                                  launch.  Changes no result                                  */
 #define GAP_STATE_DRIVE     5  /* double alpha, then double inj_weight: the imposed current
                                   j_m = alpha j_co (Sect. 2.2) and the weight of one injected
                                   electron from the next step on; ends a pending window        */
@@ -323,8 +329,10 @@ int gap_set_state(gap_t* g, int32_t kind, int32_t tube, const void* host_buf, si
  * range mapping) and over the re-sort interval (up to the longest the tile
  * margin allows), each candidate timed with HIP events over `trial_steps`
  * real steps of the simulation (at least two re-sorts for the interval).
- * The steps are part of the run: every result is independent of the launch
- * shape and of the re-sort interval.  chosen (host int32[4]) receives the
+ * The candidates are timed in the form of the step that the handle takes at
+ * the time (one launch per pass, or several passes in one where photons are
+ * few and timing is off).  The steps are part of the run: every result is
+ * independent of the launch shape and of the re-sort interval.  chosen (host int32[4]) receives the
  * lepton, photon and tail workgroup counts and the interval, which the
  * handle keeps.  Discards a captured graph.  Blocks until done. */
 int gap_autotune(gap_t* g, int32_t trial_steps, int32_t* chosen);

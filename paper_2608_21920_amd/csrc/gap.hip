@@ -286,8 +286,10 @@ struct gap_t {
   long long* counts = nullptr;   // one tube's counters, gathered for the host
   long long* shard = nullptr;   // [tube][NSHARD][C_N] event counters
   Store lep, pho;
-  // per-kernel event timing (eager steps only)
+  // per-kernel event timing (eager steps only), and, for one that the caller
+  // asked for, the particle passes in launches of their own whatever the form
   bool timing = false;
+  bool apart = false;
   std::vector<hipEvent_t> ev_pool;
   size_t ev_used = 0;
   std::vector<std::pair<int, std::pair<hipEvent_t, hipEvent_t>>> ev_marks;   // (kernel id, start, stop)
@@ -1228,7 +1230,7 @@ constexpr int64_t FUSED_PHO_CHUNKS = 4096;
 // form.  (No result depends on it.  With one period after it the tiny gap's
 // 500-step cascade took 2 % longer.)
 bool fused_form(const gap_t* g) {
-  return !g->timing && g->seen_l >= 0 && g->seen_p >= 0 && g->seen_p <= FUSED_PHO_CHUNKS && g->rb_seen <= 3;
+  return !g->apart && g->seen_l >= 0 && g->seen_p >= 0 && g->seen_p <= FUSED_PHO_CHUNKS && g->rb_seen <= 3;
 }
 
 template <bool Q, bool A, int V>
@@ -1911,7 +1913,8 @@ int graph_capture(gap_t* g, int64_t n) {
 // ------------------------------------------------------------------ autotuner
 // Launch shapes and the re-sort interval change no result (the deposit is in
 // integers and every particle's arithmetic is independent of the grid and of
-// its slot), so candidates are timed on real steps of the simulation.
+// its slot), so candidates are timed on real steps of the simulation, in the
+// form that the handle's steps take.
 int timed_steps(gap_t* g, int64_t n, double* kt, double* wall_ms) {
   g->ev_marks.clear();
   g->ev_used = 0;
@@ -2310,7 +2313,7 @@ int gap_set_state(gap_t* g, int32_t kind, int32_t tube, const void* host_buf, si
     if (bytes < 4) return GAP_EINVAL;
     int32_t on;
     std::memcpy(&on, host_buf, 4);
-    g->timing = on != 0;
+    g->timing = g->apart = on != 0;
     g->ev_marks.clear();
     g->ev_used = 0;
     return GAP_OK;

@@ -187,3 +187,23 @@ def test_a_capture_and_its_replay_count_once(host):
     assert host.lib.gap_step(h, 1) == 0
     assert {k for k, _ in _kernels(host)} == FUSED
     host.lib.gap_free(h)
+
+
+@pytest.mark.parametrize("pho,form", [(100, FUSED), (5000, GENERAL)])
+def test_autotune_times_the_form_that_steps_take(host, pho, form):
+    h = _chunky(host, 400, pho)
+    chosen = (C.c_int32 * 4)()
+    assert host.lib.gap_autotune(h, 4, chosen) == 0
+    assert {k for k, _ in _kernels(host)} == form
+    assert host.lib.gap_step(h, 2) == 0
+    assert {k for k, _ in _kernels(host)} == form
+    host.lib.gap_free(h)
+
+
+def test_a_timed_handle_launches_each_pass_alone(host):
+    h = _chunky(host, 400, 100)
+    for on, form in ((1, GENERAL), (0, FUSED)):
+        assert host.lib.gap_set_state(h, G.STATE_TIMING, 0, C.byref(C.c_int32(on)), 4) == 0
+        assert host.lib.gap_step(h, 2) == 0
+        assert {k for k, _ in _kernels(host)} == form
+    host.lib.gap_free(h)
