@@ -222,7 +222,11 @@ int gap_sync(gap_t* g);
                                   proton initial state)                                  */
 #define GAP_DIAG_LAUNCH  16    /* int32[4]: the handle's launch shape, as GAP_STATE_LAUNCH sets it
                                   (workgroups of the sorted lepton pass, of the sorted photon
-                                  pass and of the tail passes, re-sort interval; tube ignored) */
+                                  pass and of the tail passes, re-sort interval; tube ignored).
+                                  Until a lepton grid is set or tuned the handle takes one by
+                                  the store's size, and this is its present choice.  Steps that
+                                  take several passes in one launch use no more workgroups than
+                                  these, and fewer for small stores                        */
 #define GAP_DIAG_ESPECTRUM 13  /* double[M/2 + 1], M the next power of two >= N: the power
                                   spectrum of E along the gap, P_k = |sum_j E_j
                                   exp(-2 pi i j k / M)|^2 / M with E zero-padded to M cells

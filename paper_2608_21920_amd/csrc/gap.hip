@@ -2250,7 +2250,7 @@ int gap_diag(gap_t* g, int32_t kind, int32_t tube, void* host_buf, size_t buf_by
     }
     case GAP_DIAG_LAUNCH: {
       if (!fits(sizeof(int32_t) * 4)) return GAP_EINVAL;
-      const int32_t v[4] = {g->grid_lep, g->grid_pho, g->grid_tail, g->R};
+      const int32_t v[4] = {lepton_grid(g), g->grid_pho, g->grid_tail, g->R};
       std::memcpy(host_buf, v, sizeof(v));
       return GAP_OK;
     }

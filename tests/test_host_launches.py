@@ -207,3 +207,20 @@ def test_a_timed_handle_launches_each_pass_alone(host):
         assert host.lib.gap_step(h, 2) == 0
         assert {k for k, _ in _kernels(host)} == form
     host.lib.gap_free(h)
+
+
+@pytest.mark.parametrize("lep", [100, 12287, 12288, 40000])
+def test_the_launch_shape_read_is_the_one_launched(host, lep):
+    # (a store of eight chunks per workgroup of a resident round takes two rounds)
+    h = _chunky(host, lep, 5000)
+    v, wr = (C.c_int32 * 4)(), C.c_size_t(0)
+    assert host.lib.gap_diag(h, G.DIAG_LAUNCH, 0, v, 16, C.byref(wr)) == 0
+    host.launches()
+    assert host.lib.gap_step(h, 1) == 0
+    ran = dict(_kernels(host))
+    assert ran["k_leptons"] == v[0] and ran["k_photons"] == v[1]
+    # written back, it is what the handle goes on with
+    assert host.lib.gap_set_state(h, G.STATE_LAUNCH, 0, v, 16) == 0
+    assert host.lib.gap_step(h, 1) == 0
+    assert dict(_kernels(host)) == ran
+    host.lib.gap_free(h)
