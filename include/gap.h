@@ -227,6 +227,10 @@ int gap_sync(gap_t* g);
                                   the store's size, and this is its present choice.  Steps that
                                   take several passes in one launch use no more workgroups than
                                   these, and fewer for small stores                        */
+#define GAP_DIAG_FORM    18    /* int32[1]: how the last step enqueued launched its particle passes
+                                  (tube ignored): 0 one launch per pass, the photon side on the
+                                  second stream; 1 two launches (stores with few photons); 2 the
+                                  same in smaller pieces (few particles).  No result depends on it */
 #define GAP_DIAG_ESPECTRUM 13  /* double[M/2 + 1], M the next power of two >= N: the power
                                   spectrum of E along the gap, P_k = |sum_j E_j
                                   exp(-2 pi i j k / M)|^2 / M with E zero-padded to M cells

@@ -352,6 +352,8 @@ struct gap_t {
   int64_t gsteps = -1;
   bool graph_fused = false;   // the captured steps take the fused form
   int graph_rb = 0;           // re-sorts among them
+  int graph_form = 0;         // their form, as GAP_DIAG_FORM gives it
+  int form = 0;               // the last enqueued step's
   int gs_l = -1, gs_p = -1, ge_l = -1, ge_p = -1, gs_r = -1, ge_r = -1;
   int64_t gs_since = -1, ge_since = -1, gs_step = -1;
 };
@@ -890,6 +892,7 @@ void window_passes(gap_t* g, const Ctx& cx) {
     enqueue_fused(g, cx, false);
     return;
   }
+  g->form = 0;
   fork_photon_side(g, cx);
   launch_leptons(g, cx, g->s);
   launch_tails(g, cx, g->s);
@@ -1188,6 +1191,7 @@ void join_photon_side(gap_t* g) {
 // The particle passes of a step in their general form: on two streams, or
 // (two == false) on the caller's.
 void enqueue_passes(gap_t* g, bool two, bool merged) {
+  g->form = 0;
   Ctx cx = make_ctx(g);
   hipStream_t ps = g->s;
   if (two) {
@@ -1252,6 +1256,7 @@ void enqueue_fused(gap_t* g, Ctx cx, bool pre) {
   // round of them the latter takes 6.35.  No result depends on it.)
   const bool exact = g->rb_seen == 0;
   const bool pieces = !g->capturing && g->seen_l < g->cus && g->seen_p < g->cus;
+  g->form = pieces ? 2 : 1;
   auto grid = [&](int64_t chunks, int most) {
     if (g->capturing) return most;
     const int64_t n = (pieces ? PPC : 1) * (exact ? chunks : 2 * std::max<int64_t>(chunks, 16 + g->n_tiles / 8));
@@ -1899,6 +1904,7 @@ int graph_capture(gap_t* g, int64_t n) {
   hipError_t e = hipStreamEndCapture(g->s, &graph);
   g->ge_l = g->lep.cur; g->ge_p = g->pho.cur; g->ge_r = g->pr_cur; g->ge_since = g->since_rb;
   g->graph_rb = g->rb_seen;
+  g->graph_form = g->form;
   // nothing ran yet: back to the start state
   g->lep.cur = g->gs_l; g->pho.cur = g->gs_p; g->pr_cur = g->gs_r; g->since_rb = g->gs_since; g->host_step = g->gs_step;
   g->rb_seen = rb_seen;
@@ -2079,6 +2085,7 @@ int gap_step_graph(gap_t* g, int64_t n_steps) {
   g->lep.cur = g->ge_l; g->pho.cur = g->ge_p; g->pr_cur = g->ge_r; g->since_rb = g->ge_since;
   g->host_step += n_steps;
   count_resorts(g, g->graph_rb);
+  g->form = g->graph_form;
   return g->sticky;
 }
 
@@ -2092,7 +2099,8 @@ int gap_diag(gap_t* g, int32_t kind, int32_t tube, void* host_buf, size_t buf_by
   int e = GAP_OK;
   // (the other kinds wait where they read)
   if (kind == GAP_DIAG_LEPTONS || kind == GAP_DIAG_PHOTONS || kind == GAP_DIAG_PROTONS || kind == GAP_DIAG_RETURN ||
-      kind == GAP_DIAG_WATERFALL || kind == GAP_DIAG_TIMING || kind == GAP_DIAG_LAUNCH || kind == GAP_DIAG_DERIVED) {
+      kind == GAP_DIAG_WATERFALL || kind == GAP_DIAG_TIMING || kind == GAP_DIAG_LAUNCH ||
+      kind == GAP_DIAG_FORM || kind == GAP_DIAG_DERIVED) {
     e = sync_and_err(g);
     if (e == GAP_EDEVICE) return e;
   }
@@ -2252,6 +2260,12 @@ int gap_diag(gap_t* g, int32_t kind, int32_t tube, void* host_buf, size_t buf_by
       if (!fits(sizeof(int32_t) * 4)) return GAP_EINVAL;
       const int32_t v[4] = {lepton_grid(g), g->grid_pho, g->grid_tail, g->R};
       std::memcpy(host_buf, v, sizeof(v));
+      return GAP_OK;
+    }
+    case GAP_DIAG_FORM: {
+      if (!fits(sizeof(int32_t))) return GAP_EINVAL;
+      const int32_t v = g->form;
+      std::memcpy(host_buf, &v, sizeof(v));
       return GAP_OK;
     }
     case GAP_DIAG_DERIVED: {

@@ -26,7 +26,7 @@ ERRORS = {0: "GAP_OK", -1: "GAP_EINVAL", -2: "GAP_ENOMEM", -3: "GAP_ECAP", -4: "
 
 (DIAG_COUNTS, DIAG_FIELD, DIAG_ES, DIAG_RHO, DIAG_LEPTONS, DIAG_PHOTONS, DIAG_NODE_E, DIAG_DERIVED, DIAG_TIMING,
  DIAG_PROFILE, DIAG_PEAK, DIAG_RETURN, DIAG_WATERFALL, DIAG_ESPECTRUM, DIAG_SPECTRA, DIAG_PHASE, DIAG_LAUNCH,
- DIAG_PROTONS) = range(18)
+ DIAG_PROTONS, DIAG_FORM) = range(19)
 (STATE_PARTICLES, STATE_ES_STEP, STATE_FIELD, STATE_INJECTION, STATE_TIMING, STATE_DRIVE, STATE_LAUNCH,
  STATE_PROFILE_BIN, STATE_WATERFALL, STATE_RAISE, STATE_PROTONS, STATE_ATMOSPHERE) = range(12)
 INIT_GAP, INIT_UNIFORM, INIT_EMPTY, INIT_ELECTRON, INIT_ATMOSPHERE = range(5)
@@ -380,6 +380,11 @@ class Gap:
         """The launch shape and re-sort interval in use."""
         v = self._diag(DIAG_LAUNCH, 0, 16).view(np.int32)
         return dict(grid_leptons=int(v[0]), grid_photons=int(v[1]), grid_tails=int(v[2]), resort_every=int(v[3]))
+
+    def step_form(self) -> int:
+        """How the last step launched its particle passes: 0 one launch per
+        pass, 1 two launches (few photons), 2 two in smaller pieces."""
+        return int(self._diag(DIAG_FORM, 0, 4).view(np.int32)[0])
 
     def autotune(self, trial_steps: int = 32) -> dict:
         """Tune the launch shapes and the re-sort interval on real steps

@@ -224,3 +224,17 @@ def test_the_launch_shape_read_is_the_one_launched(host, lep):
     assert host.lib.gap_step(h, 1) == 0
     assert dict(_kernels(host)) == ran
     host.lib.gap_free(h)
+
+
+@pytest.mark.parametrize("lep,pho,form", [(0, 0, 2), (255, 255, 2), (256, 0, 1), (0, 256, 1), (100000, 4096, 1),
+                                          (0, 4097, 0), (-1, 0, 0)])
+def test_the_form_of_a_step_by_the_sizes_last_read(host, lep, pho, form):
+    h = _chunky(host, lep, pho)
+    got = lambda: C.c_int32.from_buffer_copy(_diag(host, h, G.DIAG_FORM, 4)[2]).value
+    assert host.lib.gap_step(h, 1) == 0
+    assert got() == form
+    assert {k for k, _ in _kernels(host)} == (FUSED if form else GENERAL)
+    # captured steps take no smaller pieces: they are replayed on other counts
+    assert host.lib.gap_step_graph(h, 1) == 0
+    assert got() == min(form, 1)
+    host.lib.gap_free(h)
