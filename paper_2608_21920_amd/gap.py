@@ -167,9 +167,20 @@ class Gap:
             alloc_p = None
             if use_torch_alloc:
                 dev = self.device
+                own = self.stream.cuda_stream
+
+                # A block may be that of a freed tensor which the current stream
+                # is still working on: a handle on another stream waits for it
+                # (once for all of its creation's blocks).
+                def _wait():
+                    cur = torch.cuda.current_stream(dev)
+                    if cur.cuda_stream != own:
+                        torch.cuda.ExternalStream(own, device=dev).wait_stream(cur)
 
                 def _alloc(nbytes, ctx):
                     t = torch.empty(int(nbytes), dtype=torch.uint8, device=dev)
+                    if self.h:
+                        _wait()
                     self._bufs[t.data_ptr()] = t
                     return t.data_ptr()
 
@@ -178,6 +189,9 @@ class Gap:
                 self._cb = GapAllocator(GapAllocator._fields_[0][1](_alloc), GapAllocator._fields_[1][1](_free), None)
                 alloc_p = C.byref(self._cb)
             h = C.c_void_p()
+            self.h = None
+            if use_torch_alloc:
+                _wait()
             code = lib.gap_init(arr, self.n_tubes, C.c_void_p(self.stream.cuda_stream), alloc_p, C.byref(h))
             _check(code, "gap_init")
             self.h = h

@@ -30,3 +30,30 @@ def test_side_stream_equals_default_stream(torch_alloc):
         else:
             assert np.array_equal(a, b)
     assert out[0][3][64] > 0
+
+
+def test_memory_that_another_stream_still_writes():
+    # the handle's memory comes from tensors freed with a write still queued on
+    # the default stream, behind 0.2 s of other work
+    import torch
+    print("case: reused memory", flush=True)
+    cfg = dict(workloads.TINY, seed=3, cap_leptons=1 << 22, cap_photons=1 << 22)
+    want = Gap(cfg)
+    want.step(20)
+    s = torch.cuda.Stream()
+    torch.cuda.empty_cache()          # (no other block to take)
+    x = torch.empty(1 << 30, dtype=torch.uint8, device="cuda")
+    lo = x.data_ptr()
+    torch.cuda.synchronize()
+    torch.cuda._sleep(400_000_000)
+    x.fill_(255)
+    del x
+    g = Gap(cfg, stream=s)
+    reused = sum(1 for p in g._bufs if lo <= p < lo + (1 << 30))
+    g.step(20)
+    torch.cuda.synchronize()
+    assert reused > 10, reused
+    assert np.array_equal(g.field(), want.field()) and np.array_equal(g.rho(), want.rho())
+    assert g.counts() == want.counts()
+    g.close()
+    want.close()
