@@ -1619,16 +1619,19 @@ int build(gap_t* g, const gap_params* p, int n_tubes) {
   if (g->total_nodes > (1LL << 30)) return GAP_EINVAL;
 
   g->tubes = (Tube*)dalloc(g, sizeof(Tube) * n_tubes);
-  // the tiles and both passes' constants of them: one allocation, one copy
-  const size_t tiles_at[4] = {0, up256(sizeof(Tile) * (size_t)g->n_tiles),
-                              up256(sizeof(Tile) * (size_t)g->n_tiles) + up256(sizeof(LTile) * (size_t)g->n_tiles),
-                              up256(sizeof(Tile) * (size_t)g->n_tiles) + up256(sizeof(LTile) * (size_t)g->n_tiles) +
-                                  up256(sizeof(PTile) * (size_t)g->n_tiles)};
-  char* tiles_d = (char*)dalloc(g, tiles_at[3]);
+  // the tiles, both passes' constants of them and the edges of the spectra's
+  // bins: one allocation, one copy
+  const size_t part_bytes[5] = {sizeof(Tile) * (size_t)g->n_tiles, sizeof(LTile) * (size_t)g->n_tiles,
+                                sizeof(PTile) * (size_t)g->n_tiles, sizeof(double) * RET_NB, sizeof(double) * SPEC_EDGES};
+  size_t part_at[6] = {0};
+  for (int i = 0; i < 5; ++i) part_at[i + 1] = part_at[i] + up256(part_bytes[i]);
+  char* tiles_d = (char*)dalloc(g, part_at[5]);
   if (!tiles_d) return GAP_ENOMEM;
   g->tiles = (Tile*)tiles_d;
-  g->ltiles = (LTile*)(tiles_d + tiles_at[1]);
-  g->ptiles = (PTile*)(tiles_d + tiles_at[2]);
+  g->ltiles = (LTile*)(tiles_d + part_at[1]);
+  g->ptiles = (PTile*)(tiles_d + part_at[2]);
+  g->ret_thr = (double*)(tiles_d + part_at[3]);
+  g->spec_thr = (double*)(tiles_d + part_at[4]);
   g->rho = (long long*)dalloc(g, sizeof(long long) * g->total_nodes);
   g->rho_last = (long long*)dalloc(g, sizeof(long long) * g->total_nodes);
   g->E = (float*)dalloc(g, sizeof(float) * g->total_cells);
@@ -1689,10 +1692,8 @@ int build(gap_t* g, const gap_params* p, int n_tubes) {
   int max_n = 1;
   for (int t = 0; t < n_tubes; ++t) max_n = std::max(max_n, p[t].n_cells);
   g->ret = (double*)dalloc(g, sizeof(double) * RET_N * (size_t)n_tubes);
-  g->ret_thr = (double*)dalloc(g, sizeof(double) * RET_NB);
-  g->spec_thr = (double*)dalloc(g, sizeof(double) * SPEC_EDGES);
   g->spec_acc = (double*)dalloc(g, sizeof(double) * 3 * SPEC_NB);
-  if (!g->ret_thr || !g->spec_thr || !g->spec_acc) return GAP_ENOMEM;
+  if (!g->spec_acc) return GAP_ENOMEM;
   g->prof_acc = (double*)dalloc(g, sizeof(double) * PROF_G * PROF_M * (size_t)max_n);
   g->prof_out = (double*)dalloc(g, sizeof(double) * PROF_G * 3 * (size_t)max_n);
   if (!g->ret || !g->prof_acc || !g->prof_out) return GAP_ENOMEM;
@@ -1739,22 +1740,14 @@ int build(gap_t* g, const gap_params* p, int n_tubes) {
   HIPCHK(hipStreamSynchronize(g->s));
   if ((e = upload_tubes(g))) return e;
   {
-    // return spectrum, bin b: gamma in [10^(b/8), 10^((b+1)/8)), i.e. u^2 = gamma^2 - 1 from 10^(b/4) - 1
-    std::vector<double> thr(RET_NB);
-    for (int b = 0; b < RET_NB; ++b) thr[b] = std::pow(10.0, b / 4.0) - 1.0;
-    HIPCHK(hipMemcpy(g->ret_thr, thr.data(), sizeof(double) * RET_NB, hipMemcpyHostToDevice));
-  }
-  {
+    // return spectrum, bin b: gamma in [10^(b/8), 10^((b+1)/8)), i.e. u^2 = gamma^2 - 1 from 10^(b/4) - 1;
     // momentum spectra, edge b at 10^(-2 + b/8) in |u| or |x|, compared as squares
-    std::vector<double> thr(SPEC_EDGES);
-    for (int b = 0; b < SPEC_EDGES; ++b) thr[b] = std::pow(10.0, 2.0 * (-2.0 + b / 8.0));
-    HIPCHK(hipMemcpy(g->spec_thr, thr.data(), sizeof(double) * SPEC_EDGES, hipMemcpyHostToDevice));
-  }
-  {
-    std::vector<char> all(tiles_at[3]);
-    std::memcpy(all.data(), g->tiles_h.data(), sizeof(Tile) * (size_t)g->n_tiles);
-    std::memcpy(all.data() + tiles_at[1], g->ltiles_h.data(), sizeof(LTile) * (size_t)g->n_tiles);
-    std::memcpy(all.data() + tiles_at[2], g->ptiles_h.data(), sizeof(PTile) * (size_t)g->n_tiles);
+    double ret_thr[RET_NB], spec_thr[SPEC_EDGES];
+    for (int b = 0; b < RET_NB; ++b) ret_thr[b] = std::pow(10.0, b / 4.0) - 1.0;
+    for (int b = 0; b < SPEC_EDGES; ++b) spec_thr[b] = std::pow(10.0, 2.0 * (-2.0 + b / 8.0));
+    const void* const part[5] = {g->tiles_h.data(), g->ltiles_h.data(), g->ptiles_h.data(), ret_thr, spec_thr};
+    std::vector<char> all(part_at[5]);
+    for (int i = 0; i < 5; ++i) std::memcpy(all.data() + part_at[i], part[i], part_bytes[i]);
     HIPCHK(hipMemcpy(g->tiles, all.data(), all.size(), hipMemcpyHostToDevice));
   }
   HIPCHK(hipMemcpy(g->fb, g->fb_h.data(), sizeof(FBlk) * g->n_fb, hipMemcpyHostToDevice));
