@@ -438,7 +438,7 @@ void drop_graph(gap_t* g) {
 
 void release(gap_t* g) {
   drop_graph(g);
-  if (g->s) (void)hipStreamSynchronize(g->s);
+  (void)hipStreamSynchronize(g->s);   // (also the default stream: an allocator may reuse a block at once)
   if (g->s2) { (void)hipStreamSynchronize(g->s2); (void)hipStreamDestroy(g->s2); g->s2 = nullptr; }
   for (hipEvent_t* e : {&g->ev_l, &g->ev_pre, &g->ev_p, &g->ev_f, &g->ev_j})
     if (*e) { (void)hipEventDestroy(*e); *e = nullptr; }
@@ -816,7 +816,7 @@ void* walloc(gap_t* g, size_t bytes) {
 }
 
 void win_release(gap_t* g) {
-  if (!g->win.mem.empty() && g->s) (void)hipStreamSynchronize(g->s);
+  if (!g->win.mem.empty()) (void)hipStreamSynchronize(g->s);
   for (void* p : g->win.mem) {
     if (g->custom_alloc) g->al.free(p, g->al.ctx);
     else (void)hipFree(p);

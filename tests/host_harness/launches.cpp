@@ -43,6 +43,7 @@ std::map<const void*, std::string>& names() {
 std::vector<Launch> g_launches;
 std::map<hipStream_t, std::vector<Fill>> g_fills;   // enqueued on non-blocking streams, not waited for
 std::vector<std::string> g_races;
+std::map<hipStream_t, long long> g_queued;          // launches since the stream was last waited for
 long long g_allocs = 0;
 long long* g_status = nullptr;                      // the library's status words: {error, chunks + 1 of both stores}
 
@@ -84,11 +85,13 @@ void __hipRegisterFunction(void** m, const void* host, char* dev, const char* na
 }
 hipError_t hipLaunchKernel(const void* f, dim3 g, dim3 b, void** a, size_t sh, hipStream_t s) {
   record(f, g, a);
+  ++g_queued[s];
   return stub_launch_kernel(f, g, b, a, sh, s);
 }
 hipError_t hipExtLaunchKernel(const void* f, dim3 g, dim3 b, void** a, size_t sh, hipStream_t s, hipEvent_t start,
                               hipEvent_t stop, int fl) {
   record(f, g, a);
+  ++g_queued[s];
   return stub_ext_launch_kernel(f, g, b, a, sh, s, start, stop, fl);
 }
 hipError_t hipMalloc(void** p, size_t n) {
@@ -107,6 +110,7 @@ hipError_t hipMemsetAsync(void* p, int v, size_t n, hipStream_t s) {
 }
 hipError_t hipStreamSynchronize(hipStream_t s) {
   g_fills.erase(s);
+  g_queued.erase(s);
   return stub_stream_synchronize(s);
 }
 
@@ -120,6 +124,11 @@ void rec_clear(void) { g_launches.clear(); }
 long long rec_count(void) { return (long long)g_launches.size(); }
 const char* rec_name(long long i) { return g_launches[(size_t)i].name.c_str(); }
 long long rec_grid(long long i) { return g_launches[(size_t)i].grid; }
+long long rec_queued(void) {
+  long long n = 0;
+  for (auto& q : g_queued) n += q.second;
+  return n;
+}
 long long rec_allocs(void) { return g_allocs; }
 long long rec_races(void) { return (long long)g_races.size(); }
 const char* rec_race(long long i) { return g_races[(size_t)i].c_str(); }

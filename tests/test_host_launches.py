@@ -26,7 +26,7 @@ class Host:
         self.lib = lib = C.CDLL(path)
         for n, res, args in (("rec_stream", C.c_void_p, []), ("rec_count", C.c_longlong, []),
                              ("rec_name", C.c_char_p, [C.c_longlong]), ("rec_grid", C.c_longlong, [C.c_longlong]),
-                             ("rec_allocs", C.c_longlong, []), ("rec_races", C.c_longlong, []),
+                             ("rec_allocs", C.c_longlong, []), ("rec_queued", C.c_longlong, []), ("rec_races", C.c_longlong, []),
                              ("rec_race", C.c_char_p, [C.c_longlong]),
                              ("rec_set_chunks", None, [C.c_longlong, C.c_longlong])):
             getattr(lib, n).restype, getattr(lib, n).argtypes = res, args
@@ -238,3 +238,28 @@ def test_the_form_of_a_step_by_the_sizes_last_read(host, lep, pho, form):
     assert host.lib.gap_step_graph(h, 1) == 0
     assert got() == min(form, 1)
     host.lib.gap_free(h)
+
+
+@pytest.mark.parametrize("own_stream", [True, False])
+def test_memory_is_given_back_after_the_work_that_uses_it(host, own_stream):
+    # (an allocator may hand a block out again at once)
+    hip = host.lib
+    hip.hipMalloc.argtypes, hip.hipFree.argtypes = [C.POINTER(C.c_void_p), C.c_size_t], [C.c_void_p]
+    left = []
+
+    def alloc(n, ctx):
+        p = C.c_void_p()
+        assert hip.hipMalloc(C.byref(p), n) == 0
+        return p.value
+
+    def free(p, ctx):
+        left.append(hip.rec_queued())
+        hip.hipFree(p)
+    al = G.GapAllocator(G.GapAllocator._fields_[0][1](alloc), G.GapAllocator._fields_[1][1](free), None)
+    p = G.make_params(dict(workloads.TINY, cap_leptons=1 << 16, cap_photons=1 << 16, n_cells=300))
+    h = C.c_void_p()
+    assert hip.gap_init(C.byref(p), 1, host.stream if own_stream else None, C.byref(al), C.byref(h)) == 0
+    assert hip.gap_step(h, 3) == 0
+    assert hip.rec_queued() > 0
+    hip.gap_free(h)
+    assert left and set(left) == {0}
