@@ -46,15 +46,12 @@ PEAK_HBM_GBS = 8000.0
 # sources of every kernel a step launches (the counter summary is keyed by them)
 KERNEL_SOURCES = ("gap_device.hpp", "gap_kernels.hpp", "gap_merge.hpp")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_step_production.txt")
-# algorithmic bytes per unit of work: a lepton-step reads position, momentum
-# and weight and writes position and momentum (20 B); a lepton-step that
-# evaluates emission also reads the 8-byte id.  A photon-step reads position,
-# energy, weight, birth step and id and writes position (28 B).
-B_LEP, B_EMIT_EVAL, B_PHO = 20, 8, 28
-# bytes the photon kernel must move at least: position, energy and birth step
-# read and position written for every photon (16 B); id and weight only for
-# the photons that draw a conversion (12 B)
-B_PHO_MIN, B_CONV_EVAL_MIN = 16, 12
+# algorithmic bytes per unit of work, those that have to move: a lepton-step
+# reads position, momentum and weight and writes position and momentum (20 B);
+# one that evaluates emission also reads the 8-byte id.  A photon-step reads
+# position and energy and writes position (12 B); one that draws a conversion
+# also reads birth step and id (12 B).
+B_LEP, B_EMIT_EVAL, B_PHO, B_DRAW = 20, 8, 12, 12
 # the reverse pass of the differentiable window: per lepton-step it reads the
 # taped position and momentum of both ends and the three adjoints and writes
 # the adjoints back (48 B)
@@ -166,7 +163,8 @@ def _window(g, torch, steps, timing=False, graph=False, region=None):
 
 
 def _alg_bytes(d):
-    return B_LEP * d["lep_steps"] + B_EMIT_EVAL * d["n_emit_eval"] + B_PHO * d["pho_steps"]
+    return (B_LEP * d["lep_steps"] + B_EMIT_EVAL * d["n_emit_eval"] + B_PHO * d["pho_steps"]
+            + B_DRAW * d["n_conv_eval"])
 
 
 def measure_gap(g, torch, cfg, steps, warmup, grow_to, max_grow, graph=False, region=None, kernels=True):
@@ -205,14 +203,13 @@ def measure_gap(g, torch, cfg, steps, warmup, grow_to, max_grow, graph=False, re
     # the same number of steps with an event pair around every kernel group
     ms_i, di, tim, _ = _window(g, torch, steps, timing=True)
     lep_b = lambda n_steps, n_eval: B_LEP * n_steps + B_EMIT_EVAL * n_eval
-    pho_b = lambda n_steps, n_eval: B_PHO * n_steps
-    pho_min = lambda n_steps, n_eval: B_PHO_MIN * n_steps + B_CONV_EVAL_MIN * n_eval
+    pho_b = lambda n_steps, n_eval: B_PHO * n_steps + B_DRAW * n_eval
     lt, pt = (di["lep_steps_tail"], di["emit_eval_tail"]), (di["pho_steps_tail"], di["conv_eval_tail"])
-    units = dict(leptons=(lep_b(di["lep_steps"] - lt[0], di["n_emit_eval"] - lt[1]),) * 2,
-                 photons=(pho_b(di["pho_steps"] - pt[0], 0), pho_min(di["pho_steps"] - pt[0], di["n_conv_eval"] - pt[1])),
-                 tails=(lep_b(*lt) + pho_b(*pt), lep_b(*lt) + pho_min(*pt)))
+    units = dict(leptons=lep_b(di["lep_steps"] - lt[0], di["n_emit_eval"] - lt[1]),
+                 photons=pho_b(di["pho_steps"] - pt[0], di["n_conv_eval"] - pt[1]),
+                 tails=lep_b(*lt) + pho_b(*pt))
     kern = {}
-    for name, (byt, byt_min) in units.items():
+    for name, byt in units.items():
         n, tms = tim[name]
         if name == "photons":
             # the sorted photon pass is two launches: streaming and draws,
@@ -220,8 +217,7 @@ def measure_gap(g, torch, cfg, steps, warmup, grow_to, max_grow, graph=False, re
             tms += tim["conversions"][1]
         per = tms / max(n, 1)
         kern[name] = dict(launches=n, avg_ms=per, bytes_per_launch=byt / max(n, 1),
-                          gbs=(byt / max(n, 1)) / (per / 1e3) / 1e9 if tms > 0 else None,
-                          min_bytes_per_launch=byt_min / max(n, 1))
+                          gbs=(byt / max(n, 1)) / (per / 1e3) / 1e9 if tms > 0 else None)
     kern["conversions"] = dict(launches=tim["conversions"][0], avg_ms=tim["conversions"][1] / max(tim["conversions"][0], 1))
     for k in ("field", "prologue"):
         kern[k] = dict(launches=tim[k][0], avg_ms=tim[k][1] / max(tim[k][0], 1))
@@ -444,7 +440,8 @@ def bench_batched(torch, plain_value, cfgs, label, ignite_steps=0, n_tubes=256, 
     a, b = (c0, c1) if graph else (c1, c2)
     ms = ms_graph if graph else ms_eager
     ps = ps_g if graph else ps_e
-    alg = B_LEP * (b["lep"] - a["lep"]) + B_EMIT_EVAL * (b["emit"] - a["emit"]) + B_PHO * (b["pho"] - a["pho"])
+    alg = (B_LEP * (b["lep"] - a["lep"]) + B_EMIT_EVAL * (b["emit"] - a["emit"]) + B_PHO * (b["pho"] - a["pho"])
+           + B_DRAW * (b["conv"] - a["conv"]))
     value = ps / (ms / 1e3)
     return dict(value=value, unit="particle-steps/s", tubes=n_tubes, steps=n, ms_per_step=ms / n,
                 ms_per_step_graph=ms_graph / n, ms_per_step_eager=ms_eager / n, graph=graph, autotune=tune,

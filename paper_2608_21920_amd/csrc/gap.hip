@@ -524,8 +524,9 @@ void atm_reset(Tube& T) {
 // Workgroups of the sorted lepton pass: those set or tuned, else one resident
 // round, or two for a store of at least eight chunks per workgroup of it, as
 // last seen (a pass is then long enough that a second, later-starting round
-// evens out its end: 136 steps of 3.8e7 leptons in 64 tubes 41.0 ms with two
-// and 43.1 with one, the production gap's 8.4e6 20.3 and 18.6).
+// evens out its end.  A step with two rounds and with one: 26 chunks per
+// workgroup, 64 tubes, 221 and 228 us; 13, 108 and 111; 10, 82.0 and 83.3; 6,
+// 62.9 and 61.4; the production gap at 5.5, 99.1 and 97.9).
 int lepton_grid(const gap_t* g) {
   return g->grid_lep_set || g->seen_l < 8LL * g->round_lep ? g->grid_lep : 2 * g->round_lep;
 }
@@ -1222,9 +1223,13 @@ void enqueue_passes(gap_t* g, bool two, bool merged) {
 }
 
 // The fused form of the particle passes (gap_fused.hpp) is for photon stores
-// of at most this many chunks (1024 slots each).  128 steps of the paper's
-// setup with 1000 to 4000 photon chunks take 7.7 ms in it and 10.6 ms in the
-// general form; 136 steps of the production gap with 13000 take 24.4 and 21.0.
+// of at most this many chunks (1024 slots each): where the forms cross depends
+// on the leptons too, and the line lies between.  A step in it and in the
+// general form: the production gap with 225 photon chunks 28 and 49 us, 3900
+// 45 and 57, 7000 (and 2600 of leptons) 65 and 67, 8200 73 and 70, 10400 88
+// and 79; the paper's setup with 6200 69 and 82, 16700 130 and 124; 8
+// QED-active tubes with 4300 lepton chunks 63 and 63 at no photons, 73 and 70
+// at 1400, 87 and 79 at 3700.
 constexpr int64_t FUSED_PHO_CHUNKS = 4096;
 
 // Whether the next step takes the fused form.  A store's chunk count, read
@@ -1232,7 +1237,7 @@ constexpr int64_t FUSED_PHO_CHUNKS = 4096;
 // taken as a sign of its size for three periods after that; a longer run
 // without such a call may have grown the store, and goes over to the general
 // form.  (No result depends on it.  With one period after it the tiny gap's
-// 500-step cascade took 2 % longer.)
+// 500-step cascade takes 14.4 to 14.8 ms instead of 11.7.)
 bool fused_form(const gap_t* g) {
   return !g->apart && g->seen_l >= 0 && g->seen_p >= 0 && g->seen_p <= FUSED_PHO_CHUNKS && g->rb_seen <= 3;
 }
@@ -1251,9 +1256,9 @@ void enqueue_fused(gap_t* g, Ctx cx, bool pre) {
   // sign only, and the grids twice what they say and at least some per tile:
   // a store may have grown since.  In a graph, which will be replayed on other
   // counts, one resident round.  (With one round also after a re-sort the tiny
-  // gap's 500-step cascade takes 13.8 ms instead of 11.7, 200 steps of the
-  // production gap's start 6.25 instead of 5.97; with pieces up to a resident
-  // round of them the latter takes 6.35.  No result depends on it.)
+  // gap's 500-step cascade takes 12.4 ms instead of 11.7, 200 steps of the
+  // production gap's start 6.37 instead of 5.89; with pieces up to a resident
+  // round of them the latter takes 6.28.  No result depends on it.)
   const bool exact = g->rb_seen == 0;
   const bool pieces = !g->capturing && g->seen_l < g->cus && g->seen_p < g->cus;
   g->form = pieces ? 2 : 1;

@@ -17,7 +17,7 @@
 //  * Waterfall (Fig. 4): the space-time diagram of E^2, the mean of E^2 over
 //    bins of cells recorded after the field update of every k-th step.
 //  * Power spectrum of E along the gap: the field zero-padded to M, the next
-//    power of two >= N, transformed by a radix-2 Stockham FFT in FP64,
+//    power of two >= N, transformed by a radix-4 Stockham FFT in FP64,
 //    P_k = |X_k|^2 / M for k = 0 .. M/2.
 #pragma once
 #include "gap_kernels.hpp"
@@ -316,9 +316,10 @@ __global__ __launch_bounds__(TPB) void k_waterfall(WfCtx w) {
   if (blockIdx.x == 0 && threadIdx.x == 0) w.steps[(size_t)t * w.cap + slot] = step;
 }
 
-// Power spectrum of E: load (zero-padded), log2 M Stockham stages (each
-// output in natural order after the last), |X|^2 / M.  One thread per pair
-// of the stage; every index is below M (M a power of two).
+// Power spectrum of E: load (zero-padded), Stockham stages of radix 4 and, for
+// an odd power of two, one of radix 2 (output in natural order after the
+// last), |X|^2 / M.  One thread per butterfly of the stage; every index is
+// below M (M a power of two).
 __global__ void k_fft_load(const float* E, int N, int M, double2* x) {
   for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < M; j += gridDim.x * blockDim.x)
     x[j] = make_double2(j < N ? (double)E[j] : 0.0, 0.0);
@@ -379,9 +380,10 @@ __global__ void k_fft_power(const double2* X, int M, double* P) {
 // per 1/8 decade of |u| and of photons per 1/8 decade of |x|, from 1e-2 to
 // 1e9, with an underflow and an overflow bin.  A value's bin is the number of
 // edges 10^(-2 + b/8) (b = 0 .. 88) whose square its square reaches, taken
-// in FP64 against a host-computed table of the squares (binary search).  Each
-// workgroup sums into an LDS histogram over a strided set of 256-slot pieces
-// of both stores and adds it to acc[3][SPEC_NB] once.
+// in FP64 against a host-computed table of the squares (spec_bin).  Each
+// workgroup sums a contiguous range of each store's sorted chunks, and its
+// share of the tails, into an LDS histogram and adds it to acc[3][SPEC_NB]
+// once.
 constexpr int SPEC_EDGES = 89;
 constexpr int SPEC_NB = SPEC_EDGES + 1;
 
