@@ -504,7 +504,7 @@ def bench_adjoint(torch, window=2000, ckpt=100):
                 forward_ms=fwd, backward_ms=bwd, plain_ms=plain, fwd_bwd_over_plain=(fwd + bwd) / plain,
                 hbm_frac=alg / ((fwd + bwd) / 1e3) / 1e9 / PEAK_HBM_GBS, bytes_fwd_bwd=alg,
                 bytes_note="forward window and its recomputation at 20 B + 8 B per evaluation per lepton-step and "
-                           "28 B per photon-step each, plus 48 B per lepton-step for the reverse step",
+                           "12 B + 12 B per draw per photon-step each, plus 48 B per lepton-step for the reverse step",
                 loss=loss, dL_dalpha=float(da[0]), dL_dninj=float(dn[0]),
                 config="16384 cells, 122 e- + 122 e+ per cell, rescaled QED, injection 0.1 n_co dx per step, "
                        "frozen QED, loss = time-averaged <E^2>")
