@@ -19,6 +19,7 @@
 #include <cstdio>
 #include <cstring>
 #include <mutex>
+#include <new>
 #include <vector>
 
 using namespace gap;
@@ -368,12 +369,15 @@ size_t up256(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
 void* dalloc(gap_t* g, size_t bytes) {
   bytes = (bytes + 255) & ~(size_t)255;
   if (bytes == 0) bytes = 256;
+  g->owned.push_back(nullptr);   // (its place first: no block is lost to a failed host allocation)
   void* p = nullptr;
   if (g->custom_alloc) p = g->al.alloc(bytes, g->al.ctx);
   else if (hipMalloc(&p, bytes) != hipSuccess) p = nullptr;
   if (p) {
-    g->owned.push_back(p);
+    g->owned.back() = p;
     (void)hipMemsetAsync(p, 0, bytes, g->s);
+  } else {
+    g->owned.pop_back();
   }
   return p;
 }
@@ -806,12 +810,15 @@ Ctl read_ctl(const Store& st);
 void* walloc(gap_t* g, size_t bytes) {
   bytes = (bytes + 255) & ~(size_t)255;
   if (bytes == 0) bytes = 256;
+  g->win.mem.push_back(nullptr);
   void* p = nullptr;
   if (g->custom_alloc) p = g->al.alloc(bytes, g->al.ctx);
   else if (hipMalloc(&p, bytes) != hipSuccess) p = nullptr;
   if (p) {
-    g->win.mem.push_back(p);
+    g->win.mem.back() = p;
     (void)hipMemsetAsync(p, 0, bytes, g->s);
+  } else {
+    g->win.mem.pop_back();
   }
   return p;
 }
@@ -1944,7 +1951,11 @@ int timed_steps(gap_t* g, int64_t n, double* kt, double* wall_ms) {
 }
 
 int autotune(gap_t* g, int trial, int32_t* chosen) {
-  const bool was = g->timing;
+  struct Timing {                     // (kernel timing as it was, however the search ends)
+    gap_t* g;
+    const bool was = g->timing;
+    ~Timing() { g->timing = was; }
+  } timing{g};
   g->timing = true;
   g->grid_lep_set = true;
   drop_graph(g);
@@ -1959,7 +1970,7 @@ int autotune(gap_t* g, int trial, int32_t* chosen) {
   Knob knobs[3] = {{&g->grid_lep, cands(g->round_lep, 8)},
                    {&g->grid_pho, cands(g->round_pho, 8)},
                    {&g->grid_tail, {g->cus * 2, g->cus * 4, g->cus * 8, g->cus * 16}}};
-  if ((e = timed_steps(g, trial, kt, &wall))) { g->timing = was; return e; }   // warm-up
+  if ((e = timed_steps(g, trial, kt, &wall))) return e;   // warm-up
   for (Knob& k : knobs) {
     double best = 1e300;
     int arg = *k.grid;
@@ -1970,7 +1981,7 @@ int autotune(gap_t* g, int trial, int32_t* chosen) {
     for (int round = 0; round < 2; ++round) {
       for (size_t ci = 0; ci < k.c.size(); ++ci) {
         *k.grid = k.c[ci];
-        if ((e = timed_steps(g, trial, kt, &wall))) { g->timing = was; return e; }
+        if ((e = timed_steps(g, trial, kt, &wall))) return e;
         tbest[ci] = std::min(tbest[ci], wall - kt[KT_RESORT]);
       }
     }
@@ -1993,13 +2004,12 @@ int autotune(gap_t* g, int trial, int32_t* chosen) {
       // only for steps actually counted since a re-sort
       g->R = r;
       const int64_t n = std::max<int64_t>(trial, 2 * (int64_t)r);
-      if ((e = timed_steps(g, n, kt, &wall))) { g->timing = was; return e; }
+      if ((e = timed_steps(g, n, kt, &wall))) return e;
       const double per = wall / (double)n;
       if (per < best) { best = per; arg = r; }
     }
     g->R = arg;
   }
-  g->timing = was;
   chosen[0] = g->grid_lep;
   chosen[1] = g->grid_pho;
   chosen[2] = g->grid_tail;
@@ -2010,6 +2020,10 @@ int autotune(gap_t* g, int trial, int32_t* chosen) {
 }  // namespace
 
 // ====================================================================== C ABI
+// Host allocations (staging, tables, records) may fail: no exception crosses
+// the ABI.
+#define GAP_NO_THROW catch (...) { return GAP_ENOMEM; }
+
 extern "C" {
 
 int gap_init(const gap_params* p, int32_t n_tubes, void* stream, const gap_allocator* alloc, gap_t** out) {
@@ -2022,7 +2036,8 @@ int gap_init(const gap_params* p, int32_t n_tubes, void* stream, const gap_alloc
   if (alloc && (!alloc->alloc || !alloc->free)) return GAP_EINVAL;
   int ndev = 0;
   if (hipGetDeviceCount(&ndev) != hipSuccess || ndev < 1) return GAP_EDEVICE;
-  gap_t* g = new gap_t();
+  gap_t* g = new (std::nothrow) gap_t();
+  if (!g) return GAP_ENOMEM;
   g->s = (hipStream_t)stream;
   {
     // this device's address of the static workspace, taken once per device
@@ -2046,7 +2061,8 @@ int gap_init(const gap_params* p, int32_t n_tubes, void* stream, const gap_alloc
     return GAP_EDEVICE;
   }
   if (alloc) { g->al = *alloc; g->custom_alloc = true; }
-  int e = build(g, p, n_tubes);
+  int e;
+  try { e = build(g, p, n_tubes); } catch (...) { e = GAP_ENOMEM; }
   if (e) {
     release(g);
     delete g;
@@ -2056,16 +2072,16 @@ int gap_init(const gap_params* p, int32_t n_tubes, void* stream, const gap_alloc
   return GAP_OK;
 }
 
-int gap_step(gap_t* g, int64_t n_steps) {
+int gap_step(gap_t* g, int64_t n_steps) try {
   if (!g || n_steps < 0) return GAP_EINVAL;
   if (g->sticky) return g->sticky;   // a reported error stops the run
   for (int64_t i = 0; i < n_steps; ++i) enqueue_step(g, i + 1 < n_steps);
   join_photon_side(g);   // the caller's stream holds all the work again
   if (hipGetLastError() != hipSuccess) return GAP_EDEVICE;
   return g->sticky;
-}
+} GAP_NO_THROW
 
-int gap_step_graph(gap_t* g, int64_t n_steps) {
+int gap_step_graph(gap_t* g, int64_t n_steps) try {
   if (!g || n_steps < 0) return GAP_EINVAL;
   if (n_steps == 0 || g->sticky) return g->sticky;
   if (g->s == nullptr) return GAP_ESTATE;   // stream capture needs a non-default stream
@@ -2085,14 +2101,14 @@ int gap_step_graph(gap_t* g, int64_t n_steps) {
   count_resorts(g, g->graph_rb);
   g->form = g->graph_form;
   return g->sticky;
-}
+} GAP_NO_THROW
 
 int gap_sync(gap_t* g) {
   if (!g) return GAP_EINVAL;
   return sync_and_err(g);
 }
 
-int gap_diag(gap_t* g, int32_t kind, int32_t tube, void* host_buf, size_t buf_bytes, size_t* bytes_written) {
+int gap_diag(gap_t* g, int32_t kind, int32_t tube, void* host_buf, size_t buf_bytes, size_t* bytes_written) try {
   if (!g || tube < 0 || tube >= g->n_tubes || (!host_buf && buf_bytes)) return GAP_EINVAL;
   int e = GAP_OK;
   // (the other kinds wait where they read)
@@ -2317,9 +2333,9 @@ int gap_diag(gap_t* g, int32_t kind, int32_t tube, void* host_buf, size_t buf_by
       (void)need;
       return refused();
   }
-}
+} GAP_NO_THROW
 
-int gap_set_state(gap_t* g, int32_t kind, int32_t tube, const void* host_buf, size_t bytes) {
+int gap_set_state(gap_t* g, int32_t kind, int32_t tube, const void* host_buf, size_t bytes) try {
   if (!g || !host_buf || tube < 0 || tube >= g->n_tubes) return GAP_EINVAL;
   if (kind == GAP_STATE_TIMING) {
     if (bytes < 4) return GAP_EINVAL;
@@ -2355,10 +2371,12 @@ int gap_set_state(gap_t* g, int32_t kind, int32_t tube, const void* host_buf, si
     const size_t nrec = (size_t)g->n_tubes * (size_t)v[2];
     auto get = [&](size_t bytes) -> void* {
       bytes = (bytes + 255) & ~(size_t)255;
+      g->wf_mem.push_back(nullptr);
       void* p = nullptr;
       if (g->custom_alloc) p = g->al.alloc(bytes, g->al.ctx);
       else if (hipMalloc(&p, bytes) != hipSuccess) p = nullptr;
-      if (p) g->wf_mem.push_back(p);
+      if (p) g->wf_mem.back() = p;
+      else g->wf_mem.pop_back();
       return p;
     };
     g->wf_ring = (double*)get(sizeof(double) * nrec * (size_t)nbmax);
@@ -2601,27 +2619,27 @@ int gap_set_state(gap_t* g, int32_t kind, int32_t tube, const void* host_buf, si
     default:
       return GAP_EINVAL;
   }
-}
+} GAP_NO_THROW
 
-int gap_autotune(gap_t* g, int32_t trial_steps, int32_t* chosen) {
+int gap_autotune(gap_t* g, int32_t trial_steps, int32_t* chosen) try {
   if (!g || trial_steps < 1 || !chosen) return GAP_EINVAL;
   int e = sync_and_err(g);
   if (e) return e;
   return autotune(g, trial_steps, chosen);
-}
+} GAP_NO_THROW
 
-int gap_window_forward(gap_t* g, int64_t window_steps, int32_t ckpt_every, double* loss) {
+int gap_window_forward(gap_t* g, int64_t window_steps, int32_t ckpt_every, double* loss) try {
   if (!g || window_steps < 1 || ckpt_every < 1 || !loss) return GAP_EINVAL;
   if (g->any_filter) return GAP_EINVAL;   // the adjoint is of the unfiltered update
   if (g->sticky) return g->sticky;
   return window_forward(g, window_steps, ckpt_every, loss);
-}
+} GAP_NO_THROW
 
-int gap_window_backward(gap_t* g, double* dL_dalpha, double* dL_dninj) {
+int gap_window_backward(gap_t* g, double* dL_dalpha, double* dL_dninj) try {
   if (!g || !dL_dalpha || !dL_dninj) return GAP_EINVAL;
   if (g->sticky) return g->sticky;
   return backward(g, dL_dalpha, dL_dninj);
-}
+} GAP_NO_THROW
 
 int gap_backward(gap_t* g, int64_t window_steps, int32_t ckpt_every, double* loss, double* dL_dalpha,
                  double* dL_dninj) {
@@ -2667,7 +2685,7 @@ int gap_e_spectrum_noalloc(gap_t* g, int32_t tube, double* power, int64_t power_
   return hipGetLastError() == hipSuccess ? GAP_OK : GAP_EDEVICE;
 }
 
-int gap_qed_sample(gap_t* g, int32_t kind, const double* chi, const uint32_t* words, int64_t n, double* out) {
+int gap_qed_sample(gap_t* g, int32_t kind, const double* chi, const uint32_t* words, int64_t n, double* out) try {
   if (!g || (kind != 0 && kind != 1) || n < 0 || (n > 0 && (!chi || !words || !out))) return GAP_EINVAL;
   if (n == 0) return GAP_OK;
   if (g->sticky) return g->sticky;
@@ -2695,9 +2713,9 @@ int gap_qed_sample(gap_t* g, int32_t kind, const double* chi, const uint32_t* wo
   if (e) return e;
   for (int64_t i = 0; i < n; ++i) out[i] = hout[i];
   return GAP_OK;
-}
+} GAP_NO_THROW
 
-int gap_sync_inverse_host(const float* r, float* xi, int64_t n) {
+int gap_sync_inverse_host(const float* r, float* xi, int64_t n) try {
   if (n < 0 || (n > 0 && (!r || !xi))) return GAP_EINVAL;
   const std::vector<float>& tab = sync_table();
   for (int64_t i = 0; i < n; ++i) {
@@ -2705,6 +2723,6 @@ int gap_sync_inverse_host(const float* r, float* xi, int64_t n) {
     xi[i] = sync_sample_host(r[i], tab.data());
   }
   return GAP_OK;
-}
+} GAP_NO_THROW
 
 }  // extern "C"

@@ -30,7 +30,18 @@ hipError_t stub_stream_synchronize(hipStream_t);
 #undef hipMemsetAsync
 #undef hipStreamSynchronize
 
-#include <vector>
+#include <new>
+
+// host allocations of at least g_fail_at bytes fail (the stand-in and the
+// recorder make none of more than about 600)
+static size_t g_fail_at = ~(size_t)0;
+void* operator new(size_t n) {
+  void* p = n >= g_fail_at ? nullptr : malloc(n ? n : 1);
+  if (!p) throw std::bad_alloc();
+  return p;
+}
+void operator delete(void* p) noexcept { free(p); }
+void operator delete(void* p, size_t) noexcept { free(p); }
 
 namespace {
 
@@ -40,9 +51,9 @@ std::map<const void*, std::string>& names() {
   static std::map<const void*, std::string> m;   // (kernels are registered before this file's globals)
   return m;
 }
-std::vector<Launch> g_launches;
-std::map<hipStream_t, std::vector<Fill>> g_fills;   // enqueued on non-blocking streams, not waited for
-std::vector<std::string> g_races;
+std::deque<Launch> g_launches;
+std::map<hipStream_t, std::deque<Fill>> g_fills;   // enqueued on non-blocking streams, not waited for
+std::deque<std::string> g_races;
 std::map<hipStream_t, long long> g_queued;          // launches since the stream was last waited for
 long long g_allocs = 0;
 long long* g_status = nullptr;                      // the library's status words: {error, chunks + 1 of both stores}
@@ -120,6 +131,7 @@ void* rec_stream(void) {
   hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
   return s;
 }
+void rec_fail_at(long long n) { g_fail_at = n < 0 ? ~(size_t)0 : (size_t)n; }
 void rec_clear(void) { g_launches.clear(); }
 long long rec_count(void) { return (long long)g_launches.size(); }
 const char* rec_name(long long i) { return g_launches[(size_t)i].name.c_str(); }

@@ -28,7 +28,7 @@ class Host:
                              ("rec_name", C.c_char_p, [C.c_longlong]), ("rec_grid", C.c_longlong, [C.c_longlong]),
                              ("rec_allocs", C.c_longlong, []), ("rec_queued", C.c_longlong, []), ("rec_races", C.c_longlong, []),
                              ("rec_race", C.c_char_p, [C.c_longlong]),
-                             ("rec_set_chunks", None, [C.c_longlong, C.c_longlong])):
+                             ("rec_fail_at", None, [C.c_longlong]), ("rec_set_chunks", None, [C.c_longlong, C.c_longlong])):
             getattr(lib, n).restype, getattr(lib, n).argtypes = res, args
         lib.gap_init.argtypes = [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.POINTER(C.c_void_p)]
         lib.gap_step.argtypes = lib.gap_step_graph.argtypes = [C.c_void_p, C.c_int64]
@@ -263,3 +263,26 @@ def test_memory_is_given_back_after_the_work_that_uses_it(host, own_stream):
     assert hip.rec_queued() > 0
     hip.gap_free(h)
     assert left and set(left) == {0}
+
+
+def test_a_failed_host_allocation_is_an_error_code(host):
+    # (no exception crosses the C ABI: thrown through ctypes it would end this process)
+    cfg = dict(workloads.PAPER, n_cells=3000, cap_leptons=1 << 16, cap_photons=1 << 16)
+    h = host.init(cfg)
+    g = C.c_void_p()
+    p = (G.GapParams * 1)(G.make_params(cfg))
+    buf = (C.c_char * (1 << 20))()
+    part = (C.c_int64 * 2)(0, 0)
+    try:
+        host.lib.rec_fail_at(1000)
+        for kind in (G.DIAG_FIELD, G.DIAG_RHO, G.DIAG_PROFILE, G.DIAG_SPECTRA, G.DIAG_ESPECTRUM):
+            assert host.lib.gap_diag(h, kind, 0, buf, 1 << 20, None) == -2, kind
+        assert host.lib.gap_init(p, 1, host.stream, None, C.byref(g)) == -2 and not g.value
+        assert host.lib.gap_set_state(h, G.STATE_FIELD, 0, buf, 12008) == -2
+        assert host.lib.gap_step(h, 2) == 0
+    finally:
+        host.lib.rec_fail_at(-1)
+    # and the handle goes on
+    assert host.lib.gap_diag(h, G.DIAG_FIELD, 0, buf, 1 << 20, None) == 0
+    assert host.lib.gap_set_state(h, G.STATE_PARTICLES, 0, part, 16) == 0
+    host.lib.gap_free(h)
